@@ -907,7 +907,9 @@ int sfm_register_images(sfm_ctx* ctx, const sfm_image* images, int32_t n_images)
     off[size_t(k) + 1] = off[size_t(k)] + s.n;
   }
   if (n_images == 0) return SFM_OK;
-  HIP_TRY(ctx, hipMalloc(&ctx->norm2_dev, std::max<size_t>(4, size_t(off.back()) * 4)));
+  // Squared norms, then the exhaustive matcher's constant terms.
+  HIP_TRY(ctx, hipMalloc(&ctx->norm2_dev, std::max<size_t>(4, size_t(off.back()) * 8)));
+  int32_t* const cword_dev = ctx->norm2_dev + off.back();
   HIP_TRY(ctx, hipMalloc(&ctx->norm_off_dev, off.size() * sizeof(int64_t)));
   HIP_TRY(ctx, hipMalloc(&ctx->images_dev, host.size() * sizeof(ImageDev)));
   for (int32_t k = 0; k < n_images; ++k) {
@@ -916,6 +918,7 @@ int sfm_register_images(sfm_ctx* ctx, const sfm_image* images, int32_t n_images)
     d.xy = images[k].xy;
     d.desc = images[k].desc;
     d.norm2 = ctx->norm2_dev + off[size_t(k)];
+    d.cword = cword_dev + off[size_t(k)];
     d.n = images[k].n;
   }
   HIP_TRY(ctx, hipMemcpy(ctx->norm_off_dev, off.data(), off.size() * sizeof(int64_t),
@@ -926,7 +929,7 @@ int sfm_register_images(sfm_ctx* ctx, const sfm_image* images, int32_t n_images)
   HIP_TRY(ctx, hipMalloc(&bad, sizeof(int32_t)));
   hipError_t e = hipMemset(bad, 0, sizeof(int32_t));
   if (e == hipSuccess)
-    e = launch_register(host.data(), ctx->images_dev, n_images, ctx->norm2_dev,
+    e = launch_register(host.data(), ctx->images_dev, n_images, ctx->norm2_dev, cword_dev,
                         ctx->norm_off_dev, nullptr, bad, nullptr);
   int32_t bad_h = 0;
   if (e == hipSuccess) e = hipMemcpy(&bad_h, bad, sizeof(int32_t), hipMemcpyDeviceToHost);

@@ -5,23 +5,33 @@
 // Work item: (pair, block of 256 queries, slice of up to 1024 targets starting
 // at a multiple of 1024).  A workgroup of four waves takes one item:
 //   - Wave w owns queries 64 w .. 64 w + 63 of the block as four 16-query
-//     tiles; their negated rows are the resident B operands of
-//     v_mfma_i32_16x16x64_i8 (two per tile: bytes 0..63 and 64..127).
+//     tiles; their rows, as signed bytes 127 - 2 q, are the resident B operands
+//     of v_mfma_i32_16x16x64_i8 (two per tile: bytes 0..63 and 64..127).
 //   - The slice's rows stream through two LDS buffers of 128 targets by LDS
 //     DMA (rows XOR-swizzled: chunk c of row r at slot c ^ (r & 7)); the next
 //     buffer loads while the current one is used, one barrier per buffer.
 //     Targets past n_b read a zero row, so their products are 0.
-//   - Per 16-target step: eight MFMAs give -q.c for 16 targets x 64 queries,
-//     then each lane folds its four results per tile into its two smallest
-//         key = ((||c||^2 - 2 q.c + 2^21) << 10) | (target mod 1024)
-//     with one v_med3_u32 and one v_min_u32 (padding targets carry the key
-//     0xFFFFFFFF).
-// Keys are unique within a slice, and at equal distance the lower index has
-// the smaller key, so a slice's smallest key names the lowest index at the
-// smallest distance.  The slice's two smallest keys of every query go to a
-// partial-result array; the merge kernel folds a query's slices in ascending
-// order (the earlier slice keeps a shared smallest distance), adds ||q||^2
-// and applies the ratio test.
+//   - Per 16-target step: eight MFMAs, whose C operand is each target's
+//     constant term ||c||^2 - 127 sum(c) + 2^21 (from registration), give
+//         ||c||^2 - 2 q.c + 2^21
+//     for 16 targets x 64 queries: sum((127 - 2 q) c) = 127 sum(c) - 2 q.c.
+//     Each lane takes the smallest of its four results per tile (v_min,
+//     v_min3) and folds it into its two smallest group keys
+//         (distance << 10) | (target mod 1024) / 4
+//     with v_lshl_add, v_med3 and v_min: 1.25 VALU instructions a comparison.
+//     A group is four consecutive targets of one lane, so groups order like
+//     their targets.  (Padding targets carry the largest distance.)
+// The slice's two smallest group keys of every query go to a partial-result
+// array; the merge kernel folds a query's slices in ascending order and looks
+// into the best group for the match and the second smallest distance.
+//
+// What bounds it: the matrix core and the VALU share most of an MFMA's
+// cycles (beside eight MFMAs about eight VALU instructions issue for free,
+// each further one costs its own cycles), and LDS operands add to that.  With
+// the key of every single product (v_lshl_add, v_med3, v_min: three VALU
+// instructions a comparison) the 16,000 x 16,000 pair took 46.0 us and a
+// staged launch of 1,770 pairs 352 us; with group keys 34 and 250 us.  Eight
+// tiles a wave halve the LDS reads but leave two waves a SIMD: 34 and 317 us.
 #include <algorithm>
 
 #include "sfm_internal.h"
@@ -97,10 +107,8 @@ __device__ __forceinline__ void dma16s(const void* base, uint32_t voff, uint32_t
 }
 #pragma clang diagnostic pop
 
-// Per-byte negation of four bytes in 0..127 (no borrow crosses a byte).
-__device__ __forceinline__ int neg_bytes(uint32_t w) {
-  return int((0x80808080u - w) ^ 0x80808080u);
-}
+// 127 - 2 q of four bytes q in 0..127, as signed bytes.
+__device__ __forceinline__ int query_bytes(uint32_t w) { return int((w << 1) ^ 0x7F7F7F7Fu); }
 
 __device__ __forceinline__ uint32_t umed3(uint32_t a, uint32_t b, uint32_t c) {
   return max(min(a, b), min(max(a, b), c));   // selects v_med3_u32
@@ -134,41 +142,59 @@ __device__ __forceinline__ void issue_rows(const uint8_t* b_desc, int32_t nb, in
   }
 }
 
-// The norm word of target j of the slice (threads 0 .. kExBuf - 1 of the
-// workgroup, one target each): ((||c||^2 + 2^21) << 10) | (j mod 1024), or
-// the largest key past n_b.
-__device__ __forceinline__ uint32_t norm_word(const int32_t* norm2, int32_t nb, int32_t j) {
-  const int32_t n = ((g_i32*)norm2)[min(j, nb - 1)];
-  return j < nb ? ((uint32_t(n) + kDistBias) << kPosBits) | uint32_t(j & (kChunk - 1)) : kKeyInf;
+// The constant term of target j of the slice (threads 0 .. kExBuf - 1 of the
+// workgroup, one target each); past n_b the largest distance.
+__device__ __forceinline__ uint32_t const_term(const int32_t* cword, int32_t nb, int32_t j) {
+  const int32_t c = ((g_i32*)cword)[min(j, nb - 1)];
+  return j < nb ? uint32_t(c) : kExKeyDistInf;
 }
 
-// Eight MFMAs of one step: -q.c for the step's 16 targets (the lane's
-// chunks of k-half 0 at a0, of k-half 1 at a1) and the wave's four query tiles.
-__device__ __forceinline__ void mfma_step(const uint8_t* a0p, const uint8_t* a1p,
-                                          const v4i (&bq)[kExTiles][2], v4i (&acc)[kExTiles]) {
-  const v4i a0 = *reinterpret_cast<const v4i*>(a0p);
-  const v4i a1 = *reinterpret_cast<const v4i*>(a1p);
+// One step's LDS operands: the lane's chunks of both k-halves of its target
+// row and the constant terms of its four targets.
+struct StepIn {
+  v4i a0, a1, c;
+};
+__device__ __forceinline__ StepIn read_step(const uint8_t* a0p, const uint8_t* a1p,
+                                            const uint32_t* cp) {
+  return {*reinterpret_cast<const v4i*>(a0p), *reinterpret_cast<const v4i*>(a1p),
+          *reinterpret_cast<const v4i*>(cp)};
+}
+
+// Eight MFMAs of one step: the biased key distances of 16 targets and the
+// wave's four query tiles (the constant terms enter as the C operand).
+__device__ __forceinline__ void mfma_step(const StepIn& in, const v4i (&bq)[kExTiles][2],
+                                          v4i (&acc)[kExTiles]) {
+#pragma unroll
+  for (int k = 0; k < kExTiles; ++k)
+    acc[k] = __builtin_amdgcn_mfma_i32_16x16x64_i8(in.a0, bq[k][0], in.c, 0, 0, 0);
+#pragma unroll
+  for (int k = 0; k < kExTiles; ++k)
+    acc[k] = __builtin_amdgcn_mfma_i32_16x16x64_i8(in.a1, bq[k][1], acc[k], 0, 0, 0);
+}
+
+// The smallest of the lane's four distances per tile, as one group key, into
+// the two smallest (gid: the group's index in the slice).
+__device__ __forceinline__ void fold_step(uint32_t gid, const v4i (&acc)[kExTiles],
+                                          uint32_t (&k1)[kExTiles], uint32_t (&k2)[kExTiles]) {
 #pragma unroll
   for (int k = 0; k < kExTiles; ++k) {
-    acc[k] = __builtin_amdgcn_mfma_i32_16x16x64_i8(a0, bq[k][0], v4i{0, 0, 0, 0}, 0, 0, 0);
-    acc[k] = __builtin_amdgcn_mfma_i32_16x16x64_i8(a1, bq[k][1], acc[k], 0, 0, 0);
+    const uint32_t m = min(min(min(uint32_t(acc[k][0]), uint32_t(acc[k][1])), uint32_t(acc[k][2])),
+                           uint32_t(acc[k][3]));
+    const uint32_t key = (m << kPosBits) + gid;
+    k2[k] = umed3(k1[k], key, k2[k]);
+    k1[k] = min(k1[k], key);
   }
 }
 
-// The lane's four results per tile into its two smallest keys (nw: the norm
-// words of the lane's four targets).
-__device__ __forceinline__ void fold_step(const uint32_t* nw, const v4i (&acc)[kExTiles],
-                                          uint32_t (&k1)[kExTiles], uint32_t (&k2)[kExTiles]) {
-  const uint4 nn = *reinterpret_cast<const uint4*>(nw);
-  const uint32_t nv[4] = {nn.x, nn.y, nn.z, nn.w};
+// Asks the scheduler for one step's MFMAs with the previous step's fold
+// between them (one MFMA keeps the matrix core busy for as long as four VALU
+// instructions issue), so a wave overlaps the two itself.
+__device__ __forceinline__ void interleave_step() {
+  __builtin_amdgcn_sched_group_barrier(0x100, 3, 0);     // the LDS reads
 #pragma unroll
-  for (int k = 0; k < kExTiles; ++k) {
-#pragma unroll
-    for (int e = 0; e < 4; ++e) {
-      const uint32_t key = nv[e] + (uint32_t(acc[k][e]) << 11);
-      k2[k] = umed3(k1[k], key, k2[k]);
-      k1[k] = min(k1[k], key);
-    }
+  for (int k = 0; k < 2 * kExTiles; ++k) {
+    __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);   // one MFMA
+    __builtin_amdgcn_sched_group_barrier(0x002, 3, 0);   // three VALU
   }
 }
 
@@ -223,15 +249,15 @@ void exhaustive_kernel(BatchView v, const int2* items, int32_t n_items, uint2* p
     qr[k][0] = *(g_nv4u*)row;
     qr[k][1] = *(g_nv4u*)(row + 64);
   }
-  uint32_t nw = tid < kExBuf ? norm_word(B.norm2, P.nb, t0 + tid) : 0u;
+  uint32_t nw = tid < kExBuf ? const_term(B.cword, P.nb, t0 + tid) : 0u;
   if (tid < kExBuf) lds.nc[0][tid] = nw;
   v4i bq[kExTiles][2];
 #pragma unroll
   for (int k = 0; k < kExTiles; ++k)
 #pragma unroll
     for (int h = 0; h < 2; ++h)
-      bq[k][h] = v4i{neg_bytes(qr[k][h].x), neg_bytes(qr[k][h].y), neg_bytes(qr[k][h].z),
-                     neg_bytes(qr[k][h].w)};
+      bq[k][h] = v4i{query_bytes(qr[k][h].x), query_bytes(qr[k][h].y), query_bytes(qr[k][h].z),
+                     query_bytes(qr[k][h].w)};
   uint32_t k1[kExTiles], k2[kExTiles];
 #pragma unroll
   for (int k = 0; k < kExTiles; ++k) k1[k] = k2[k] = kKeyInf;
@@ -246,35 +272,46 @@ void exhaustive_kernel(BatchView v, const int2* items, int32_t n_items, uint2* p
     if (more) {
       issue_rows(B.desc, P.nb, tf + kExBuf, lrows + uint32_t((cur ^ 1) * kExBuf * kDescBytes),
                  voff, w, lane);
-      if (tid < kExBuf) nw = norm_word(B.norm2, P.nb, tf + kExBuf + tid);
+      if (tid < kExBuf) nw = const_term(B.cword, P.nb, tf + kExBuf + tid);
     }
     // A wave whose queries all lie past n_a only fetches its share of the
     // buffers and meets the barriers.
     const int32_t nsteps =
         qw < P.na ? (min(kExBuf, t0 + cnt - tf) + kQueryTile - 1) / kQueryTile : 0;
     // Step i: A operand from buffer row 16 i + col, k-slices g and g + 4
-    // (chunk slots g ^ (row & 7) and that ^ 4); norm words of rows
-    // 16 i + 4 g .. + 3.  A whole buffer runs unrolled with step i + 1's
-    // MFMAs issued before step i's fold, so the matrix core's work can
-    // overlap the fold; a partial buffer (the end of b) runs step by step.
+    // (chunk slots g ^ (row & 7) and that ^ 4); constant terms of rows
+    // 16 i + 4 g .. + 3.  A whole buffer runs unrolled: step i + 2's operands
+    // are read and step i + 1's MFMAs issued around step i's fold.  A partial
+    // buffer (the end of b) runs step by step.
     const uint8_t* r0 = lds.rows[cur] + col * kDescBytes + ((g ^ (col & 7)) << 4);
     const uint8_t* r1 = lds.rows[cur] + col * kDescBytes + (((g ^ (col & 7)) ^ 4) << 4);
-    const uint32_t* nb4 = lds.nc[cur] + 4 * g;
+    const uint32_t* cp = lds.nc[cur] + 4 * g;
     constexpr int kStepBytes = kQueryTile * kDescBytes;
+    const uint32_t gid0 = uint32_t((kExBuf / 4) * f + g);   // the lane's group of step 0
     if (nsteps == kExSteps) {
       v4i acc[2][kExTiles];
-      mfma_step(r0, r1, bq, acc[0]);
+      StepIn in = read_step(r0, r1, cp);
+      mfma_step(in, bq, acc[0]);
+      in = read_step(r0 + kStepBytes, r1 + kStepBytes, cp + kQueryTile);
+      __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
       for (int i = 0; i < kExSteps; ++i) {
-        if (i + 1 < kExSteps)
-          mfma_step(r0 + (i + 1) * kStepBytes, r1 + (i + 1) * kStepBytes, bq, acc[(i + 1) & 1]);
-        fold_step(nb4 + i * kQueryTile, acc[i & 1], k1, k2);
+        StepIn next = in;
+        if (i + 2 < kExSteps)
+          next = read_step(r0 + (i + 2) * kStepBytes, r1 + (i + 2) * kStepBytes,
+                           cp + (i + 2) * kQueryTile);
+        if (i + 1 < kExSteps) mfma_step(in, bq, acc[(i + 1) & 1]);
+        fold_step(gid0 + uint32_t(4 * i), acc[i & 1], k1, k2);
+        if (i + 1 < kExSteps) interleave_step();
+        __builtin_amdgcn_sched_barrier(0);
+        in = next;
       }
     } else {
       for (int32_t i = 0; i < nsteps; ++i) {
         v4i acc[kExTiles];
-        mfma_step(r0 + i * kStepBytes, r1 + i * kStepBytes, bq, acc);
-        fold_step(nb4 + i * kQueryTile, acc, k1, k2);
+        mfma_step(read_step(r0 + i * kStepBytes, r1 + i * kStepBytes, cp + i * kQueryTile), bq,
+                  acc);
+        fold_step(gid0 + uint32_t(4 * i), acc, k1, k2);
       }
     }
     if (more) {
@@ -301,23 +338,46 @@ void exhaustive_kernel(BatchView v, const int2* items, int32_t n_items, uint2* p
   }
 }
 
-// One thread per query: fold the pair's slices in ascending order (strictly
-// smaller replaces, so the earlier slice keeps a shared smallest distance and
-// the second distance becomes equal to it), then the ratio test and the
-// per-query result (the index in b).
+// One thread per query folds the pair's slices in ascending order (strictly
+// smaller replaces, so the earlier slice keeps a shared smallest distance).
+// What the slices give is the smallest distance, the group of four targets
+// that holds it first, and the smallest distance of any other group.  The
+// group's own four distances (four lanes per query) then name the lowest index
+// at the smallest distance and complete the second smallest.  Queries that
+// fail the ratio test against the other groups alone skip that, unless every
+// query's result is asked for: the second distance could only get smaller.
 constexpr int kMergeThreads = 256;
 constexpr int kMergeBatch = 8;
+
+// Squared L2 of query row i of A and target j of B, four dot products a word.
+__device__ __forceinline__ int32_t row_dot(const uint8_t* p, const uint8_t* q) {
+  uint32_t dot = 0;
+#pragma unroll
+  for (int w = 0; w < kDescBytes / 16; ++w) {
+    const nv4u u = ((g_nv4u*)p)[w], x = ((g_nv4u*)q)[w];
+    dot = __builtin_amdgcn_udot4(u.x, x.x, dot, false);
+    dot = __builtin_amdgcn_udot4(u.y, x.y, dot, false);
+    dot = __builtin_amdgcn_udot4(u.z, x.z, dot, false);
+    dot = __builtin_amdgcn_udot4(u.w, x.w, dot, false);
+  }
+  return int32_t(dot);
+}
+
 __global__ __launch_bounds__(kMergeThreads) void exhaustive_merge_kernel(BatchView v,
                                                                          const uint2* part) {
   const int32_t p = int32_t(blockIdx.x);
   const PairDesc P = v.pairs[p];
-  const int32_t i = int32_t(blockIdx.y) * kMergeThreads + int32_t(threadIdx.x);
-  bool accept = false;
+  const int lane = threadIdx.x & 63;
+  const int32_t i0 = int32_t(blockIdx.y) * kMergeThreads + int32_t(threadIdx.x & ~63u);
+  if (i0 >= P.na) return;   // uniform over the wave
+  const int32_t i = i0 + lane;
+  const ImageDev A = v.images[P.a], B = v.images[P.b];
+  int32_t d1 = kDistInf, d2 = kDistInf, j1 = -1;
+  const int32_t nq = ((g_i32*)A.norm2)[min(i, P.na - 1)];
   if (i < P.na) {
     const int32_t nsl = (P.nb + kExSlice - 1) / kExSlice;
     const uint2* pp = part + P.ex_off + i;
     uint32_t s1 = kExKeyDistInf, s2 = kExKeyDistInf;
-    int32_t j1 = -1;
     // kMergeBatch slices' loads in flight together (clamped past the last).
     for (int32_t s0 = 0; s0 < nsl; s0 += kMergeBatch) {
       v2u kk[kMergeBatch];
@@ -331,7 +391,7 @@ __global__ __launch_bounds__(kMergeThreads) void exhaustive_merge_kernel(BatchVi
         if (kd1 < s1) {
           s2 = min(s1, kd2);
           s1 = kd1;
-          j1 = (s0 + b) * kExSlice + int32_t(kk[b].x & (kChunk - 1));
+          j1 = (s0 + b) * kExSlice + 4 * int32_t(kk[b].x & (kChunk - 1));
         } else if (kd1 == s1) {
           s2 = s1;
         } else {
@@ -339,13 +399,51 @@ __global__ __launch_bounds__(kMergeThreads) void exhaustive_merge_kernel(BatchVi
         }
       }
     }
-    const int32_t nq = v.images[P.a].norm2[i];
-    const int32_t d1 = s1 != kExKeyDistInf ? int32_t(s1) - int32_t(kDistBias) + nq : kDistInf;
-    const int32_t d2 = s2 != kExKeyDistInf ? int32_t(s2) - int32_t(kDistBias) + nq : kDistInf;
-    if (d2 != kDistInf)
-      accept = int64_t(v.ratio_den) * d1 < int64_t(v.ratio_num) * d2;
-    else
-      accept = d1 != kDistInf && v.accept_single;
+    if (s1 != kExKeyDistInf) d1 = int32_t(s1) - int32_t(kDistBias) + nq;
+    if (s2 != kExKeyDistInf) d2 = int32_t(s2) - int32_t(kDistBias) + nq;
+  }
+  const bool open = d1 != kDistInf &&
+                    (v.keep_counts || d2 == kDistInf ||
+                     int64_t(v.ratio_den) * d1 < int64_t(v.ratio_num) * d2);
+  // The open queries of the wave, sixteen at a time, four lanes each.
+  unsigned long long todo = __ballot(open);
+  while (todo) {
+    unsigned long long left = todo;   // lane's query: the (lane / 4)-th one left
+    for (int k = 0; k < (lane >> 2) && left; ++k) left &= left - 1;
+    const int src = left ? __builtin_ctzll(left) : -1;
+    const int from = max(src, 0);
+    const int32_t jj = __shfl(j1, from, 64) + (lane & 3);
+    const int32_t qn = __shfl(nq, from, 64);
+    int32_t D = kDistInf;
+    if (src >= 0 && jj < P.nb)
+      D = qn + ((g_i32*)B.norm2)[jj] -
+          2 * row_dot(A.desc + int64_t(i0 + src) * kDescBytes, B.desc + int64_t(jj) * kDescBytes);
+    // The two smallest of the four and the lowest index of the smallest.
+    int32_t w1 = D, w2 = kDistInf, wj = jj;
+#pragma unroll
+    for (int o = 1; o <= 2; o <<= 1) {
+      const int32_t e1 = __shfl_xor(w1, o, 64), e2 = __shfl_xor(w2, o, 64);
+      const int32_t ej = __shfl_xor(wj, o, 64);
+      w2 = min(max(w1, e1), min(w2, e2));
+      wj = e1 < w1 || (e1 == w1 && ej < wj) ? ej : wj;
+      w1 = min(w1, e1);
+    }
+    // Back to the query's own lane: it is number r of the queries left.
+    const int r = __builtin_popcountll(todo & ((1ull << lane) - 1));
+    const bool mine = ((todo >> lane) & 1) && r < 16;
+    const int32_t g2 = __shfl(w2, 4 * (r & 15), 64), gj = __shfl(wj, 4 * (r & 15), 64);
+    if (mine) {
+      d2 = min(d2, g2);
+      j1 = gj;
+    }
+    todo &= ~__ballot(mine);
+  }
+  bool accept = false;
+  if (d2 != kDistInf)
+    accept = int64_t(v.ratio_den) * d1 < int64_t(v.ratio_num) * d2;
+  else
+    accept = d1 != kDistInf && v.accept_single;
+  if (i < P.na) {
     QueryResult r;
     r.match = d1 != kDistInf ? j1 : -1;
     r.d1 = d1;
@@ -354,7 +452,7 @@ __global__ __launch_bounds__(kMergeThreads) void exhaustive_merge_kernel(BatchVi
     v.res[P.q_off + i] = r;
   }
   const unsigned long long m = __ballot(accept);
-  if ((threadIdx.x & 63) == 0 && m)
+  if (lane == 0 && m)
     atomicAdd(&v.counters[p].accepted, uint32_t(__builtin_popcountll(m)));
 }
 

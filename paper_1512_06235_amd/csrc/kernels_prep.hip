@@ -19,19 +19,21 @@ namespace sfm {
 namespace {
 
 // ---------------------------------------------------------------------------
-// Registration: squared norms, byte range check, keypoint bounding box.
-// One workgroup per image.
+// Registration: squared norms and the exhaustive matcher's constant terms,
+// byte range check, keypoint bounding box.  One workgroup per image.
 // ---------------------------------------------------------------------------
 __global__ __launch_bounds__(256) void register_kernel(ImageDev* imgs, int32_t* norm2_all,
+                                                       int32_t* cword_all,
                                                        const int64_t* norm_off, int32_t* bad) {
   const int k = blockIdx.x;
   const ImageDev im = imgs[k];
   int32_t* nrm = norm2_all + norm_off[k];
+  int32_t* cw = cword_all + norm_off[k];
   float mnx = INFINITY, mny = INFINITY, mxx = -INFINITY, mxy = -INFINITY;
   uint32_t orbits = 0;
   for (int32_t f = threadIdx.x; f < im.n; f += blockDim.x) {
     const uint4* row = reinterpret_cast<const uint4*>(im.desc + int64_t(f) * kDescBytes);
-    int32_t s = 0;
+    int32_t s = 0, sum = 0;
 #pragma unroll
     for (int w = 0; w < 8; ++w) {
       const uint4 v = row[w];
@@ -40,9 +42,11 @@ __global__ __launch_bounds__(256) void register_kernel(ImageDev* imgs, int32_t* 
       for (int t = 0; t < 4; ++t) {
         orbits |= d[t];
         s = __builtin_amdgcn_udot4(d[t], d[t], uint32_t(s), false);
+        sum = __builtin_amdgcn_udot4(d[t], 0x01010101u, uint32_t(sum), false);
       }
     }
     nrm[f] = s;
+    cw[f] = s - 127 * sum + int32_t(kDistBias);
     const float x = im.xy[2 * f], y = im.xy[2 * f + 1];
     if (!(isfinite(x) && isfinite(y))) orbits |= 0x80u;  // reported as invalid input
     mnx = fminf(mnx, x); mny = fminf(mny, y);
@@ -782,13 +786,13 @@ __global__ __launch_bounds__(256) void schedule_kernel(BatchView v, int32_t pb, 
 }  // namespace
 
 hipError_t launch_register(const ImageDev* imgs_host, ImageDev* imgs_dev, int32_t n_images,
-                           int32_t* norm2_all, const int64_t* norm_off, float* bbox_dev,
-                           int32_t* bad_flag, hipStream_t st) {
+                           int32_t* norm2_all, int32_t* cword_all, const int64_t* norm_off,
+                           float* bbox_dev, int32_t* bad_flag, hipStream_t st) {
   (void)imgs_host;
   (void)bbox_dev;
   if (n_images == 0) return hipSuccess;
   hipLaunchKernelGGL(register_kernel, dim3(n_images), dim3(256), 0, st, imgs_dev, norm2_all,
-                     norm_off, bad_flag);
+                     cword_all, norm_off, bad_flag);
   return hipGetLastError();
 }
 

@@ -22,6 +22,7 @@ __global__ __launch_bounds__(256) void make_views_kernel(const ImageDev* images,
     d.xy += 2 * int64_t(first);
     d.desc += 128 * int64_t(first);
     d.norm2 += first;
+    d.cword += first;
     d.n = count;
     views[i] = d;
   }

@@ -32,6 +32,7 @@ struct ImageDev {
   const float* xy;          // float2[n]
   const uint8_t* desc;      // uint8[n][128]
   const int32_t* norm2;     // int32[n], owned by the context
+  const int32_t* cword;     // int32[n], owned by the context: norm2 - 127 * (sum of the bytes) + 2^21
   int32_t n;
   int32_t pad;
   float bbox[4];            // min x, min y, max x, max y of the keypoints
@@ -322,8 +323,8 @@ int serve_match(sfm_ctx* ctx, ServeSpace* sp, const sfm_pair* pairs, int32_t n_p
 
 // Host launchers (one translation unit each).
 hipError_t launch_register(const ImageDev* imgs_host, ImageDev* imgs_dev, int32_t n_images,
-                           int32_t* norm2_all, const int64_t* norm_off, float* bbox_dev,
-                           int32_t* bad_flag, hipStream_t st);
+                           int32_t* norm2_all, int32_t* cword_all, const int64_t* norm_off,
+                           float* bbox_dev, int32_t* bad_flag, hipStream_t st);
 // Preparation of pairs [pair_begin, pair_begin + pair_count), whose tile groups
 // are [grp_begin, grp_begin + grp_count), for `wgs` match workgroups (the
 // groups are split into min(kXcds, wgs) shares of about equal cost, one per
