@@ -181,19 +181,25 @@ struct CovisArgs {
   const int32_t* vis_pts;
   int64_t nnz;
   int32_t n_images, n_points, threshold, top_k;
-  // Workspace: observers per point (counts, offsets, cursors, image ids),
-  // scan block sums, pair bits and per-row pair counts and offsets.
-  int32_t *pt_count, *pt_off, *cursor, *pt_imgs, *sums, *row_count, *row_off;
+  // Workspace: pair bits and per-row pair counts; for the histogram,
+  // observers per point (counts, offsets, cursors, image ids) and scan block
+  // sums.
+  int32_t *pt_count, *pt_off, *cursor, *pt_imgs, *sums, *row_count;
   uint32_t* bits;
-  // Bit-matrix path (when gram is not NULL): image bitsets, n x n counts.
+  // Bit-matrix path (when gram is not NULL): image bitsets
+  // (covis_bitset_words per row), then `slices` n x n count matrices.
   uint32_t* bitset;
   int32_t* gram;
+  int32_t slices;
   // Outputs.
   int32_t *cand, *n_shared, *n_cand, *pairs;
   int64_t* n_pairs;
   int32_t* err;
 };
 hipError_t launch_candidates(const CovisArgs& a, hipStream_t st);
+int64_t covis_bitset_words(int32_t n_points);
+// Slices of the points the count matrices are best split into.
+int32_t covis_gram_slices(int32_t n_images, int32_t n_points);
 
 // Device-wide prefix sums of int32 (kernels_scan.hip): out[i] = sum of in[0..i)
 // (exclusive) or in[0..i] (inclusive), in place allowed; `copy` (may be NULL)
