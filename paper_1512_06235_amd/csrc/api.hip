@@ -1066,16 +1066,22 @@ int sfm_grid_match(sfm_ctx* ctx, const sfm_pair* pairs, int32_t n_pairs, const d
                  (long long)kGridMaxCells);
         return fail(ctx, SFM_ECAPACITY, buf);
       }
-      g.cx0[t] = int32_t(fx0);
-      g.cy0[t] = int32_t(fy0);
-      g.ncx[t] = int32_t(ncx);
-      g.ncy[t] = int32_t(ncy);
-      g.cell_off[t] = cells;
-      cells += int64_t(ncx) * int64_t(ncy) + 1;
-      max_cells = std::max(max_cells, int64_t(ncx) * int64_t(ncy));
     }
+    // The d x d cells over the box (fine_cell of the binning kernel).
+    const auto fine = [&](double x) {
+      return std::floor(x / two_d) + std::floor((x - g.d) / two_d) + 1.0;
+    };
+    g.fx0 = int32_t(fine(g.box[0])) - kGridMargin;
+    g.fy0 = int32_t(fine(g.box[1])) - kGridMargin;
+    g.nfx = int32_t(fine(g.box[2])) + kGridMargin - g.fx0 + 1;
+    g.nfy = int32_t(fine(g.box[3])) + kGridMargin - g.fy0 + 1;
+    g.strip = 4 * g.nfx;
+    g.ncell = (g.nfy + 3) / 4 * g.strip;
+    g.cell_off = cells;
+    cells += (int64_t(g.ncell) + 1 + 31) & ~int64_t(31);   // tables start on 128-byte lines
+    max_cells = std::max(max_cells, int64_t(g.ncell));
     sum_na += g.na;
-    items += 4 * int64_t(g.nb);
+    items += g.nb;
   }
   if (out->capacity < sum_na) {
     char buf[128];
@@ -1099,13 +1105,31 @@ int sfm_grid_match(sfm_ctx* ctx, const sfm_pair* pairs, int32_t n_pairs, const d
   const size_t o_gp = o; o = align_up(o + P * sizeof(GridPair));
   const size_t o_pd = o; o = align_up(o + P * sizeof(PairDesc));
   const size_t o_F = o; o = align_up(o + P * 9 * sizeof(double));
+  // The block table in eight shares of about equal cost, one per XCD (workgroup
+  // k runs on XCD k mod 8): a share is a run of consecutive blocks, so an XCD
+  // works on a pair or two at a time and their descriptors stay in its L2.  A
+  // query's cost is its samples plus its candidates, about n_b / 100 of them.
   std::vector<int2> blocks;
-  int32_t max_nb = 0, max_na = 0;
-  for (size_t k = 0; k < P; ++k) {
-    for (int32_t q0 = 0; q0 < gp[k].na; q0 += kGridQueriesPerBlock)
-      blocks.push_back(make_int2(int32_t(k), q0));
-    max_nb = std::max(max_nb, gp[k].nb);
-    max_na = std::max(max_na, gp[k].na);
+  int32_t max_na = 0;
+  {
+    const auto cost = [&](const GridPair& g) { return 1000 + int64_t(g.nb) / 8; };
+    int64_t total = 0;
+    for (const GridPair& g : gp)
+      total += cost(g) * ((g.na + kGridQueriesPerBlock - 1) / kGridQueriesPerBlock);
+    std::vector<int2> share[kXcds];
+    int64_t before = 0;
+    for (size_t k = 0; k < P; ++k) {
+      for (int32_t q0 = 0; q0 < gp[k].na; q0 += kGridQueriesPerBlock) {
+        share[before * kXcds / total].push_back(make_int2(int32_t(k), q0));
+        before += cost(gp[k]);
+      }
+      max_na = std::max(max_na, gp[k].na);
+    }
+    size_t longest = 0;
+    for (const auto& s : share) longest = std::max(longest, s.size());
+    blocks.resize(longest * kXcds, make_int2(-1, 0));
+    for (size_t x = 0; x < size_t(kXcds); ++x)
+      for (size_t i = 0; i < share[x].size(); ++i) blocks[i * kXcds + x] = share[x][i];
   }
   if (blocks.size() > size_t(INT32_MAX)) return fail(ctx, SFM_ECAPACITY, "too many queries");
   const size_t o_blk = o; o = align_up(o + std::max<size_t>(blocks.size(), 1) * sizeof(int2));
@@ -1122,7 +1146,6 @@ int sfm_grid_match(sfm_ctx* ctx, const sfm_pair* pairs, int32_t n_pairs, const d
   const size_t o_sten = o; o = align_up(o + (grouped ? 3 * N * sizeof(int32_t) : 0));
   const size_t o_temp = o; o = align_up(o + temp_bytes);
   const size_t o_start = o; o = align_up(o + size_t(cells) * sizeof(int32_t));
-  const size_t o_cur = o; o = align_up(o + size_t(cells) * sizeof(int32_t));
   const size_t o_items = o; o = align_up(o + size_t(std::max<int64_t>(items, 1)) * sizeof(int32_t));
   const size_t o_res = o; o = align_up(o + size_t(std::max<int64_t>(sum_na, 1)) * sizeof(QueryResult));
   const size_t o_cnt = o; o = align_up(o + P * sizeof(PairCounters));
@@ -1151,11 +1174,10 @@ int sfm_grid_match(sfm_ctx* ctx, const sfm_pair* pairs, int32_t n_pairs, const d
   gv.pairs = reinterpret_cast<const GridPair*>(ctx->ws + o_gp);
   gv.F = reinterpret_cast<const double*>(ctx->ws + o_F);
   gv.cell_start = reinterpret_cast<int32_t*>(ctx->ws + o_start);
-  gv.cursor = reinterpret_cast<int32_t*>(ctx->ws + o_cur);
   gv.items = reinterpret_cast<int32_t*>(ctx->ws + o_items);
   gv.blocks = reinterpret_cast<const int2*>(ctx->ws + o_blk);
-  gv.bitmap_words = std::max(1, (max_nb + 31) / 32);
-  gv.lds_cells = int32_t(std::min<int64_t>(max_cells, kGridLdsCells));
+  gv.strip_cells = int32_t(std::min<int64_t>(max_cells, kGridLdsCells));
+  gv.strips = int32_t((max_cells + gv.strip_cells - 1) / gv.strip_cells);
   gv.res = reinterpret_cast<QueryResult*>(ctx->ws + o_res);
   gv.counters = reinterpret_cast<PairCounters*>(ctx->ws + o_cnt);
   gv.err = ctx->err_dev;

@@ -1,20 +1,31 @@
 // Grid-based approximate candidate search (Section 6.2.1, eqs. 4-9, and the
 // GPU steps 1, 3 and 4 of Appendix A).
 //
-// b's features are binned once per pair into four grids of 2d x 2d cells,
-// shifted by (0,0), (d,0), (0,d) and (d,d).  A query's line is cut by b's
-// keypoint box at A and B; K + 1 equidistant points are taken between them
-// (K the smallest integer with K d >= |AB|), and each point selects the
-// centre-most of the four cells that contain it.  C' is the union of the
-// features of the selected cells, made a set with a per-query bitmap in LDS;
-// the two nearest of C' by exact squared L2 and the ratio test decide the
-// match.  C' approximates the band of eq. (2): it can hold features up to 2d
-// (per axis) from a sample point and miss band members near a cell corner.
+// The paper bins b's features into four grids of 2d x 2d cells, shifted by
+// (0,0), (d,0), (0,d) and (d,d).  A query's line is cut by b's keypoint box at
+// A and B; K + 1 equidistant points are taken between them (K the smallest
+// integer with K d >= |AB|), and each point selects the centre-most of the
+// four cells that contain it.  C' is the union of the features of the selected
+// cells; the two nearest of C' by exact squared L2 and the ratio test decide
+// the match.  C' approximates the band of eq. (2): it can hold features up to
+// 2d (per axis) from a sample point and miss band members near a cell corner.
+//
+// Here b is binned once, into d x d cells: a cell of any of the four grids is a
+// block of 2 x 2 of them, and the centre-most cell of a point is the block
+// around its nearest multiple of d in x and y.  Along a line the blocks move
+// monotonically in x and in y, so the samples whose block holds a given cell
+// follow each other, and a cell is new to C' exactly when the sample before
+// did not hold it: no set needs to be kept.  (Rounding can make a line that
+// runs along a boundary between two blocks step back and forth; a query where
+// that happens compares with eight samples instead of one, see walk_robust.)
 //
 // Every floating-point decision (crossings, sample points, cells, centre
-// distances) is IEEE double with no contraction, in a fixed order, so the
-// result is reproducible bit for bit by a plain implementation of the same
-// steps.
+// distances) has the result of IEEE double with no contraction, in a fixed
+// order, so the result is reproducible bit for bit by a plain implementation
+// of the same steps.  Cells and samples are first placed by one multiplication
+// with 1 / d; where that lands within 1e-5 of a cell boundary (its error is
+// below 1e-6: coordinates are at most 2^31 cells from the origin) the steps
+// are evaluated as written.
 #include <algorithm>
 #include <cmath>
 
@@ -26,86 +37,115 @@
 namespace sfm {
 namespace {
 
-constexpr int kBinThreads = 256;
+constexpr int kBinThreads = 1024;
+constexpr double kNearEdge = 1e-5;   // cells: nearer than this to an edge, decide as written
 
-__device__ __forceinline__ double grid_shift(int g, double d, int axis) {
-  return ((g >> axis) & 1) ? d : 0.0;
+// d x d cell of coordinate x: the two 2d-wide cells (shift 0 and d) that hold x
+// are floor(x / 2d) and floor((x - d) / 2d), and these two name it.
+__device__ __forceinline__ int32_t fine_cell(double x, double d, double inv_d) {
+  const double t = x * inv_d, m = floor(t), f = t - m;
+  if (f > kNearEdge && f < 1.0 - kNearEdge) return int32_t(m);
+  const double two_d = 2.0 * d;
+  return int32_t(floor(x / two_d) + floor((x - d) / two_d) + 1.0);
 }
 
-// Cell of (x, y) in grid g of pair P, as an index into its table; -1 outside.
-// (The pair record stays in global memory: indexing its per-grid arrays
-// with a run-time grid number would otherwise put a copy in scratch.)
-__device__ __forceinline__ int64_t cell_of(const GridPair* P, int g, double x, double y) {
-  const double two_d = 2.0 * P->d;
-  const double sx = grid_shift(g, P->d, 0), sy = grid_shift(g, P->d, 1);
-  const int64_t cx = int64_t(floor((x - sx) / two_d)) - P->cx0[g];
-  const int64_t cy = int64_t(floor((y - sy) / two_d)) - P->cy0[g];
-  if (cx < 0 || cx >= P->ncx[g] || cy < 0 || cy >= P->ncy[g]) return -1;
-  return cy * P->ncx[g] + cx;
+// Cells are stored in strips of four rows, column by column within a strip:
+// cell (x, y) is 4 x + cell_row(y).  A line in any direction then touches few
+// lines of the start table (read column by column over the whole height, nearly
+// every sample was a line of its own).
+__device__ __forceinline__ int32_t cell_row(int32_t strip, int32_t y) {
+  return (y >> 2) * strip + (y & 3);
+}
+// cell_row(y + 1) from r = cell_row(y).
+__device__ __forceinline__ int32_t next_row(int32_t strip, int32_t y, int32_t r) {
+  return r + ((y & 3) == 3 ? strip - 3 : 1);
 }
 
-__device__ __forceinline__ int32_t load_count(const int32_t* p) {
-  return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+// Entry i (uniform) of a table that this kernel only reads, by scalar loads.
+template <class T>
+__device__ __forceinline__ T read_uniform(const T* table, int32_t i) {
+  static_assert(sizeof(T) % 4 == 0, "whole words");
+  typedef const __attribute__((address_space(4))) int32_t c_i32;
+  c_i32* src = (c_i32*)(table + __builtin_amdgcn_readfirstlane(i));
+  union {
+    int32_t w[sizeof(T) / 4];
+    T t;
+  } u;
+#pragma unroll
+  for (int k = 0; k < int(sizeof(T) / 4); ++k) u.w[k] = src[k];
+  return u.t;
 }
 
-// One workgroup per (pair, grid): count per cell, scan, scatter.  Features
-// of one cell land in any order; C' is a set, so the order never matters.
-// The counts live in LDS when the grid has at most v.lds_cells cells, else in
-// the HBM cursor array (atomics there are many times slower).
+// One workgroup per (pair, strip of kGridLdsCells cells in storage order):
+// counts per cell in LDS, a scan, then a scatter of the features of the strip;
+// the features of earlier strips are only counted.  Features of one cell land
+// in any order; C' is a set, so the order never matters.
 __global__ __launch_bounds__(kBinThreads) void grid_bin_kernel(GridView v) {
-  extern __shared__ int32_t lcnt[];
-  __shared__ int64_t part[kBinThreads];
-  const int32_t p = blockIdx.x >> 2, g = blockIdx.x & 3;
+  extern __shared__ int32_t cnt[];
+  __shared__ int32_t wsum[kBinThreads / 64], wbelow[kBinThreads / 64];
+  const int32_t p = blockIdx.x;
   const GridPair* P = v.pairs + p;
+  const int64_t ncell = P->ncell;
+  const int64_t c0 = int64_t(blockIdx.y) * v.strip_cells;
+  if (c0 >= ncell) return;   // uniform
+  const int32_t nc = int32_t(min(ncell - c0, int64_t(v.strip_cells)));
   const ImageDev B = v.images[P->b];
-  const int32_t nb = P->nb;
-  const int64_t ncell = int64_t(P->ncx[g]) * P->ncy[g];
-  int32_t* start = v.cell_start + P->cell_off[g];
-  int32_t* items = v.items + P->item_off + int64_t(g) * nb;
-  const bool local = ncell <= v.lds_cells;
-  int32_t* cur = local ? lcnt : v.cursor + P->cell_off[g];
-  const int t = threadIdx.x;
-  for (int64_t c = t; c < ncell; c += kBinThreads) cur[c] = 0;
+  const int32_t nb = P->nb, fx0 = P->fx0, fy0 = P->fy0, nfx = P->nfx, nfy = P->nfy;
+  const int32_t strip = P->strip;
+  const double d = P->d, inv_d = 1.0 / d;
+  int32_t* start = v.cell_start + P->cell_off + c0;
+  int32_t* items = v.items + P->item_off;
+  const int t = threadIdx.x, lane = t & 63, wave = t >> 6;
+  for (int32_t c = t; c < nc; c += kBinThreads) cnt[c] = 0;
   __syncthreads();
-  for (int32_t j = t; j < nb; j += kBinThreads) {
-    const int64_t c = cell_of(P, g, double(B.xy[2 * j]), double(B.xy[2 * j + 1]));
-    if (c < 0) {
+  // The strip's cell of feature j: negative before the strip, nc or more after
+  // it (or outside the grid).
+  auto cell_of = [&](int32_t j) -> int64_t {
+    const float2 xy = reinterpret_cast<const float2*>(B.xy)[j];
+    const int32_t cx = fine_cell(double(xy.x), d, inv_d) - fx0;
+    const int32_t cy = fine_cell(double(xy.y), d, inv_d) - fy0;
+    if (cx < 0 || cx >= nfx || cy < 0 || cy >= nfy) {
       *v.err = 1;
-      continue;
+      return nc;
     }
-    atomicAdd(&cur[c], 1);
+    return int64_t(4 * cx) + cell_row(strip, cy) - c0;
+  };
+  int32_t below = 0;
+  for (int32_t j = t; j < nb; j += kBinThreads) {
+    const int64_t c = cell_of(j);
+    if (c < 0)
+      ++below;
+    else if (c < nc)
+      atomicAdd(&cnt[c], 1);
   }
   __syncthreads();
-  // Exclusive scan: each thread owns a contiguous run of cells.  (HBM counts
-  // are read as device-scope atomics: the adds happened in L2.)
-  const int64_t chunk = (ncell + kBinThreads - 1) / kBinThreads;
-  const int64_t c0 = std::min<int64_t>(ncell, chunk * t), c1 = std::min<int64_t>(ncell, c0 + chunk);
-  int64_t sum = 0;
-  for (int64_t c = c0; c < c1; ++c) sum += local ? cur[c] : load_count(&cur[c]);
-  part[t] = sum;
-  __syncthreads();
-  for (int o = 1; o < kBinThreads; o <<= 1) {
-    const int64_t add = t >= o ? part[t - o] : 0;
-    __syncthreads();
-    part[t] += add;
-    __syncthreads();
+  // Exclusive scan: each thread owns a contiguous run of cells.
+  const int32_t chunk = (nc + kBinThreads - 1) / kBinThreads;
+  const int32_t r0 = min(nc, chunk * t), r1 = min(nc, r0 + chunk);
+  int32_t sum = 0;
+  for (int32_t c = r0; c < r1; ++c) sum += cnt[c];
+  int32_t inc = sum;
+  for (int o = 1; o < 64; o <<= 1) {
+    const int32_t y = __shfl_up(inc, o, 64);
+    if (lane >= o) inc += y;
   }
-  int64_t run = part[t] - sum;
-  for (int64_t c = c0; c < c1; ++c) {
-    const int32_t n = local ? cur[c] : load_count(&cur[c]);
-    start[c] = int32_t(run);
-    if (local)
-      cur[c] = int32_t(run);
-    else
-      __hip_atomic_store(&cur[c], int32_t(run), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  for (int o = 32; o > 0; o >>= 1) below += __shfl_xor(below, o, 64);
+  if (lane == 63) wsum[wave] = inc;
+  if (lane == 0) wbelow[wave] = below;
+  __syncthreads();
+  int32_t run = inc - sum;
+  for (int w = 0; w < kBinThreads / 64; ++w) run += wbelow[w] + (w < wave ? wsum[w] : 0);
+  for (int32_t c = r0; c < r1; ++c) {
+    const int32_t n = cnt[c];
+    start[c] = run;
+    cnt[c] = run;
     run += n;
   }
-  if (t == kBinThreads - 1) start[ncell] = int32_t(part[t]);
+  if (t == kBinThreads - 1 && c0 + nc == ncell) start[nc] = run;
   __syncthreads();
   for (int32_t j = t; j < nb; j += kBinThreads) {
-    const int64_t c = cell_of(P, g, double(B.xy[2 * j]), double(B.xy[2 * j + 1]));
-    if (c < 0) continue;
-    items[atomicAdd(&cur[c], 1)] = j;
+    const int64_t c = cell_of(j);
+    if (c >= 0 && c < nc) items[atomicAdd(&cnt[c], 1)] = j;
   }
 }
 
@@ -152,66 +192,285 @@ __device__ __forceinline__ bool line_crossings(const GridView& v, const GridPair
   return nh > 0;
 }
 
-// Walks the cells of query i of pair pr and calls on_new(j) once for every
-// feature j of C' (the bitmap, one bit per feature of b, clear on entry,
-// makes C' a set).  Lanes take the sample points k = lane, lane + 64, ...
-template <class OnNew>
-__device__ __forceinline__ void grid_walk(const GridView& v, const GridPair* P, int32_t pr,
-                                          const ImageDev& A, int32_t i, uint32_t* bitmap,
-                                          OnNew&& on_new) {
-  const int lane = threadIdx.x;
-  double xA = 0.0, yA = 0.0, xB = 0.0, yB = 0.0;
-  const bool crosses = line_crossings(v, P, pr, A, i, xA, yA, xB, yB);
-  if (!crosses || P->nb == 0) return;
-  {
-    const double dx = xB - xA, dy = yB - yA;
-    const double len2 = dx * dx + dy * dy;
-    const double d2 = P->d * P->d;
-    int64_t K = int64_t(ceil(sqrt(len2) / P->d));
-    while (K > 0 && double((K - 1) * (K - 1)) * d2 >= len2) --K;
-    while (double(K * K) * d2 < len2) ++K;
-    const double two_d = 2.0 * P->d;
-    for (int64_t k = lane; k <= K; k += 64) {
-      double px = xA, py = yA;
-      if (K > 0) {
-        const double kd = double(k), rd = double(K - k), Kd = double(K);
-        px = (kd * xA + rd * xB) / Kd;
-        py = (kd * yA + rd * yB) / Kd;
-      }
-      // Centre-most of the four cells holding the point (lower grid on ties).
-      int gsel = 0;
-      double best = INFINITY, bcx = 0.0, bcy = 0.0;
-      for (int g = 0; g < 4; ++g) {
-        const double sx = grid_shift(g, P->d, 0), sy = grid_shift(g, P->d, 1);
-        const double cx = floor((px - sx) / two_d), cy = floor((py - sy) / two_d);
-        const double ex = px - (cx * two_d + sx + P->d);
-        const double ey = py - (cy * two_d + sy + P->d);
-        const double r = ex * ex + ey * ey;
-        if (r < best) { best = r; gsel = g; bcx = cx; bcy = cy; }
-      }
-      const int64_t cx = int64_t(bcx) - P->cx0[gsel], cy = int64_t(bcy) - P->cy0[gsel];
-      if (cx < 0 || cx >= P->ncx[gsel] || cy < 0 || cy >= P->ncy[gsel]) continue;
-      const int32_t* start = v.cell_start + P->cell_off[gsel];
-      const int32_t* items = v.items + P->item_off + int64_t(gsel) * P->nb;
-      const int64_t c = cy * P->ncx[gsel] + cx;
-      for (int32_t s = start[c], e = start[c + 1]; s < e; ++s) {
-        const int32_t j = items[s];
-        const uint32_t bit = 1u << (j & 31);
-        if (atomicOr(&bitmap[j >> 5], bit) & bit) continue;
-        on_new(j);
+// A query's line between its crossings: A, B and K (K < 0: no crossing, or
+// no features of b).
+struct Segment {
+  double xA, yA, xB, yB;
+  int32_t K;
+};
+
+__device__ __forceinline__ Segment query_segment(const GridView& v, const GridPair* P, int32_t pr,
+                                                 const ImageDev& A, int32_t i) {
+  Segment s = {0.0, 0.0, 0.0, 0.0, -1};
+  if (!line_crossings(v, P, pr, A, i, s.xA, s.yA, s.xB, s.yB) || P->nb == 0) return s;
+  const double dx = s.xB - s.xA, dy = s.yB - s.yA;
+  const double len2 = dx * dx + dy * dy;
+  const double d2 = P->d * P->d;
+  int64_t K = int64_t(ceil(sqrt(len2) / P->d));
+  while (K > 0 && double((K - 1) * (K - 1)) * d2 >= len2) --K;
+  while (double(K * K) * d2 < len2) ++K;
+  s.K = int32_t(K);
+  return s;
+}
+
+// Samples of one segment.  at(k): the lower corner of the block of 2 x 2 cells
+// that sample k selects, relative to the pair's first cell.
+struct Sampler {
+  const Segment* seg;   // in LDS
+  int32_t K;
+  double d, inv_d, tx, ty, dtx, dty;
+  int32_t fx0, fy0, xmax, ymax;   // first cell; last lower corner of a block
+
+  __device__ __forceinline__ Sampler(const Segment& s, bool live, const GridPair* P)
+      : seg(&s), K(live ? s.K : -1), d(P->d), inv_d(1.0 / P->d), fx0(P->fx0), fy0(P->fy0), xmax(P->nfx - 2),
+        ymax(P->nfy - 2) {
+    const double step = K > 0 ? inv_d / double(K) : 0.0;
+    // Of a sample at m d (m an integer) the block's lower corner is cell m - 1.
+    tx = s.xB * inv_d - double(fx0 + 1);
+    ty = s.yB * inv_d - double(fy0 + 1);
+    dtx = (s.xA - s.xB) * step;
+    dty = (s.yA - s.yB) * step;
+  }
+
+  // Relative to the first cell.  (Samples lie in b's box, whose cells have a
+  // margin of two on every side: the clamp never changes one.)
+  __device__ __forceinline__ int2 corner(int32_t x, int32_t y) const {
+    return make_int2(min(max(x - fx0, 0), xmax), min(max(y - fy0, 0), ymax));
+  }
+
+  // As written: the sample point, and the centre-most of the four cells that
+  // hold it (lower grid on ties).
+  __device__ __forceinline__ int2 exact(int32_t k) const {
+    const Segment s = *seg;
+    const double two_d = 2.0 * d;
+    double px = s.xA, py = s.yA;
+    if (s.K > 0) {
+      const double kd = double(k), rd = double(s.K - k), Kd = double(s.K);
+      px = (kd * s.xA + rd * s.xB) / Kd;
+      py = (kd * s.yA + rd * s.yB) / Kd;
+    }
+    double best = INFINITY, fx = 0.0, fy = 0.0;
+    for (int g = 0; g < 4; ++g) {
+      const double sx = (g & 1) ? d : 0.0, sy = (g & 2) ? d : 0.0;
+      const double cx = floor((px - sx) / two_d), cy = floor((py - sy) / two_d);
+      const double ex = px - (cx * two_d + sx + d);
+      const double ey = py - (cy * two_d + sy + d);
+      const double r = ex * ex + ey * ey;
+      if (r < best) {
+        best = r;
+        fx = 2.0 * cx + double(g & 1);
+        fy = 2.0 * cy + double(g >> 1);
       }
     }
+    return corner(int32_t(fx), int32_t(fy));
+  }
+
+  // Relative to the first cell, from one multiplication; false where that is
+  // too near an edge to tell.  (Adding 1.5 * 2^52 rounds to an integer in the
+  // low bits.  Samples lie in b's box, which the grid's margin encloses, so no
+  // clamp is needed.)
+  __device__ __forceinline__ bool quick(int32_t k, int32_t& x, int32_t& y) const {
+    constexpr double kRound = 6755399441055744.0;
+    const double kd = double(k);
+    const double ax = __builtin_fma(kd, dtx, tx), ay = __builtin_fma(kd, dty, ty);
+    const double rx = ax + kRound, ry = ay + kRound;
+    const double ex = ax - (rx - kRound), ey = ay - (ry - kRound);
+    x = int32_t(uint32_t(__double_as_longlong(rx)));
+    y = int32_t(uint32_t(__double_as_longlong(ry)));
+    return fmax(fabs(ex), fabs(ey)) < 0.5 - kNearEdge;
+  }
+};
+
+constexpr int kListCap = 256;   // found features a query lists in LDS before they are consumed
+
+// Keeps the compiler from moving a wave's LDS accesses across this point (a
+// wave's LDS accesses are carried out in order).
+__device__ __forceinline__ void wave_lds_fence() {
+  __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+  __builtin_amdgcn_wave_barrier();
+}
+
+// The item range of a cell by its index (one 8-byte load; starts are 4-byte
+// aligned, which global loads allow).
+typedef int32_t int2u __attribute__((ext_vector_type(2), aligned(4)));
+__device__ __forceinline__ int2 cell_range(const int32_t* start, int32_t c) {
+  const int2u r = *reinterpret_cast<const __attribute__((address_space(1))) int2u*>(
+      (const __attribute__((address_space(1))) int32_t*)(start + c));
+  return make_int2(r.x, r.y);
+}
+
+// The cells that are new to C' at samples kb .. kb + kPer - 1: those of each
+// sample's block that the sample before did not hold, three at most, a fourth
+// for sample 0.  (The new column, then, where the block moved in y, the new
+// row's cells of the columns that are not new.)  Samples past the last one
+// repeat it, so nothing moves and nothing is new.  Cell 0 is in the empty
+// margin of the grid.  Selections only: as branches these took most of the
+// kernel's instructions.  step: the smallest and largest moves in x and y.
+constexpr int kPer = 6;   // 96 samples a query and chunk: three chunks for the usual 260
+constexpr int kRanges = 3 * kPer + 1;
+struct Steps {
+  int32_t lo_x, hi_x, lo_y, hi_y;
+};
+__device__ __forceinline__ void new_cells(const Sampler& S, int32_t strip, int32_t kb,
+                                          int32_t (&cell)[kRanges], Steps& step) {
+  const int32_t Kc = max(S.K, 0);
+  int32_t cx[kPer + 1], cy[kPer + 1];   // samples kb - 1 .. kb + kPer - 1
+  uint32_t edge = 0u;
+#pragma unroll
+  for (int u = 0; u <= kPer; ++u)
+    if (!S.quick(min(u ? kb - 1 + u : max(kb - 1, 0), Kc), cx[u], cy[u])) edge |= 1u << u;
+  while (edge) {
+    const int u = __builtin_ctz(edge);
+    edge &= edge - 1;
+    const int2 e = S.exact(min(max(kb - 1 + u, 0), Kc));
+#pragma unroll
+    for (int n = 0; n <= kPer; ++n) {
+      cx[n] = n == u ? e.x : cx[n];
+      cy[n] = n == u ? e.y : cy[n];
+    }
+  }
+#pragma unroll
+  for (int u = 0; u < kPer; ++u) {
+    const int32_t x = cx[u + 1], y = cy[u + 1];
+    const int32_t my = y - cy[u];
+    int32_t mx = x - cx[u];
+    step.lo_x = min(step.lo_x, mx);
+    step.hi_x = max(step.hi_x, mx);
+    step.lo_y = min(step.lo_y, my);
+    step.hi_y = max(step.hi_y, my);
+    const bool first = u == 0 && kb == 0 && S.K >= 0;
+    if (u == 0) mx = first ? 1 : mx;
+    const int32_t X0 = 4 * x, Y0 = cell_row(strip, y), Y1 = next_row(strip, y, Y0);
+    const int32_t XN = mx > 0 ? X0 + 4 : X0, YN = my > 0 ? Y1 : Y0;
+    const int32_t rowA = my != 0 ? X0 + YN : 0, rowB = my != 0 ? X0 + 4 + YN : 0;
+    cell[3 * u] = mx != 0 ? XN + Y0 : rowA;
+    cell[3 * u + 1] = mx != 0 ? XN + Y1 : rowB;
+    int32_t corner = mx != 0 ? (mx > 0 ? rowA : rowB) : 0;
+    if (u == 0) {
+      corner = first ? X0 + Y0 : corner;
+      cell[3 * kPer] = first ? X0 + Y1 : 0;
+    }
+    cell[3 * u + 2] = corner;
   }
 }
 
-// C' of query i into the LDS list `cand` (count in *ncand).
-__device__ __forceinline__ void grid_collect(const GridView& v, const GridPair* P, int32_t pr,
-                                             const ImageDev& A, int32_t i, uint32_t* bitmap,
-                                             int32_t* cand, int32_t* ncand) {
-  grid_walk(v, P, pr, A, i, bitmap, [&](int32_t j) {
-    const int32_t slot = atomicAdd(ncand, 1);
-    if (slot < kGridMaxCand) cand[slot] = j;
-  });
+// The same for one sample k, where blocks step back and forth or by two: a
+// cell is new when none of the eight samples before holds it.  (Samples more
+// than six steps apart share no cell: a cell lies within 1.5 d of its sample
+// in x and y, and K >= 2 steps are longer than d / 2.)
+__device__ __forceinline__ void new_cells_robust(const Sampler& S, int32_t strip, int32_t k,
+                                                 int32_t (&cell)[kRanges]) {
+#pragma unroll
+  for (int n = 0; n < kRanges; ++n) cell[n] = 0;
+  if (k > S.K) return;
+  int2 c = make_int2(0, 0);
+  uint32_t held = 0u;   // bit 2 a + b: cell (x + a, y + b) is not new
+  for (int32_t q = k; q >= max(0, k - 8); --q) {
+    const int2 e = S.exact(q);
+    if (q == k) {
+      c = e;
+      continue;
+    }
+#pragma unroll
+    for (int n = 0; n < 4; ++n) {
+      const int32_t x = c.x + (n >> 1) - e.x, y = c.y + (n & 1) - e.y;
+      if (x >= 0 && x <= 1 && y >= 0 && y <= 1) held |= 1u << n;
+    }
+  }
+#pragma unroll
+  for (int n = 0; n < 4; ++n)
+    if (!((held >> n) & 1u))
+      cell[n] = 4 * (c.x + (n >> 1)) + cell_row(strip, c.y + (n & 1));
+}
+
+// Walks the samples of a query's segment with W lanes and lists every feature
+// of C' once in LDS, as its position in the item array; consume(count) takes
+// a list of up to kListCap of them, when it is full and at the end (a chunk
+// that does not fit is worked out again after the list was taken).  Several
+// queries walk side by side in one wave, so lists are taken when one of them
+// is full.  Sets `back` when the blocks did not move monotonically (what was
+// listed is then not C', and `robust` is to be used).  Returns the number listed.
+template <int W, class Consume>
+__device__ __forceinline__ int32_t walk(const GridView& v, const GridPair* P, const Sampler& S,
+                                        int32_t* list, int sub, bool robust, bool& back,
+                                        Consume&& consume) {
+  const int32_t* start = v.cell_start + P->cell_off;
+  const int32_t strip = P->strip;
+  Steps step = {0, 0, 0, 0};
+  int32_t found = 0, count = 0, w0 = 0;
+  const int32_t stride = robust ? W : W * kPer;
+  for (int32_t k0 = 0;;) {
+    const bool more = __any(k0 <= S.K);
+    bool take = !more;
+    if (more) {
+      int32_t cell[kRanges];
+      if (robust)
+        new_cells_robust(S, strip, k0 + sub, cell);
+      else
+        new_cells(S, strip, k0 + kPer * sub, cell, step);
+      int2 r[kRanges];
+#pragma unroll
+      for (int n = 0; n < kRanges; ++n) r[n] = cell_range(start, cell[n]);
+      int32_t own = 0;
+#pragma unroll
+      for (int n = 0; n < kRanges; ++n) own += r[n].y - r[n].x;
+      int32_t inc = own;
+#pragma unroll
+      for (int o = 1; o < W; o <<= 1) {
+        const int32_t y = __shfl_up(inc, o, W);
+        if (sub >= o) inc += y;
+      }
+      const int32_t total = __shfl(inc, W - 1, W);
+      const int32_t left = max(total - w0, 0);
+      int32_t n_list = 0;   // how many of the chunk's features are listed now
+      if (!__any(count + left > kListCap)) {
+        n_list = left;
+      } else {
+        take = true;
+        if (!__any(count > 0)) n_list = min(left, kListCap);
+      }
+      // Positions w0 .. w0 + n_list - 1 of the chunk go to count ...
+      int32_t pos = inc - own - w0;
+      if (!__any(n_list != total)) {
+        pos += count;
+        if (own > 0) {
+#pragma unroll
+          for (int n = 0; n < kRanges; ++n)
+            for (int32_t s = r[n].x; s < r[n].y; ++s) list[pos++] = s;
+        }
+      } else if (n_list > 0 && pos < n_list && pos + own > 0) {
+#pragma unroll
+        for (int n = 0; n < kRanges; ++n)
+          for (int32_t s = r[n].x; s < r[n].y; ++s, ++pos)
+            if (pos >= 0 && pos < n_list) list[count + pos] = s;
+      }
+      const bool whole = !take;
+      if (whole) {
+        found += total;
+        k0 += stride;
+        w0 = 0;
+      } else if (!__any(count > 0)) {
+        w0 += kListCap;
+      }
+      count += n_list;
+    }
+    if (take) {
+      wave_lds_fence();
+      consume(count);
+      wave_lds_fence();
+      count = 0;
+      if (!more) break;
+    }
+  }
+  const bool odd = (step.lo_x < 0 && step.hi_x > 0) || (step.lo_y < 0 && step.hi_y > 0) ||
+                   step.lo_x < -1 || step.hi_x > 1 || step.lo_y < -1 || step.hi_y > 1;
+  // A lane sees its own samples: also steps of opposite signs on two lanes.
+  uint32_t signs = (step.lo_x < 0 ? 1u : 0u) | (step.hi_x > 0 ? 2u : 0u) |
+                   (step.lo_y < 0 ? 4u : 0u) | (step.hi_y > 0 ? 8u : 0u) | (odd ? 16u : 0u);
+#pragma unroll
+  for (int o = 1; o < W; o <<= 1) signs |= uint32_t(__shfl_xor(int32_t(signs), o, 64));
+  back = (signs & 3u) == 3u || (signs & 12u) == 12u || (signs & 16u) != 0u;
+  return found;
 }
 
 // The query's 128 descriptor bytes as 32 words, and its exact squared
@@ -288,40 +547,159 @@ __device__ __forceinline__ void grid_decide(const GridView& v, int64_t q_off, in
   grid_finish(v, q_off, pr, i, b1, b2, n);
 }
 
-// One wave per workgroup, taking up to kGridQueriesPerBlock consecutive
-// queries of one pair (an entry of the host's block table) one after the
-// other.  LDS: a bitmap with one bit per feature of the largest b of the
-// call, then kGridMaxCand candidate slots and their count.  (Computing each
-// distance in the walk, by the lane that finds the candidate, needs no list
-// but measured 10% slower: the walk's lanes diverge, the list pass does not.)
-// The occupancy hint (6 waves per SIMD) holds it to 68 VGPRs without spills;
-// with the 1,024-slot list that keeps more queries in flight (22.2 -> 19.9 ms
-// on the 500-pair batch).
-__global__ __launch_bounds__(64, 6) void grid_query_kernel(GridView v) {
-  extern __shared__ uint32_t lds[];
-  const int2 blk = v.blocks[blockIdx.x];
+// One wave per workgroup and kGridQueriesPerBlock consecutive queries of one
+// pair (an entry of the host's block table).  Lane q first cuts query q's
+// line; then each 16 lanes take one query at a time, four queries side by
+// side: they walk its samples, list the new features in LDS and compute the
+// listed features' distances.
+// C' has 30 to 300 features at the usual sizes, so 16 lanes are mostly in use
+// where 64 were half idle.  Bound by the VALU: about 45 instructions a sample
+// and lane (placing it, its new cells and their lists) and 75 for 16
+// candidates.  60 pairs (0.43 M queries, d = 4, 257 samples and about 110
+// candidates a query): 0.70 ms.  With four grids, ten FP64 divisions a sample
+// and a bitmap per query it took 2.31 ms; on the way here, lanes that read
+// whole rows (1.87 ms, every line of a row asked of the L2 eight times) and
+// pairs dealt to all XCDs at once (1.17 ms, 5 GB of L2 misses).
+constexpr int kGroupLanes = 16;
+
+// Within each four lanes: lane u's value; the value of lane ^ 1; of lane ^ 2.
+__device__ __forceinline__ int32_t quad_lane(int32_t x, int u) {
+  switch (u) {
+    case 0: return __builtin_amdgcn_mov_dpp(x, 0x00, 0xF, 0xF, true);
+    case 1: return __builtin_amdgcn_mov_dpp(x, 0x55, 0xF, 0xF, true);
+    case 2: return __builtin_amdgcn_mov_dpp(x, 0xAA, 0xF, 0xF, true);
+    default: return __builtin_amdgcn_mov_dpp(x, 0xFF, 0xF, 0xF, true);
+  }
+}
+__device__ __forceinline__ int32_t quad_swap1(int32_t x) {
+  return __builtin_amdgcn_mov_dpp(x, 0xB1, 0xF, 0xF, true);
+}
+__device__ __forceinline__ int32_t quad_swap2(int32_t x) {
+  return __builtin_amdgcn_mov_dpp(x, 0x4E, 0xF, 0xF, true);
+}
+
+__global__ __launch_bounds__(64, 4) void grid_query_kernel(GridView v) {
+  __shared__ Segment segs[kGridQueriesPerBlock];
+  __shared__ int32_t lists[64 / kGroupLanes][kListCap];
+  const int2 blk = read_uniform(v.blocks, int32_t(blockIdx.x));
   const int32_t pr = blk.x;
-  const GridPair* P = v.pairs + pr;
-  const ImageDev A = v.images[P->a], B = v.images[P->b];
+  if (pr < 0) return;   // padding of the table
+  const GridPair pair = read_uniform(v.pairs, pr);
+  const GridPair* P = &pair;
+  const ImageDev A = read_uniform(v.images, pair.a), B = read_uniform(v.images, pair.b);
   const int64_t q_off = P->q_off;
-  uint32_t* bitmap = lds;
-  int32_t* cand = reinterpret_cast<int32_t*>(lds + v.bitmap_words);
-  int32_t* ncand = cand + kGridMaxCand;
-  const int32_t words = (P->nb + 31) >> 5;
-  const int32_t i_end = min(P->na, blk.y + kGridQueriesPerBlock);
-  for (int32_t i = blk.y; i < i_end; ++i) {
-    for (int32_t w = threadIdx.x; w < words; w += 64) bitmap[w] = 0;
-    if (threadIdx.x == 0) *ncand = 0;
-    __syncthreads();
-    grid_collect(v, P, pr, A, i, bitmap, cand, ncand);
-    __syncthreads();
-    int32_t n = *ncand;
-    if (n > kGridMaxCand) {
-      if (threadIdx.x == 0) *v.err = 1;
-      n = kGridMaxCand;
+  const int32_t n_here = min(kGridQueriesPerBlock, P->na - blk.y);
+  const int lane = threadIdx.x, sub = lane & (kGroupLanes - 1), grp = lane / kGroupLanes;
+  if (lane < n_here) segs[lane] = query_segment(v, P, pr, A, blk.y + lane);
+  __syncthreads();
+  int32_t* list = lists[grp];
+  const int32_t* items = v.items + P->item_off;
+  unsigned long long comparisons = 0;
+  uint32_t accepted = 0;
+  for (int32_t q0 = 0; q0 < n_here; q0 += 64 / kGroupLanes) {
+    const bool live = q0 + grp < n_here;
+    const int32_t q = min(q0 + grp, n_here - 1), i = blk.y + q;
+    // The lane's two 16-byte chunks of the query's row.
+    const int quad = sub & 3;
+    const uint4* qd = reinterpret_cast<const uint4*>(A.desc + 128 * int64_t(i));
+    const uint4 qa = qd[quad], qb = qd[quad + 4];
+    const int32_t qn = A.norm2[i];
+    int32_t d1 = kDistInf, j1 = 0x7FFFFFFF, d2 = kDistInf, taken = 0;
+    auto consume = [&](int32_t count) {
+      // Past the limit on |C'| the first found are kept (the error flag says so).
+      count = min(count, kGridMaxCand - taken);
+      // Sixteen candidates at a time, one a lane; four lanes read a row, 64
+      // bytes a load (a lane reading whole rows asked the L2 for every line
+      // eight times), and sum their parts of its product.
+      if (count <= 0) return;
+      int32_t jn = items[list[min(sub, count - 1)]];
+      for (int32_t e0 = 0; e0 < count; e0 += kGroupLanes) {
+        const int32_t j = jn;   // the next sixteen load meanwhile
+        jn = items[list[min(e0 + kGroupLanes + sub, count - 1)]];
+        const int32_t nb2 = B.norm2[j];
+        uint4 ra[4], rb[4];
+#pragma unroll
+        for (int u = 0; u < 4; ++u) {
+          const uint4* row =
+              reinterpret_cast<const uint4*>(B.desc + 128 * int64_t(quad_lane(j, u))) + quad;
+          ra[u] = row[0];
+          rb[u] = row[4];
+        }
+        int32_t dot = 0;
+#pragma unroll
+        for (int u = 0; u < 4; ++u) {
+          uint32_t s = 0;
+          s = __builtin_amdgcn_udot4(ra[u].x, qa.x, s, false);
+          s = __builtin_amdgcn_udot4(ra[u].y, qa.y, s, false);
+          s = __builtin_amdgcn_udot4(ra[u].z, qa.z, s, false);
+          s = __builtin_amdgcn_udot4(ra[u].w, qa.w, s, false);
+          s = __builtin_amdgcn_udot4(rb[u].x, qb.x, s, false);
+          s = __builtin_amdgcn_udot4(rb[u].y, qb.y, s, false);
+          s = __builtin_amdgcn_udot4(rb[u].z, qb.z, s, false);
+          s = __builtin_amdgcn_udot4(rb[u].w, qb.w, s, false);
+          s += uint32_t(quad_swap1(int32_t(s)));
+          s += uint32_t(quad_swap2(int32_t(s)));
+          dot = quad == u ? int32_t(s) : dot;
+        }
+        const int32_t D = e0 + sub < count ? qn + nb2 - 2 * dot : kDistInf;
+        const bool first = D < d1 || (D == d1 && j < j1);
+        d2 = min(d2, first ? d1 : D);
+        j1 = first ? j : j1;
+        d1 = first ? D : d1;
+      }
+      taken += count;
+    };
+    int32_t found = 0;
+    bool again = live;   // this query is to be walked (again)
+    Sampler S(segs[q], live, P);
+    for (int pass = 0; pass < 2; ++pass) {
+      bool back;
+      const int32_t n = walk<kGroupLanes>(v, P, S, list, sub, pass != 0, back, consume);
+      if (again) found = n;
+      again = again && pass == 0 && back;
+      if (!__any(again)) break;
+      S.K = again ? S.K : -1;
+      if (again) {
+        d1 = d2 = kDistInf;
+        j1 = 0x7FFFFFFF;
+        taken = 0;
+      }
     }
-    grid_decide(v, q_off, pr, A, B, i, cand, n);
-    __syncthreads();   // the next query clears the bitmap and the list
+    // The two smallest over the query's lanes, lowest index on ties.
+#pragma unroll
+    for (int o = 1; o < kGroupLanes; o <<= 1) {
+      const int32_t e1 = __shfl_xor(d1, o, 64), ej = __shfl_xor(j1, o, 64);
+      const int32_t e2 = __shfl_xor(d2, o, 64);
+      const bool other = e1 < d1 || (e1 == d1 && ej < j1);
+      d2 = min(min(d2, e2), max(d1, e1));
+      j1 = other ? ej : j1;
+      d1 = min(d1, e1);
+    }
+    if (sub == 0 && live) {
+      if (found > kGridMaxCand) *v.err = 1;
+      const int32_t n = taken;
+      QueryResult r;
+      r.match = n > 0 ? j1 : -1;
+      r.d1 = n > 0 ? d1 : kDistInf;
+      r.d2 = n > 1 ? d2 : kDistInf;
+      bool accept = false;
+      if (n >= 2)
+        accept = int64_t(v.ratio_den) * r.d1 < int64_t(v.ratio_num) * r.d2;
+      else if (n == 1)
+        accept = v.accept_single != 0;
+      r.flags = (accept ? 1 : 0) | (v.keep_counts ? (n << 1) : 0);
+      v.res[q_off + i] = r;
+      comparisons += uint32_t(n);
+      accepted += accept ? 1u : 0u;
+    }
+  }
+  for (int o = kGroupLanes; o < 64; o <<= 1) {
+    comparisons += (unsigned long long)__shfl_xor((long long)comparisons, o, 64);
+    accepted += uint32_t(__shfl_xor(int32_t(accepted), o, 64));
+  }
+  if (lane == 0) {
+    if (comparisons) atomicAdd(&v.counters[pr].comparisons, comparisons);
+    if (accepted) atomicAdd(&v.counters[pr].accepted, accepted);
   }
 }
 
@@ -568,7 +946,9 @@ __global__ __launch_bounds__(256) void grid_gstart_kernel(GroupView g) {
 
 __global__ __launch_bounds__(64) void grid_group_query_kernel(GridView v, GroupView g,
                                                               int32_t n_groups) {
-  extern __shared__ uint32_t lds[];
+  __shared__ int32_t cand[kGridMaxCand];
+  __shared__ int32_t list[kListCap];
+  __shared__ Segment seg;
   const int32_t gi = blockIdx.x;
   const int32_t t0 = g.gstart[gi], t1 = gi + 1 < n_groups ? g.gstart[gi + 1] : g.n;
   const int32_t pr = pair_of(g.seg_begin, v.n_pairs, t0);
@@ -576,20 +956,26 @@ __global__ __launch_bounds__(64) void grid_group_query_kernel(GridView v, GroupV
   const ImageDev A = v.images[P->a], B = v.images[P->b];
   const int64_t q_off = P->q_off;
   const int32_t* order = g.val[0];
-  uint32_t* bitmap = lds;
-  int32_t* cand = reinterpret_cast<int32_t*>(lds + v.bitmap_words);
-  int32_t* ncand = cand + kGridMaxCand;
-  const int32_t words = (P->nb + 31) >> 5;
-  for (int32_t w = threadIdx.x; w < words; w += 64) bitmap[w] = 0;
-  if (threadIdx.x == 0) *ncand = 0;
+  const int32_t* items = v.items + P->item_off;
+  const int lane = threadIdx.x;
+  if (lane == 0) seg = query_segment(v, P, pr, A, int32_t(order[t0] - q_off));
   __syncthreads();
-  grid_collect(v, P, pr, A, int32_t(order[t0] - q_off), bitmap, cand, ncand);
-  __syncthreads();
-  int32_t n = *ncand;
-  if (n > kGridMaxCand) {
-    if (threadIdx.x == 0) *v.err = 1;
-    n = kGridMaxCand;
+  const Sampler S(seg, true, P);
+  int32_t n = 0;
+  auto consume = [&](int32_t count) {
+    count = min(count, kGridMaxCand - n);
+    for (int32_t e = lane; e < count; e += 64) cand[n + e] = items[list[e]];
+    n += max(count, 0);
+  };
+  int32_t found = 0;
+  for (int pass = 0; pass < 2; ++pass) {
+    bool back;
+    n = 0;
+    found = walk<64>(v, P, S, list, lane, pass != 0, back, consume);
+    if (!back) break;   // uniform
   }
+  if (found > kGridMaxCand && lane == 0) *v.err = 1;
+  __syncthreads();
   for (int32_t t = t0; t < t1; ++t) grid_decide(v, q_off, pr, A, B, int32_t(order[t] - q_off), cand, n);
 }
 
@@ -653,20 +1039,17 @@ hipError_t launch_grid_group_prepare(const GridView& v, const GroupView& g, hipS
 hipError_t launch_grid_groups(const GridView& v, const GroupView& g, int32_t n_groups,
                               hipStream_t st) {
   if (n_groups <= 0) return hipSuccess;
-  const size_t lds = sizeof(uint32_t) * (size_t(v.bitmap_words) + kGridMaxCand + 1);
-  hipLaunchKernelGGL(grid_group_query_kernel, dim3(uint32_t(n_groups)), dim3(64), lds, st, v, g,
+  hipLaunchKernelGGL(grid_group_query_kernel, dim3(uint32_t(n_groups)), dim3(64), 0, st, v, g,
                      n_groups);
   return hipGetLastError();
 }
 
 hipError_t launch_grid(const GridView& v, int64_t n_blocks, hipStream_t st) {
   if (v.n_pairs <= 0) return hipSuccess;
-  hipLaunchKernelGGL(grid_bin_kernel, dim3(4 * v.n_pairs), dim3(kBinThreads),
-                     sizeof(int32_t) * size_t(v.lds_cells), st, v);
-  if (n_blocks > 0) {
-    const size_t lds = sizeof(uint32_t) * (size_t(v.bitmap_words) + kGridMaxCand + 1);
-    hipLaunchKernelGGL(grid_query_kernel, dim3(uint32_t(n_blocks)), dim3(64), lds, st, v);
-  }
+  hipLaunchKernelGGL(grid_bin_kernel, dim3(v.n_pairs, v.strips), dim3(kBinThreads),
+                     sizeof(int32_t) * size_t(v.strip_cells), st, v);
+  if (n_blocks > 0)
+    hipLaunchKernelGGL(grid_query_kernel, dim3(uint32_t(n_blocks)), dim3(64), 0, st, v);
   return hipGetLastError();
 }
 

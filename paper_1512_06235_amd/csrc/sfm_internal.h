@@ -222,20 +222,24 @@ hipError_t launch_triangulate(int64_t n_nodes, const int32_t* label, const int32
                               int32_t* n_obs, int32_t* err, hipStream_t st);
 
 // Grid-based approximate candidate search (kernels_grid.hip).
-constexpr int32_t kGridMaxTargets = 65536;            // features of b (one LDS bit each)
-constexpr int32_t kGridMaxCand = 1024;                // |C'| per query (LDS slots)
-constexpr int32_t kGridQueriesPerBlock = 16;          // queries one workgroup takes in turn
+constexpr int32_t kGridMaxTargets = 65536;            // features of b
+constexpr int32_t kGridMaxCand = 1024;                // |C'| per query
+constexpr int32_t kGridQueriesPerBlock = 32;          // queries of one workgroup (at most 64)
 constexpr int64_t kGridMaxCells = int64_t(1) << 22;   // cells of one grid of one pair
 
-// Per pair, filled on the host: the four grids over b's keypoint box.
+// Per pair, filled on the host: the d x d cells over b's keypoint box with an
+// empty margin of two (kGridMargin), stored in strips of four rows.
+constexpr int32_t kGridMargin = 2;
 struct GridPair {
   int32_t a, b, na, nb;
   int64_t q_off;            // into per-query results
-  int64_t item_off;         // into the binned feature lists (4 nb per pair)
-  int64_t cell_off[4];      // into the cell tables (cells + 1 per grid)
-  int32_t cx0[4], cy0[4];   // first cell of each grid
-  int32_t ncx[4], ncy[4];   // cells of each grid
-  double d;                 // cell parameter: cells are 2d x 2d, grids shifted by d
+  int64_t item_off;         // into the binned feature lists (nb per pair)
+  int64_t cell_off;         // into the cell table (ncell + 1 per pair)
+  int32_t fx0, fy0;         // first cell
+  int32_t nfx, nfy;         // cells
+  int32_t ncell;            // cells of whole strips
+  int32_t strip;            // cells of a strip
+  double d;                 // cell parameter
   double box[4];            // min x, min y, max x, max y of b's keypoints
 };
 
@@ -243,9 +247,8 @@ struct GridView {
   const ImageDev* images;
   const GridPair* pairs;
   const double* F;          // 9 per pair, as given
-  int32_t* cell_start;      // per grid: cells + 1 starts
-  int32_t* cursor;          // per grid: counts, then fill positions
-  int32_t* items;           // feature indices of b ordered by cell, per grid
+  int32_t* cell_start;      // per pair: cells + 1 starts
+  int32_t* items;           // per pair: feature indices of b ordered by cell
   const int2* blocks;       // per query workgroup: (pair, first query)
   QueryResult* res;
   PairCounters* counters;
@@ -254,13 +257,13 @@ struct GridView {
   int32_t ratio_num, ratio_den;
   int32_t accept_single;
   int32_t keep_counts;
-  int32_t bitmap_words;     // ceil(largest n_b of the call / 32)
-  int32_t lds_cells;        // cell counts the binning keeps in LDS (larger grids use HBM)
+  int32_t strip_cells;      // cells one binning workgroup counts in LDS
+  int32_t strips;           // strips of the call's largest grid
 };
-constexpr int32_t kGridLdsCells = 15360;              // 60 KB of LDS counts (64 KB with the scan)
-// Bins b's features into the four grids of every pair, then finds C', the
-// two nearest candidates and the ratio test for every query (n_blocks
-// entries of the block table; 0 = binning only).
+constexpr int32_t kGridLdsCells = 15360;              // 60 KB of LDS counts: two workgroups per CU
+// Bins b's features into the cells of every pair, then finds C', the two
+// nearest candidates and the ratio test for every query (n_blocks entries of
+// the block table; 0 = binning only).
 hipError_t launch_grid(const GridView& v, int64_t n_blocks, hipStream_t st);
 
 // Query grouping (Section 6.2.2): buffers over the n query positions of a
