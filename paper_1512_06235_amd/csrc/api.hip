@@ -37,9 +37,8 @@ struct sfm_ctx {
   int32_t n_images = 0;
   std::vector<int32_t> n_host;
   std::vector<float> bbox_host;        // 4 per image: min x, min y, max x, max y
-  ImageDev* images_dev = nullptr;
-  int32_t* norm2_dev = nullptr;
-  int64_t* norm_off_dev = nullptr;
+  ImageDev* images_dev = nullptr;      // the image table, and in the same allocation
+                                       // everything its entries own
 
   // Workspace and its host staging.
   char* ws = nullptr;
@@ -140,9 +139,9 @@ Layout plan(const PairDesc* pd, size_t P, int32_t device, int32_t group_tiles,
   L.F = o; o = align_up(o + P * 9 * sizeof(double));
   L.order = o; o = align_up(o + P * sizeof(int32_t));
   L.items = o; o = align_up(o + size_t(n_items) * sizeof(int2));
+  L.counters = o; o = align_up(o + P * sizeof(PairCounters));   // staged as zeros
   L.staged = o;
   L.geom = o; o = align_up(o + P * sizeof(PairGeom));
-  L.counters = o; o = align_up(o + P * sizeof(PairCounters));
   L.wgs = match_workgroups(device, group_tiles, L.sum_groups);
   L.wg_start = o; o = align_up(o + size_t(L.wgs + 1) * sizeof(int32_t));
   L.cand_x = o; o = align_up(o + size_t(L.sum_nc) * sizeof(float));
@@ -307,6 +306,7 @@ struct GraphKey {
   BatchView v;
   sfm_matches out;
   int32_t n_pairs, sum_groups, wgs, max_na;
+  int32_t direct, per_wave;   // the direct form and its queries per wave
   const int32_t* order;
 };
 
@@ -328,9 +328,12 @@ int replay_batched(sfm_ctx* ctx, const GraphKey& key, int32_t* am, int32_t* ad1,
     const BatchView& v = key.v;
     const sfm_matches& out = key.out;
     HIP_TRY(ctx, hipStreamBeginCapture(cs, hipStreamCaptureModeThreadLocal));
-    const hipError_t e1 = launch_prepare(v, 0, key.n_pairs, 0, key.sum_groups, key.wgs, key.order,
-                                         key.max_na, cs);
-    const hipError_t e2 = launch_match(v, key.sum_groups > 0 ? key.wgs : 0, cs);
+    const hipError_t e1 =
+        key.direct ? launch_direct(v, 0, key.n_pairs, key.max_na, key.per_wave, cs)
+                   : launch_prepare(v, 0, key.n_pairs, 0, key.sum_groups, key.wgs, key.order,
+                                    key.max_na, cs);
+    const hipError_t e2 =
+        key.direct ? hipSuccess : launch_match(v, key.sum_groups > 0 ? key.wgs : 0, cs);
     const hipError_t e3 = launch_emit(v, 0, key.n_pairs, out.offset, out.query, out.match, out.d1,
                                       out.d2, out.n_comparisons, out.n_borderline, am, ad1, ad2, ac, cs);
     hipGraph_t g = nullptr;
@@ -459,6 +462,70 @@ void binning_order(const PairDesc* pd, int32_t n_pairs, int32_t* ord) {
   });
 }
 
+// True when the epipole of b lies in or near b's keypoint box bb, where the
+// binned form scans all of b (setup_pair in kernels_prep.hip; only speed depends
+// on this).  half: half the band's width.
+bool epipole_near_box(const double* F, const float* bb, double half) {
+  double best = 0.0, e[3] = {0.0, 0.0, 0.0};
+  for (int p = 0; p < 3; ++p) {   // the best-conditioned pair of columns
+    const int i = p == 2 ? 1 : 0, j = p == 0 ? 1 : 2;
+    const double x = F[3 + i] * F[6 + j] - F[6 + i] * F[3 + j];
+    const double y = F[6 + i] * F[j] - F[i] * F[6 + j];
+    const double z = F[i] * F[3 + j] - F[3 + i] * F[j];
+    const double n = x * x + y * y + z * z;
+    if (n > best) {
+      best = n;
+      e[0] = x;
+      e[1] = y;
+      e[2] = z;
+    }
+  }
+  if (!(best > 0.0)) return true;
+  if (std::fabs(e[2]) <= 1e-12 * std::hypot(e[0], e[1])) return false;
+  const double ex = e[0] / e[2], ey = e[1] / e[2];
+  const double ux = 0.5 * (double(bb[0]) + bb[2]) - ex, uy = 0.5 * (double(bb[1]) + bb[3]) - ey;
+  const double un = std::hypot(ux, uy);
+  double vmin = INFINITY;
+  for (int c = 0; c < 4; ++c)
+    vmin = std::min(vmin, ((bb[(c & 1) * 2] - ex) * ux + (bb[(c >> 1) * 2 + 1] - ey) * uy) / un);
+  return !(vmin > std::max(1.0, 4.0 * half));
+}
+
+// Whether pairs [0, n) of pd, with matrices F, are matched directly
+// (kernels_direct.hip) or binned, by estimates in microseconds fitted to both
+// forms on 42 calls: 1 pair of 300 to 32,000 features (band 2, 4 and 8 px), 2 to
+// 200 pairs of 300 to 16,000, epipoles inside the image.  (Calls of one
+// process, direct against binned: a pair of 300 features 22 / 43 us, 2,000:
+// 27 / 50, 8,000: 45 / 63, 16,000: 77 / 88; 16,000 with an 8 px band 101 / 97,
+// 24,000: 136 / 107; 37 pairs of 500: 32 / 52, of 301 to 6,007: 96 / 80;
+// epipole inside the image, 7,000: 44 / 439.)
+bool direct_pays(const sfm_ctx* ctx, const PairDesc* pd, const double* F, int32_t n,
+                 double margin) {
+  // The binned form counts borderline slots within its windows, which are
+  // kBandSlackPx wider than the band.
+  if (margin > 0.5 * kBandSlackPx) return false;
+  double cost = 0.0, binned = 43.0, side = 0.0;
+  for (int32_t k = 0; k < n; ++k) {
+    const PairDesc& P = pd[k];
+    if (P.nb > kDirectMaxTargets) return false;
+    const float* bb = &ctx->bbox_host[4 * size_t(P.b)];
+    const double w = std::max(1.0, double(bb[2]) - double(bb[0]));
+    const double h = std::max(1.0, double(bb[3]) - double(bb[1]));
+    // The share of b's features in a band as long as the box is wide or high,
+    // and the boxes it crosses.
+    const double share = std::min(1.0, 2.0 * P.band * std::max(w, h) / (w * h));
+    const double boxes = double(P.nb) / kBoxFeatures;
+    const double hit = std::min(boxes, 2.0 * std::sqrt(boxes) + share * boxes);
+    cost += double(P.na) * (60.0 + 3.0 * hit + 1.5 * share * double(P.nb));
+    side = std::max(side, double(std::max(P.na, P.nb)));
+    binned += 2.2e-4 * P.na;
+    if (!(P.band < 1e30) || epipole_near_box(F + 9 * size_t(k), bb, P.band + kBandSlackPx))
+      binned += 3e-6 * double(P.na) * double(P.nb);
+    if (21.0 + 7.5e-6 * cost > 400.0 + binned) return false;   // large batches end here soon
+  }
+  return 21.0 + 7.5e-6 * cost < binned + 2.5e-3 * side;
+}
+
 // One matching call over the images of `tab`; the caller holds ctx->mu.
 // kBandError runs the preparation and the FP32-accuracy diagnostic instead
 // of matching (`out` is unused; diag receives the two result words).
@@ -519,10 +586,15 @@ int match_locked(sfm_ctx* ctx, const ImageTable& tab, const sfm_pair* pairs, int
     memcpy((*S.pinned) + L.F, F, pd.size() * 9 * sizeof(double));
   }
   binning_order(pd.data(), n_pairs, reinterpret_cast<int32_t*>((*S.pinned) + L.order));
+  memset((*S.pinned) + L.counters, 0, pd.size() * sizeof(PairCounters));
   HIP_TRY(ctx, hipMemcpyAsync((*S.ws), (*S.pinned), L.staged, hipMemcpyHostToDevice, st));
   HIP_TRY(ctx, hipEventRecord(S.staging_done, st));
 
-  const BatchView v = batch_view(ctx, tab, (*S.ws), L, n_pairs, opt);
+  BatchView v = batch_view(ctx, tab, (*S.ws), L, n_pairs, opt);
+  const bool direct = form == Form::kBatched &&
+                      direct_pays(ctx, pd.data(), F, n_pairs, opt.recheck_margin_px);
+  const int32_t per_wave = direct_queries(L.sum_na);
+  if (direct) v.cand_j = nullptr;   // results hold the index in b
 
   // The layout of a batched call, for graph replay.
   const bool replay = !alt && ctx->graph_replay && !ctx->profiling && form == Form::kBatched;
@@ -534,6 +606,8 @@ int match_locked(sfm_ctx* ctx, const ImageTable& tab, const sfm_pair* pairs, int
     key.n_pairs = n_pairs;
     key.sum_groups = int32_t(L.sum_groups);
     key.wgs = L.wgs;
+    key.direct = direct ? 1 : 0;
+    key.per_wave = per_wave;
     for (const PairDesc& pp : pd) key.max_na = std::max(key.max_na, pp.na);
     key.order = reinterpret_cast<const int32_t*>((*S.ws) + L.order);
     if (!opt.emit_all) {
@@ -554,13 +628,21 @@ int match_locked(sfm_ctx* ctx, const ImageTable& tab, const sfm_pair* pairs, int
   } else if (form == Form::kPlain) {
     for (int32_t p = 0; p < n_pairs; ++p) {
       HIP_TRY(ctx, prof_mark(ctx, st));
-      const int32_t g0 = int32_t(pd[size_t(p)].grp_off), gn = pd[size_t(p)].ngroups;
-      const int32_t wgs = match_workgroups(ctx->device, ctx->group_tiles, gn);
-      HIP_TRY(ctx, launch_prepare(v, p, 1, g0, gn, wgs, nullptr, pd[size_t(p)].na, st));
+      const PairDesc& pp = pd[size_t(p)];
+      BatchView vp = v;
+      if (direct_pays(ctx, &pp, F + 9 * size_t(p), 1, opt.recheck_margin_px)) {
+        vp.cand_j = nullptr;
+        HIP_TRY(ctx, prof_mark(ctx, st));
+        HIP_TRY(ctx, launch_direct(vp, p, 1, pp.na, direct_queries(pp.na), st));
+      } else {
+        const int32_t g0 = int32_t(pp.grp_off), gn = pp.ngroups;
+        const int32_t wgs = match_workgroups(ctx->device, ctx->group_tiles, gn);
+        HIP_TRY(ctx, launch_prepare(v, p, 1, g0, gn, wgs, nullptr, pp.na, st));
+        HIP_TRY(ctx, prof_mark(ctx, st));
+        HIP_TRY(ctx, launch_match(v, gn > 0 ? wgs : 0, st));
+      }
       HIP_TRY(ctx, prof_mark(ctx, st));
-      HIP_TRY(ctx, launch_match(v, gn > 0 ? wgs : 0, st));
-      HIP_TRY(ctx, prof_mark(ctx, st));
-      HIP_TRY(ctx, launch_emit(v, p, 1, out->offset, out->query, out->match, out->d1, out->d2,
+      HIP_TRY(ctx, launch_emit(vp, p, 1, out->offset, out->query, out->match, out->d1, out->d2,
                                out->n_comparisons, out->n_borderline, am, ad1, ad2, ac, st));
       HIP_TRY(ctx, prof_mark(ctx, st));
     }
@@ -588,12 +670,16 @@ int match_locked(sfm_ctx* ctx, const ImageTable& tab, const sfm_pair* pairs, int
       ctx->last_key.assign(kb, kb + sizeof key);
     }
     HIP_TRY(ctx, prof_mark(ctx, st));
-    int32_t max_na = 0;
-    for (const PairDesc& pp : pd) max_na = std::max(max_na, pp.na);
-    HIP_TRY(ctx, launch_prepare(v, 0, n_pairs, 0, int32_t(L.sum_groups), L.wgs,
-                                reinterpret_cast<const int32_t*>((*S.ws) + L.order), max_na, st));
-    HIP_TRY(ctx, prof_mark(ctx, st));
-    HIP_TRY(ctx, launch_match(v, L.sum_groups > 0 ? L.wgs : 0, st));
+    if (direct) {
+      HIP_TRY(ctx, prof_mark(ctx, st));
+      HIP_TRY(ctx, launch_direct(v, 0, n_pairs, L.max_na, per_wave, st));
+    } else {
+      HIP_TRY(ctx, launch_prepare(v, 0, n_pairs, 0, int32_t(L.sum_groups), L.wgs,
+                                  reinterpret_cast<const int32_t*>((*S.ws) + L.order), L.max_na,
+                                  st));
+      HIP_TRY(ctx, prof_mark(ctx, st));
+      HIP_TRY(ctx, launch_match(v, L.sum_groups > 0 ? L.wgs : 0, st));
+    }
     HIP_TRY(ctx, prof_mark(ctx, st));
     HIP_TRY(ctx, launch_emit(v, 0, n_pairs, out->offset, out->query, out->match, out->d1,
                              out->d2, out->n_comparisons, out->n_borderline, am, ad1, ad2, ac,
@@ -622,8 +708,8 @@ int run_match(sfm_ctx* ctx, const sfm_pair* pairs, int32_t n_pairs, const double
 constexpr int kMaxScratchDevices = 64;
 // plan()'s staged prefix (pairs, F, order) at the most pairs a call takes.
 constexpr size_t kNoAllocStageBytes =
-    3 * kAlign +
-    size_t(SFM_NOALLOC_MAX_PAIRS) * (sizeof(PairDesc) + 9 * sizeof(double) + sizeof(int32_t));
+    4 * kAlign + size_t(SFM_NOALLOC_MAX_PAIRS) * (sizeof(PairDesc) + 9 * sizeof(double) +
+                                                  sizeof(int32_t) + sizeof(PairCounters));
 
 struct ScratchDevice {
   char* ptr = nullptr;           // device address of this GPU's `scratch`
@@ -709,18 +795,22 @@ int noalloc_locked(sfm_ctx* ctx, const sfm_pair* pairs, int32_t n_pairs, const d
   char* ws = ctx->noalloc_scratch;
   memcpy(g_stage + L.F, F, size_t(n_pairs) * 9 * sizeof(double));
   binning_order(pd, n_pairs, reinterpret_cast<int32_t*>(g_stage + L.order));
+  memset(g_stage + L.counters, 0, size_t(n_pairs) * sizeof(PairCounters));
   HIP_TRY(ctx, hipMemcpyAsync(ws, g_stage, L.staged, hipMemcpyHostToDevice, st));
   HIP_TRY(ctx, hipEventRecord(sd.staged, st));
   g_stage_device = ctx->device;
 
-  // The geometry kernel zeroes the per-pair counters; every other section is
+  // The staging copy zeroes the per-pair counters; every other section is
   // written before it is read, so nothing left by an earlier call is used.
-  const BatchView v = batch_view(ctx, registered(ctx), ws, L, n_pairs, opt);
-  int32_t max_na = 0;
-  for (int32_t k = 0; k < n_pairs; ++k) max_na = std::max(max_na, pd[k].na);
-  HIP_TRY(ctx, launch_prepare(v, 0, n_pairs, 0, int32_t(L.sum_groups), L.wgs,
-                              reinterpret_cast<const int32_t*>(ws + L.order), max_na, st));
-  HIP_TRY(ctx, launch_match(v, L.sum_groups > 0 ? L.wgs : 0, st));
+  BatchView v = batch_view(ctx, registered(ctx), ws, L, n_pairs, opt);
+  if (direct_pays(ctx, pd, F, n_pairs, opt.recheck_margin_px)) {
+    v.cand_j = nullptr;
+    HIP_TRY(ctx, launch_direct(v, 0, n_pairs, L.max_na, direct_queries(L.sum_na), st));
+  } else {
+    HIP_TRY(ctx, launch_prepare(v, 0, n_pairs, 0, int32_t(L.sum_groups), L.wgs,
+                                reinterpret_cast<const int32_t*>(ws + L.order), L.max_na, st));
+    HIP_TRY(ctx, launch_match(v, L.sum_groups > 0 ? L.wgs : 0, st));
+  }
   const bool ea = opt.emit_all != 0;
   HIP_TRY(ctx, launch_emit(v, 0, n_pairs, out->offset, out->query, out->match, out->d1, out->d2,
                            out->n_comparisons, out->n_borderline, ea ? out->all_match : nullptr,
@@ -857,11 +947,7 @@ int sfm_create(sfm_ctx** out, int32_t device, size_t budget) {
 
 static void free_registration(sfm_ctx* ctx) {
   if (ctx->images_dev) (void)hipFree(ctx->images_dev);
-  if (ctx->norm2_dev) (void)hipFree(ctx->norm2_dev);
-  if (ctx->norm_off_dev) (void)hipFree(ctx->norm_off_dev);
   ctx->images_dev = nullptr;
-  ctx->norm2_dev = nullptr;
-  ctx->norm_off_dev = nullptr;
   ctx->n_images = 0;
   ctx->n_host.clear();
   ctx->bbox_host.clear();
@@ -896,7 +982,7 @@ int sfm_register_images(sfm_ctx* ctx, const sfm_image* images, int32_t n_images)
   if (ctx->has_work) HIP_TRY(ctx, hipEventSynchronize(ctx->work_done));
   free_registration(ctx);
   std::vector<ImageDev> host(static_cast<size_t>(n_images));
-  std::vector<int64_t> off(size_t(n_images) + 1, 0);
+  size_t total = 0, outers = 0;   // features, outer boxes of whole images
   for (int32_t k = 0; k < n_images; ++k) {
     const sfm_image& s = images[k];
     if (s.n < 0 || (s.n > 0 && (!s.xy || !s.desc))) {
@@ -904,50 +990,58 @@ int sfm_register_images(sfm_ctx* ctx, const sfm_image* images, int32_t n_images)
       snprintf(buf, sizeof buf, "image %d: bad pointers or size", k);
       return fail(ctx, SFM_EINVAL, buf);
     }
-    off[size_t(k) + 1] = off[size_t(k)] + s.n;
+    total += size_t(s.n);
+    outers += (size_t(s.n) + kOuterFeatures - 1) / kOuterFeatures;
   }
   if (n_images == 0) return SFM_OK;
-  // Squared norms, then the exhaustive matcher's constant terms.
-  HIP_TRY(ctx, hipMalloc(&ctx->norm2_dev, std::max<size_t>(4, size_t(off.back()) * 8)));
-  int32_t* const cword_dev = ctx->norm2_dev + off.back();
-  HIP_TRY(ctx, hipMalloc(&ctx->norm_off_dev, off.size() * sizeof(int64_t)));
-  HIP_TRY(ctx, hipMalloc(&ctx->images_dev, host.size() * sizeof(ImageDev)));
+  // One allocation: the table and the flag of bad input, squared norms and
+  // constant terms, and the spatial orders.
+  const size_t feats = outers * kOuterFeatures;
+  size_t o = 0;
+  o += host.size() * sizeof(ImageDev);
+  const size_t o_bad = o; o = align_up(o + sizeof(int32_t));
+  const size_t o_norm2 = o; o = align_up(o + total * sizeof(int32_t));
+  const size_t o_cword = o; o = align_up(o + total * sizeof(int32_t));
+  const size_t o_outer = o; o = align_up(o + outers * sizeof(float4));
+  const size_t o_box = o; o = align_up(o + outers * kOuterBoxes * sizeof(float4));
+  const size_t o_sxy = o; o = align_up(o + feats * sizeof(float2));
+  const size_t o_sj = o; o = align_up(o + feats * sizeof(int32_t));
+  char* base = nullptr;
+  HIP_TRY(ctx, hipMalloc(&base, o));
+  ctx->images_dev = reinterpret_cast<ImageDev*>(base);
+  std::vector<char> table(o_bad + sizeof(int32_t), 0);
+  size_t at = 0, ob = 0;
   for (int32_t k = 0; k < n_images; ++k) {
     ImageDev& d = host[size_t(k)];
     memset(&d, 0, sizeof d);
     d.xy = images[k].xy;
     d.desc = images[k].desc;
-    d.norm2 = ctx->norm2_dev + off[size_t(k)];
-    d.cword = cword_dev + off[size_t(k)];
+    d.norm2 = reinterpret_cast<int32_t*>(base + o_norm2) + at;
+    d.cword = reinterpret_cast<int32_t*>(base + o_cword) + at;
+    d.outer = reinterpret_cast<float4*>(base + o_outer) + ob;
+    d.box = reinterpret_cast<float4*>(base + o_box) + ob * kOuterBoxes;
+    d.sxy = reinterpret_cast<float2*>(base + o_sxy) + ob * kOuterFeatures;
+    d.sj = reinterpret_cast<int32_t*>(base + o_sj) + ob * kOuterFeatures;
     d.n = images[k].n;
+    at += size_t(d.n);
+    ob += (size_t(d.n) + kOuterFeatures - 1) / kOuterFeatures;
   }
-  HIP_TRY(ctx, hipMemcpy(ctx->norm_off_dev, off.data(), off.size() * sizeof(int64_t),
-                         hipMemcpyHostToDevice));
-  HIP_TRY(ctx, hipMemcpy(ctx->images_dev, host.data(), host.size() * sizeof(ImageDev),
-                         hipMemcpyHostToDevice));
-  int32_t* bad = nullptr;
-  HIP_TRY(ctx, hipMalloc(&bad, sizeof(int32_t)));
-  hipError_t e = hipMemset(bad, 0, sizeof(int32_t));
+  memcpy(table.data(), host.data(), o_bad);
+  hipError_t e = hipMemcpy(base, table.data(), table.size(), hipMemcpyHostToDevice);
   if (e == hipSuccess)
-    e = launch_register(host.data(), ctx->images_dev, n_images, ctx->norm2_dev, cword_dev,
-                        ctx->norm_off_dev, nullptr, bad, nullptr);
-  int32_t bad_h = 0;
-  if (e == hipSuccess) e = hipMemcpy(&bad_h, bad, sizeof(int32_t), hipMemcpyDeviceToHost);
-  (void)hipFree(bad);
+    e = launch_register(ctx->images_dev, n_images, reinterpret_cast<int32_t*>(base + o_bad), nullptr);
+  if (e == hipSuccess) e = hipMemcpy(table.data(), base, table.size(), hipMemcpyDeviceToHost);
   if (e != hipSuccess) {
     free_registration(ctx);
     return hip_fail(ctx, e, "image registration");
   }
-  if (bad_h) {
+  int32_t bad = 0;
+  memcpy(&bad, table.data() + o_bad, sizeof bad);
+  if (bad) {
     free_registration(ctx);
     return fail(ctx, SFM_EINVAL, "a descriptor byte exceeds 127 or a keypoint is not finite");
   }
-  e = hipMemcpy(host.data(), ctx->images_dev, host.size() * sizeof(ImageDev),
-                hipMemcpyDeviceToHost);
-  if (e != hipSuccess) {
-    free_registration(ctx);
-    return hip_fail(ctx, e, "image registration");
-  }
+  memcpy(host.data(), table.data(), o_bad);
   ctx->n_images = n_images;
   ctx->n_host.resize(size_t(n_images));
   ctx->bbox_host.resize(4 * size_t(n_images));

@@ -30,6 +30,7 @@
 #include <cmath>
 
 
+#include "line.h"
 #include "sfm_internal.h"
 
 #pragma clang fp contract(off)
@@ -61,21 +62,6 @@ __device__ __forceinline__ int32_t next_row(int32_t strip, int32_t y, int32_t r)
   return r + ((y & 3) == 3 ? strip - 3 : 1);
 }
 
-// Entry i (uniform) of a table that this kernel only reads, by scalar loads.
-template <class T>
-__device__ __forceinline__ T read_uniform(const T* table, int32_t i) {
-  static_assert(sizeof(T) % 4 == 0, "whole words");
-  typedef const __attribute__((address_space(4))) int32_t c_i32;
-  c_i32* src = (c_i32*)(table + __builtin_amdgcn_readfirstlane(i));
-  union {
-    int32_t w[sizeof(T) / 4];
-    T t;
-  } u;
-#pragma unroll
-  for (int k = 0; k < int(sizeof(T) / 4); ++k) u.w[k] = src[k];
-  return u.t;
-}
-
 // One workgroup per (pair, strip of kGridLdsCells cells in storage order):
 // counts per cell in LDS, a scan, then a scatter of the features of the strip;
 // the features of earlier strips are only counted.  Features of one cell land
@@ -101,7 +87,7 @@ __global__ __launch_bounds__(kBinThreads) void grid_bin_kernel(GridView v) {
   // The strip's cell of feature j: negative before the strip, nc or more after
   // it (or outside the grid).
   auto cell_of = [&](int32_t j) -> int64_t {
-    const float2 xy = reinterpret_cast<const float2*>(B.xy)[j];
+    const float2 xy = ldg_xy(B.xy, j);
     const int32_t cx = fine_cell(double(xy.x), d, inv_d) - fx0;
     const int32_t cy = fine_cell(double(xy.y), d, inv_d) - fy0;
     if (cx < 0 || cx >= nfx || cy < 0 || cy >= nfy) {
@@ -282,13 +268,6 @@ struct Sampler {
 };
 
 constexpr int kListCap = 256;   // found features a query lists in LDS before they are consumed
-
-// Keeps the compiler from moving a wave's LDS accesses across this point (a
-// wave's LDS accesses are carried out in order).
-__device__ __forceinline__ void wave_lds_fence() {
-  __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
-  __builtin_amdgcn_wave_barrier();
-}
 
 // The item range of a cell by its index (one 8-byte load; starts are 4-byte
 // aligned, which global loads allow).
@@ -562,22 +541,6 @@ __device__ __forceinline__ void grid_decide(const GridView& v, int64_t q_off, in
 // pairs dealt to all XCDs at once (1.17 ms, 5 GB of L2 misses).
 constexpr int kGroupLanes = 16;
 
-// Within each four lanes: lane u's value; the value of lane ^ 1; of lane ^ 2.
-__device__ __forceinline__ int32_t quad_lane(int32_t x, int u) {
-  switch (u) {
-    case 0: return __builtin_amdgcn_mov_dpp(x, 0x00, 0xF, 0xF, true);
-    case 1: return __builtin_amdgcn_mov_dpp(x, 0x55, 0xF, 0xF, true);
-    case 2: return __builtin_amdgcn_mov_dpp(x, 0xAA, 0xF, 0xF, true);
-    default: return __builtin_amdgcn_mov_dpp(x, 0xFF, 0xF, 0xF, true);
-  }
-}
-__device__ __forceinline__ int32_t quad_swap1(int32_t x) {
-  return __builtin_amdgcn_mov_dpp(x, 0xB1, 0xF, 0xF, true);
-}
-__device__ __forceinline__ int32_t quad_swap2(int32_t x) {
-  return __builtin_amdgcn_mov_dpp(x, 0x4E, 0xF, 0xF, true);
-}
-
 __global__ __launch_bounds__(64, 4) void grid_query_kernel(GridView v) {
   __shared__ Segment segs[kGridQueriesPerBlock];
   __shared__ int32_t lists[64 / kGroupLanes][kListCap];
@@ -601,46 +564,20 @@ __global__ __launch_bounds__(64, 4) void grid_query_kernel(GridView v) {
     const int32_t q = min(q0 + grp, n_here - 1), i = blk.y + q;
     // The lane's two 16-byte chunks of the query's row.
     const int quad = sub & 3;
-    const uint4* qd = reinterpret_cast<const uint4*>(A.desc + 128 * int64_t(i));
-    const uint4 qa = qd[quad], qb = qd[quad + 4];
+    const RowPart qr = row_part(A.desc, i, quad);
     const int32_t qn = A.norm2[i];
     int32_t d1 = kDistInf, j1 = 0x7FFFFFFF, d2 = kDistInf, taken = 0;
     auto consume = [&](int32_t count) {
       // Past the limit on |C'| the first found are kept (the error flag says so).
       count = min(count, kGridMaxCand - taken);
-      // Sixteen candidates at a time, one a lane; four lanes read a row, 64
-      // bytes a load (a lane reading whole rows asked the L2 for every line
-      // eight times), and sum their parts of its product.
+      // Sixteen candidates at a time, one a lane.
       if (count <= 0) return;
       int32_t jn = items[list[min(sub, count - 1)]];
       for (int32_t e0 = 0; e0 < count; e0 += kGroupLanes) {
         const int32_t j = jn;   // the next sixteen load meanwhile
         jn = items[list[min(e0 + kGroupLanes + sub, count - 1)]];
         const int32_t nb2 = B.norm2[j];
-        uint4 ra[4], rb[4];
-#pragma unroll
-        for (int u = 0; u < 4; ++u) {
-          const uint4* row =
-              reinterpret_cast<const uint4*>(B.desc + 128 * int64_t(quad_lane(j, u))) + quad;
-          ra[u] = row[0];
-          rb[u] = row[4];
-        }
-        int32_t dot = 0;
-#pragma unroll
-        for (int u = 0; u < 4; ++u) {
-          uint32_t s = 0;
-          s = __builtin_amdgcn_udot4(ra[u].x, qa.x, s, false);
-          s = __builtin_amdgcn_udot4(ra[u].y, qa.y, s, false);
-          s = __builtin_amdgcn_udot4(ra[u].z, qa.z, s, false);
-          s = __builtin_amdgcn_udot4(ra[u].w, qa.w, s, false);
-          s = __builtin_amdgcn_udot4(rb[u].x, qb.x, s, false);
-          s = __builtin_amdgcn_udot4(rb[u].y, qb.y, s, false);
-          s = __builtin_amdgcn_udot4(rb[u].z, qb.z, s, false);
-          s = __builtin_amdgcn_udot4(rb[u].w, qb.w, s, false);
-          s += uint32_t(quad_swap1(int32_t(s)));
-          s += uint32_t(quad_swap2(int32_t(s)));
-          dot = quad == u ? int32_t(s) : dot;
-        }
+        const int32_t dot = quad_dots(qr, quad_rows(B.desc, j, quad), quad);
         const int32_t D = e0 + sub < count ? qn + nb2 - 2 * dot : kDistInf;
         const bool first = D < d1 || (D == d1 && j < j1);
         d2 = min(d2, first ? d1 : D);

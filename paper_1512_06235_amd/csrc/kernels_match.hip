@@ -40,6 +40,7 @@
 #include <cmath>
 #include <cstddef>
 
+#include "line.h"
 #include "sfm_internal.h"
 
 namespace sfm {
@@ -66,43 +67,6 @@ static_assert((kBuf & (kBuf - 1)) == 0, "buffer offsets wrap with a mask");
 static_assert(kQueryTile == kBlock, "one MFMA column block of queries per tile");
 static_assert(kBuf <= kChunk, "a tile's steps in one fill fit one key chunk");
 constexpr uint32_t kKeyDistInf = kKeyInf >> kPosBits;
-
-// A global load through an address-space-1 pointer: the pointers used with
-// it come from records, and the flat loads the compiler would otherwise emit
-// also count against the LDS counter, so each would be waited for alone.
-template <class T>
-__device__ __forceinline__ T ldg(const T* p) {
-  return *(const __attribute__((address_space(1))) T*)p;
-}
-
-// Epipolar distance of eqs. (2)-(3) on centred FP32 coordinates,
-// |a x + b y + c| with (a, b) unit.  The single FP32 evaluation every pass uses.
-__device__ __forceinline__ float band_dist32(float a, float b, float c, float x, float y) {
-  return __builtin_fabsf(__builtin_fmaf(a, x, __builtin_fmaf(b, y, c)));
-}
-
-// The epipolar distance of eqs. (2)-(3) in FP64, on the caller's F and the
-// original keypoints, every operation as written (no contraction): the line
-// l = F (x, y, 1)^T row by row, s = sqrt(l0^2 + l1^2), then
-// |l0 x' + l1 y' + l2| / s.  NaN when s = 0 or s or l2 is not finite (such a
-// line has no candidates).
-__device__ __forceinline__ double band_dist64(const double* F, float xq, float yq, float xb,
-                                           float yb) {
-#pragma clang fp contract(off)
-  const double x = xq, y = yq;
-  double f[9];
-#pragma unroll
-  for (int k = 0; k < 9; ++k) f[k] = ldg(F + k);
-  const double a = f[0] * x + f[1] * y + f[2];
-  const double b = f[3] * x + f[4] * y + f[5];
-  const double c = f[6] * x + f[7] * y + f[8];
-  const double s = sqrt(a * a + b * b);
-  const bool line = s > 0.0 && isfinite(s) && isfinite(c);
-  // Computed either way and selected, so the loads of (xb, yb) are not
-  // moved into a branch behind this one's.
-  const double e = fabs(a * double(xb) + b * double(yb) + c) / s;
-  return line ? e : NAN;
-}
 
 // Per-byte negation of four bytes in 0..127 (no borrow crosses a byte).
 __device__ __forceinline__ int neg_bytes(uint32_t w) {

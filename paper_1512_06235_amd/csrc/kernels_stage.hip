@@ -23,6 +23,10 @@ __global__ __launch_bounds__(256) void make_views_kernel(const ImageDev* images,
     d.desc += 128 * int64_t(first);
     d.norm2 += first;
     d.cword += first;
+    d.sxy = nullptr;   // a view has no spatial order
+    d.sj = nullptr;
+    d.box = nullptr;
+    d.outer = nullptr;
     d.n = count;
     views[i] = d;
   }

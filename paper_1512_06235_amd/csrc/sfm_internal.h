@@ -22,6 +22,10 @@ constexpr uint32_t kKeyInf = 0xFFFFFFFFu;
 constexpr int32_t kDistInf = 0x7FFFFFFF;
 constexpr uint32_t kDistBias = 1u << 21;  // makes norm2(c) - 2 q.c >= 0
 constexpr int kMaxBins = 8192;          // LDS histogram size per pair
+constexpr int kBoxFeatures = 16;        // spatially sorted features sharing a bounding box
+constexpr int kOuterBoxes = 16;         // boxes sharing an outer box
+constexpr int kOuterFeatures = kBoxFeatures * kOuterBoxes;
+constexpr int32_t kDirectMaxTargets = 65536;   // spatial positions fit 16 bits
 constexpr double kBandSlackPx = 1e-2;   // bin windows widen the band by this
 constexpr int32_t kGroupStartCost = 48;  // schedule cost of starting a tile group
 constexpr int32_t kSegCost = 4;          // schedule cost of streaming one 64-position segment
@@ -33,6 +37,13 @@ struct ImageDev {
   const uint8_t* desc;      // uint8[n][128]
   const int32_t* norm2;     // int32[n], owned by the context
   const int32_t* cword;     // int32[n], owned by the context: norm2 - 127 * (sum of the bytes) + 2^21
+  // The features in spatial order (order_kernel), padded to whole outer boxes,
+  // owned by the context: coordinates on the image box's centre, original
+  // indices, and the centres and half extents of the boxes and outer boxes.
+  const float2* sxy;
+  const int32_t* sj;
+  const float4* box;
+  const float4* outer;
   int32_t n;
   int32_t pad;
   float bbox[4];            // min x, min y, max x, max y of the keypoints
@@ -331,9 +342,10 @@ int serve_match(sfm_ctx* ctx, ServeSpace* sp, const sfm_pair* pairs, int32_t n_p
                 const double* F, const sfm_options* opt, const sfm_matches* out, hipStream_t st);
 
 // Host launchers (one translation unit each).
-hipError_t launch_register(const ImageDev* imgs_host, ImageDev* imgs_dev, int32_t n_images,
-                           int32_t* norm2_all, int32_t* cword_all, const int64_t* norm_off,
-                           float* bbox_dev, int32_t* bad_flag, hipStream_t st);
+// Fills what the entries of the image table own (norms, constant terms, boxes,
+// spatial orders); *bad_flag (zero before) is set for invalid input.
+hipError_t launch_register(ImageDev* imgs_dev, int32_t n_images, int32_t* bad_flag,
+                           hipStream_t st);
 // Preparation of pairs [pair_begin, pair_begin + pair_count), whose tile groups
 // are [grp_begin, grp_begin + grp_count), for `wgs` match workgroups (the
 // groups are split into min(kXcds, wgs) shares of about equal cost, one per
@@ -364,6 +376,13 @@ void exhaustive_plan(PairDesc* pd, int32_t n_pairs, int2* items, int64_t* n_item
                      int64_t* n_part);
 hipError_t launch_exhaustive(const BatchView& v, const int2* items, int64_t n_items, uint2* part,
                              hipStream_t st);
+// Direct guided matching (kernels_direct.hip) of pairs [pair_begin, pair_begin
+// + pair_count): no preparation, results hold the index in b (emission runs
+// with v.cand_j NULL); the pairs' counters start at zero.  max_queries is
+// the largest n_a among the pairs, queries_per_wave from direct_queries.
+int32_t direct_queries(int64_t total_queries);
+hipError_t launch_direct(const BatchView& v, int32_t pair_begin, int32_t pair_count,
+                         int32_t max_queries, int32_t queries_per_wave, hipStream_t st);
 // Diagnostic after a preparation: out[0] receives (atomic max) the bits of
 // the largest |FP32 - FP64| epipolar distance over the evaluated slots whose
 // FP64 distance is at most 2d, out[1] (atomic add) their number.
