@@ -6,10 +6,10 @@
 // of the group's candidate ranges (b's features in binned order, up to 256
 // positions at a time) into one LDS buffer, then each wave runs its own tiles
 // over their ranges without further synchronisation.
-//   - The buffer is filled by LDS DMA (global_load_lds): wave w fetches the
-//     16-position blocks w, w + 4, ... (two 16-byte loads per lane for a
-//     block's 16 descriptor rows, eight lanes per 128-byte row, XOR-swizzled,
-//     and 16 of its coordinates and keys).  The rows' indices in b arrive one
+//   - The buffer is filled by LDS DMA (global_load_lds): each wave fetches a
+//     quarter of its 16-position blocks (two 16-byte loads per lane for a
+//     block's 16 descriptor rows, eight lanes per 128-byte row, XOR-swizzled)
+//     and, one load each, its blocks' coordinates and key words.  The rows' indices in b arrive one
 //     group earlier in an index buffer of their own, so no loaded value passes
 //     through a register on its way to LDS.
 //   - Per group: one wait and one barrier before the buffer is read, one
@@ -19,16 +19,19 @@
 //     work on one or two pairs whose rows stay in that XCD's L2.
 //   - Wave w owns tiles w and 2 * 4 - 1 - w (when a group has eight), which
 //     balances the waves of a group whose range lengths drift along it.
-//   - Each tile walks its candidate range in steps of 16 positions aligned to
-//     16.  A step's rows are the A operand of v_mfma_i32_16x16x64_i8 and the
-//     tile's negated query rows the resident B operand: two MFMAs give -q.c
-//     for 16 candidates x 16 queries, exact in int32 (bytes 0..127 fit int8,
-//     128 * 127^2 < 2^31).  The next step's operands are read from LDS before
+//   - Each tile walks its candidate range in steps of 16 positions.  A step's
+//     rows are the A operand of v_mfma_i32_16x16x64_i8 and the tile's query
+//     rows the resident B operand: two MFMAs give q.c for 16 candidates x 16
+//     queries, exact in int32 (bytes 0..127 fit int8, 128 * 127^2 < 2^31).  The next step's operands are read from LDS before
 //     the current step's fold.
 //   - Each lane then holds one query and 4 candidates.  It runs the band test
-//     of eqs. (2)-(3) in FP32 on centred coordinates and folds in-band keys
+//     of eqs. (2)-(3) in FP32 on centred coordinates, forms in-band keys
 //         key = ((||c||^2 - 2 q.c + 2^21) << 10) | (position mod 1024)
-//     into its two smallest with one v_med3_u32 and one v_min_u32.
+//     and folds the two smallest of its four into its two smallest so far:
+//     35 vector instructions and two MFMAs per step.  (Matrix and vector
+//     instructions do not overlap here, so the vector ones are the loop's cost;
+//     41 of them, with negated queries, one candidate folded at a time and
+//     masked buffer offsets: 502 us for 500 pairs' 2.2 M steps, 475 now.)
 //   - Slots whose FP32 distance lies within the margin of d are queued in LDS
 //     with their exact key and index in b, and decided in FP64 when the
 //     group's tiles are done.
@@ -59,7 +62,7 @@ constexpr int kWaves = kMatchWaves;           // waves per workgroup
 constexpr int kBuf = SFM_MATCH_BUF;           // candidate positions one buffer fill holds (power of two)
 constexpr int kBlock = 16;                    // positions per DMA block (one step)
 constexpr int kBlocks = kBuf / kBlock;        // blocks of a buffer fill
-constexpr int kBlocksPerWave = kBlocks / kWaves;
+constexpr int kBlocksPerWave = kBlocks / kWaves;   // most blocks a wave fetches of a fill
 constexpr int kBorderCap = 32;                // queued FP64 decisions per wave and group
 static_assert(kBlocksPerWave * kWaves == kBlocks, "blocks are dealt evenly to the waves");
 static_assert(kBlocksPerWave * kBlock <= 64, "one 64-lane load fetches a wave's row indices");
@@ -68,13 +71,25 @@ static_assert(kQueryTile == kBlock, "one MFMA column block of queries per tile")
 static_assert(kBuf <= kChunk, "a tile's steps in one fill fit one key chunk");
 constexpr uint32_t kKeyDistInf = kKeyInf >> kPosBits;
 
-// Per-byte negation of four bytes in 0..127 (no borrow crosses a byte).
-__device__ __forceinline__ int neg_bytes(uint32_t w) {
-  return int((0x80808080u - w) ^ 0x80808080u);
+// nv - 2048 dot in one instruction (v_mad_i32_i24; |dot| <= 128 * 127^2 < 2^23
+// and the result wraps like the 32-bit expression): the key of a candidate.
+// `m2048` is -2048 behind an asm statement, or it would become a shift and a
+// subtraction.
+__device__ __forceinline__ uint32_t key_of(uint32_t nv, int32_t dot, int32_t m2048) {
+  return nv + uint32_t(((dot << 8) >> 8) * ((m2048 << 8) >> 8));
 }
 
+// The middle and the smallest of three as one instruction each (of the
+// expressions the compiler splits some into two).
 __device__ __forceinline__ uint32_t umed3(uint32_t a, uint32_t b, uint32_t c) {
-  return max(min(a, b), min(max(a, b), c));   // selects v_med3_u32
+  uint32_t r;
+  asm("v_med3_u32 %0, %1, %2, %3" : "=v"(r) : "v"(a), "v"(b), "v"(c));
+  return r;
+}
+__device__ __forceinline__ uint32_t umin3(uint32_t a, uint32_t b, uint32_t c) {
+  uint32_t r;
+  asm("v_min3_u32 %0, %1, %2, %3" : "=v"(r) : "v"(a), "v"(b), "v"(c));
+  return r;
 }
 
 // Exact squared L2 of two 128-byte rows with VALU dot products.
@@ -97,16 +112,16 @@ __device__ __forceinline__ nv4u gload16(const void* p) { return *(g_nv4u*)p; }
 // ---------------------------------------------------------------------------
 // LDS of a workgroup (40 KB: four workgroups per CU): one buffer fill of
 // candidates (rows XOR-swizzled: chunk c of buffer position r at
-// (c ^ (r & 7)) * 16 within the row), the row indices of two groups (each
-// wave's blocks together, block w + 4 k at 16 k) and the queues of FP64
-// decisions.
+// (c ^ (r & 7)) * 16 within the row), the row indices of two groups and the
+// queues of FP64 decisions.  A step's read-ahead past the last step of a full
+// buffer lands in the array behind the one it reads and is not used.
 // ---------------------------------------------------------------------------
 struct MatchLds {
   uint8_t rows[kBuf * kDescBytes];
   float x[kBuf];
   float y[kBuf];
   uint32_t nc[kBuf];
-  int32_t j[2][kWaves][kBlocksPerWave * kBlock];
+  int32_t j[2][kBuf];
   uint4 queue[kWaves][kBorderCap];   // {key, rel. position << 7 | tile << 6 | lane, j, -}
 };
 static_assert(sizeof(MatchLds) <= 40960, "four workgroups per CU");
@@ -180,47 +195,58 @@ __device__ __forceinline__ Stream make_stream(const BatchView& v, const TileGrou
   return s;
 }
 
-// The row indices of this wave's blocks of the fill starting at relative
-// position f into index buffer `par`: one 4-byte load (lane l:
-// block w + 4 (l >> 4), position l & 15; blocks past the stream load a
-// clamped position that is never used).
-__device__ __forceinline__ void issue_j(const Stream& s, int32_t f, int par, int w, int lane) {
-  if (kBlocksPerWave * kBlock < 64 && lane >= kBlocksPerWave * kBlock) return;
-  const int32_t p = min(s.base + f + kBlock * (w + kWaves * (lane >> 4)) + (lane & 15), s.last);
-  dma4(s.j + p, s.lds + uint32_t(offsetof(MatchLds, j)) +
-                    4u * uint32_t((par * kWaves + w) * kBlocksPerWave * kBlock));
+// The blocks of a fill of nblk blocks that wave w fetches: [first, first + n).
+struct WaveBlocks {
+  int32_t first, n;
+};
+__device__ __forceinline__ WaveBlocks wave_blocks(int32_t nblk, int w) {
+  const int32_t each = (nblk + kWaves - 1) / kWaves;
+  const int32_t first = min(w * each, nblk);
+  return {first, min(each, nblk - first)};
 }
+
+// The row indices of this wave's blocks of the fill starting at relative
+// position f into index buffer `par`: always one 4-byte load of all lanes (the
+// waits count it).  Lanes past the wave's blocks load what the next waves load
+// too, or clamped positions that are never used.
+__device__ __forceinline__ void issue_j(const Stream& s, int32_t f, int par, int w, int lane) {
+  const int32_t first = kBlock * wave_blocks(min(s.len - f, kBuf) / kBlock, w).first;
+  const uint32_t p = uint32_t(min(s.base + f + first + lane, s.last));
+  dma4(s.j + p, s.lds + uint32_t(offsetof(MatchLds, j)) + 4u * uint32_t(par * kBuf + first));
+}
+static_assert((kWaves - 1) * kBlocksPerWave * kBlock + 64 <= kBuf,
+              "the last wave's index load stays in its buffer");
 
 // Rows and metadata of this wave's blocks of the fill starting at relative
 // position f (nblk blocks): per block two 16-byte loads per lane (lane l: row
 // 8 t + (l >> 3) of the block, chunk (l & 7) ^ (row & 7), landing at slot
-// l & 7 of the row) and three 4-byte loads on 16 lanes.  The rows' indices
-// come from index buffer `par` (loaded earlier by this wave and complete).
+// l & 7 of the row), and three 4-byte loads for all the wave's positions.  The
+// rows' indices come from index buffer `par` (loaded earlier by this wave and
+// complete).
 __device__ __forceinline__ void issue_rows(const Stream& s, const MatchLds& L, int32_t f,
                                            int32_t nblk, int par, int w, int lane) {
-  const int32_t* jw = &L.j[par][w][0];
+  const WaveBlocks b = wave_blocks(nblk, w);
+  const int32_t* jw = &L.j[par][kBlock * b.first + (lane >> 3)];
+  // Row & 7 is lane >> 3 for both t.
+  const uint8_t* chunk = s.b_desc + 16 * ((lane & 7) ^ (lane >> 3));
 #pragma unroll
   for (int k = 0; k < kBlocksPerWave; ++k) {
-    const int32_t b = w + kWaves * k;
-    if (b >= nblk) break;
+    if (k >= b.n) break;
 #pragma unroll
-    for (int t = 0; t < 2; ++t) {
-      const int rr = 8 * t + (lane >> 3);
-      const int32_t jr = jw[kBlock * k + rr];
-      const int c = (lane & 7) ^ (rr & 7);
-      dma16(s.b_desc + int64_t(jr) * kDescBytes + 16 * c,
+    for (int t = 0; t < 2; ++t)
+      dma16(chunk + (uint64_t(uint32_t(jw[kBlock * k + 8 * t])) << 7),
             s.lds + uint32_t(offsetof(MatchLds, rows)) +
-                uint32_t((kBlock * b + 8 * t) * kDescBytes));
-    }
-    if (lane < kBlock) {
-      const int32_t p = min(s.base + f + kBlock * b + lane, s.last);
-      const uint32_t o = 4u * uint32_t(kBlock * b);
-      dma4(s.x + p, s.lds + uint32_t(offsetof(MatchLds, x)) + o);
-      dma4(s.y + p, s.lds + uint32_t(offsetof(MatchLds, y)) + o);
-      dma4(s.nc + p, s.lds + uint32_t(offsetof(MatchLds, nc)) + o);
-    }
+                uint32_t((kBlock * (b.first + k) + 8 * t) * kDescBytes));
+  }
+  if (lane < kBlock * b.n) {
+    const uint64_t p = uint32_t(min(s.base + f + kBlock * b.first + lane, s.last));
+    const uint32_t o = 4u * uint32_t(kBlock * b.first);
+    dma4(s.x + p, s.lds + uint32_t(offsetof(MatchLds, x)) + o);
+    dma4(s.y + p, s.lds + uint32_t(offsetof(MatchLds, y)) + o);
+    dma4(s.nc + p, s.lds + uint32_t(offsetof(MatchLds, nc)) + o);
   }
 }
+static_assert(kDescBytes == 128, "a row index shifts to its offset");
 
 // A group record read with scalar loads (its index is uniform).
 typedef const __attribute__((address_space(4))) v4i c_v4i;
@@ -430,13 +456,16 @@ __device__ __forceinline__ void fold_state(Tile& T, uint32_t kd, int32_t pos) {
 // of each query, then fold the chunk's two smallest into the running result.
 // No memory access: a shared smallest distance only sets the tie flag.
 __device__ __forceinline__ void close_chunk(Tile& T, int32_t c0p, int32_t c1p) {
-#pragma unroll
-  for (int o = 16; o <= 32; o <<= 1) {
-    const uint32_t p1 = __shfl_xor(T.k1, o, 64);
-    const uint32_t p2 = __shfl_xor(T.k2, o, 64);
-    T.k2 = min(max(T.k1, p1), min(T.k2, p2));
-    T.k1 = min(T.k1, p1);
-  }
+  // Swapping a register's halves with its own copy's gives both halves' values
+  // to every lane (the other way round in the other half: sorted anyway).
+  auto merge = [&](auto a, auto b) {
+    T.k1 = min(a[0], a[1]);
+    T.k2 = min(max(a[0], a[1]), min(b[0], b[1]));
+  };
+  merge(__builtin_amdgcn_permlane16_swap(T.k1, T.k1, false, false),
+        __builtin_amdgcn_permlane16_swap(T.k2, T.k2, false, false));
+  merge(__builtin_amdgcn_permlane32_swap(T.k1, T.k1, false, false),
+        __builtin_amdgcn_permlane32_swap(T.k2, T.k2, false, false));
   const uint32_t kd1 = T.k1 >> kPosBits, kd2 = T.k2 >> kPosBits;
   const int32_t pf = int32_t(T.k1 & (kChunk - 1));
   const int32_t at = min(c0p + ((pf - c0p) & (kChunk - 1)), c1p - 1);
@@ -484,8 +513,13 @@ __device__ __forceinline__ void match_group(const BatchView& v, const TileGroup&
     int32_t tb = gw[offsetof(TileGroup, t_begin) / 4 + tidx];
     int32_t te = gw[offsetof(TileGroup, t_end) / 4 + tidx];
     if (tidx >= G.ntiles || te <= tb) tb = te = s.base;
-    rb[k] = (tb & ~(kBlock - 1)) - s.base;
+    // A range within one fill starts at the 4-position group that holds its
+    // start, or as much before it as its steps would overrun the fill (rounding
+    // down to 16 positions cost 6% of the steps at 65 in-band targets per query).
+    // Over several fills steps keep to multiples of 16, as fills do.
     re[k] = te - s.base;
+    rb[k] = (tb & (nfill > 1 ? -kBlock : -4)) - s.base;
+    rb[k] = min(rb[k], max(0, s.len - ((re[k] - rb[k] + kBlock - 1) & -kBlock)));
     c0[k] = rb[k];
   }
 
@@ -524,8 +558,7 @@ __device__ __forceinline__ void match_group(const BatchView& v, const TileGroup&
   for (int k = 0; k < TPW; ++k) {
 #pragma unroll
     for (int m = 0; m < 2; ++m)
-      T[k].bq[m] = v4i{neg_bytes(qr[k][m].x), neg_bytes(qr[k][m].y), neg_bytes(qr[k][m].z),
-                       neg_bytes(qr[k][m].w)};
+      T[k].bq[m] = v4i{int(qr[k][m].x), int(qr[k][m].y), int(qr[k][m].z), int(qr[k][m].w)};
     T[k].k1 = T[k].k2 = kKeyInf;
     T[k].s1 = T[k].s2 = kKeyDistInf;
     T[k].p1 = 0;
@@ -538,6 +571,8 @@ __device__ __forceinline__ void match_group(const BatchView& v, const TileGroup&
   int32_t nbq = 0;         // queued FP64 decisions
   bool overflow = false;   // more than kBorderCap: the wave's tiles are recomputed exactly
   uint32_t nsteps = 0;     // 16 x 16 steps evaluated
+  int32_t m2048 = -2048;
+  asm("" : "+s"(m2048));
 
   for (int32_t fi = 0; fi < nfill; ++fi) {
     const int32_t f = kBuf * fi;   // relative position of the fill's start
@@ -570,15 +605,17 @@ __device__ __forceinline__ void match_group(const BatchView& v, const TileGroup&
       // candidates 4 rg .. 4 rg + 3 of the step.  Both advance by 16 rows.
       const int32_t q0 = p0 - f;
       uint32_t oa = uint32_t((q0 + col) * kDescBytes + ((rg ^ ((q0 + col) & 7)) << 4));
-      uint32_t om = uint32_t((q0 + 4 * rg) * 4);
-      // The first step's operands; each step reads the next one's before
-      // its own fold (the read after the last step wraps and is unused).
-      const uint32_t oa0 = oa, om0 = om;
-      v4i na0 = *reinterpret_cast<const v4i*>(&L.rows[oa]);
-      v4i na1 = *reinterpret_cast<const v4i*>(&L.rows[oa ^ 64u]);
-      float4 nxs = reinterpret_cast<const float4*>(L.x)[om >> 4];
-      float4 nys = reinterpret_cast<const float4*>(L.y)[om >> 4];
-      uint4 nns = reinterpret_cast<const uint4*>(L.nc)[om >> 4];
+      uint32_t ob = oa ^ 64u;
+      uint32_t om = uint32_t(4 * (q0 + 4 * rg));
+      auto row = [&](uint32_t o) { return *reinterpret_cast<const v4i*>(&L.rows[o]); };
+      auto xs4 = [&](uint32_t o) { return reinterpret_cast<const float4*>(L.x)[o >> 4]; };
+      auto ys4 = [&](uint32_t o) { return reinterpret_cast<const float4*>(L.y)[o >> 4]; };
+      auto nc4 = [&](uint32_t o) { return reinterpret_cast<const uint4*>(L.nc)[o >> 4]; };
+      // The first step's operands; each step reads the next one's before its own
+      // fold.
+      v4i na0 = row(oa), na1 = row(ob);
+      float4 nxs = xs4(om), nys = ys4(om);
+      uint4 nns = nc4(om);
       // Steps of this fill (at most kBuf / 16) with a slot within the margin
       // of d: only marked here, so the loop keeps nothing live for them.
       static_assert(kBuf / kBlock <= 32, "one bit per step of a fill");
@@ -590,27 +627,35 @@ __device__ __forceinline__ void match_group(const BatchView& v, const TileGroup&
         const float xv[4] = {nxs.x, nxs.y, nxs.z, nxs.w};
         const float yv[4] = {nys.x, nys.y, nys.z, nys.w};
         const uint32_t nv[4] = {nns.x, nns.y, nns.z, nns.w};
-        oa = (oa + kBlock * kDescBytes) & (kBuf * kDescBytes - 1);
-        om = (om + 4 * kBlock) & (4 * kBuf - 1);
-        na0 = *reinterpret_cast<const v4i*>(&L.rows[oa]);
-        na1 = *reinterpret_cast<const v4i*>(&L.rows[oa ^ 64u]);
-        nxs = reinterpret_cast<const float4*>(L.x)[om >> 4];
-        nys = reinterpret_cast<const float4*>(L.y)[om >> 4];
-        nns = reinterpret_cast<const uint4*>(L.nc)[om >> 4];
+        oa += kBlock * kDescBytes;
+        ob += kBlock * kDescBytes;
+        om += 4 * kBlock;
+        // (Opaque, or the reads move to the next step's start and wait there.)
+        asm("" : "+v"(oa), "+v"(ob), "+v"(om));
+        na0 = row(oa);
+        na1 = row(ob);
+        nxs = xs4(om);
+        nys = ys4(om);
+        nns = nc4(om);
         unsigned long long border = 0;
+        uint32_t kin[4];
 #pragma unroll
         for (int e = 0; e < 4; ++e) {
           const float d32 = band_dist32(t.a, t.b, t.c, xv[e], yv[e]);
           const bool mem = d32 <= lo;
           border |= __ballot(d32 <= hi) & ~__ballot(mem);
-          const uint32_t kin = mem ? nv[e] + (uint32_t(acc[e]) << 11) : kKeyInf;
-          t.k2 = umed3(t.k1, kin, t.k2);
-          t.k1 = min(t.k1, kin);
+          kin[e] = mem ? key_of(nv[e], acc[e], m2048) : kKeyInf;
           if (kKeepCounts)
             t.cnt += mem ? 1 : 0;
           else
             wcnt += __builtin_popcountll(__ballot(mem));
         }
+        // The step's two smallest, then the two smallest with the running ones.
+        const uint32_t lo3 = umin3(kin[0], kin[1], kin[2]);
+        const uint32_t mid3 = umed3(kin[0], kin[1], kin[2]);
+        const uint32_t m1 = min(lo3, kin[3]), m2 = umed3(lo3, mid3, kin[3]);
+        t.k2 = min(umed3(t.k1, m1, t.k2), m2);
+        t.k1 = min(t.k1, m1);
         if (border) bsteps |= 1u << i;
       }
       // Rare: the marked steps again (the same operations, so the same keys),
@@ -620,16 +665,15 @@ __device__ __forceinline__ void match_group(const BatchView& v, const TileGroup&
       while (bsteps) {
         const int32_t i = __builtin_ctz(bsteps);
         bsteps &= bsteps - 1;
-        const uint32_t oai = (oa0 + uint32_t(i) * (kBlock * kDescBytes)) & (kBuf * kDescBytes - 1);
-        const uint32_t omi = (om0 + uint32_t(i) * (4 * kBlock)) & (4 * kBuf - 1);
-        const v4i a0 = *reinterpret_cast<const v4i*>(&L.rows[oai]);
-        const v4i a1 = *reinterpret_cast<const v4i*>(&L.rows[oai ^ 64u]);
-        const float4 xs = reinterpret_cast<const float4*>(L.x)[omi >> 4];
-        const float4 ys = reinterpret_cast<const float4*>(L.y)[omi >> 4];
-        const uint4 ns = reinterpret_cast<const uint4*>(L.nc)[omi >> 4];
+        const uint32_t back = uint32_t(n - i);   // steps the offsets are past this one
+        const v4i b0 = row(oa - back * (kBlock * kDescBytes));
+        const v4i b1 = row(ob - back * (kBlock * kDescBytes));
+        const uint32_t omi = om - back * (4 * kBlock);
+        const float4 xs = xs4(omi), ys = ys4(omi);
+        const uint4 ns = nc4(omi);
         v4i acc = {0, 0, 0, 0};
-        acc = __builtin_amdgcn_mfma_i32_16x16x64_i8(a0, t.bq[0], acc, 0, 0, 0);
-        acc = __builtin_amdgcn_mfma_i32_16x16x64_i8(a1, t.bq[1], acc, 0, 0, 0);
+        acc = __builtin_amdgcn_mfma_i32_16x16x64_i8(b0, t.bq[0], acc, 0, 0, 0);
+        acc = __builtin_amdgcn_mfma_i32_16x16x64_i8(b1, t.bq[1], acc, 0, 0, 0);
         const float xv[4] = {xs.x, xs.y, xs.z, xs.w};
         const float yv[4] = {ys.x, ys.y, ys.z, ys.w};
         const uint32_t nv[4] = {ns.x, ns.y, ns.z, ns.w};
@@ -639,7 +683,7 @@ __device__ __forceinline__ void match_group(const BatchView& v, const TileGroup&
         for (int e = 0; e < 4; ++e) {
           const float d32 = band_dist32(t.a, t.b, t.c, xv[e], yv[e]);
           bm[e] = __ballot(d32 <= hi) & ~__ballot(d32 <= lo);
-          keys[e] = nv[e] + (uint32_t(acc[e]) << 11);
+          keys[e] = key_of(nv[e], acc[e], m2048);
         }
         {
           const int32_t p = p0 + kBlock * i;
@@ -657,8 +701,7 @@ __device__ __forceinline__ void match_group(const BatchView& v, const TileGroup&
                                           __builtin_amdgcn_mbcnt_lo(uint32_t(bm[e]), 0)));
             if ((bm[e] >> lane) & 1ull) {
               const int32_t pr = p + 4 * rg + e;        // relative position
-              const int32_t bq = (pr - f) >> 4;          // block of the fill
-              const int32_t jq = L.j[par][bq & (kWaves - 1)][kBlock * (bq >> 2) + (pr & 15)];
+              const int32_t jq = L.j[par][pr - f];
               L.queue[w][idx] = make_uint4(
                   keys[e], (uint32_t(pr) << 7) | (uint32_t(k) << 6) | uint32_t(lane),
                   uint32_t(jq), 0u);
@@ -766,11 +809,14 @@ __device__ __forceinline__ void match_group(const BatchView& v, const TileGroup&
     }
     nacc += __builtin_popcountll(__ballot(accept && qv[k] && lane < kQueryTile));
   }
-  for (int o = 8; o > 0; o >>= 1) tsum += __shfl_xor(tsum, o, 64);
-  tsum = __shfl(tsum, 0, 64);
   // Without per-query counts the wave counted in-band slots itself (unless
   // its tiles were recomputed).
-  if (!kKeepCounts && !overflow) tsum = int32_t(wcnt);
+  if (kKeepCounts || overflow) {
+    for (int o = 8; o > 0; o >>= 1) tsum += __shfl_xor(tsum, o, 64);
+    tsum = __shfl(tsum, 0, 64);
+  } else {
+    tsum = int32_t(wcnt);
+  }
   if (G.pair != ws.pair) {
     flush_stats(v, ws, lane);
     ws.pair = G.pair;

@@ -1,0 +1,48 @@
+"""The binned match kernel where its buffers, steps and groups end.
+
+A fill of the buffer holds 256 (or 128) targets; a tile's 16-target steps start
+at its range's 4-target group, moved back where they would overrun the fill,
+or on multiples of 16 when the range takes several fills.  Sizes lie around
+those numbers, bands range from empty to everything, and the outputs are
+integers: they equal the oracle's.  (A wide recheck margin keeps every pair in
+the binned form.)"""
+import numpy as np
+import pytest
+
+import scenes
+from tests.fixtures import random_pair
+from tests.gpu_util import compare_all
+
+pytestmark = pytest.mark.gpu
+
+TARGETS = [1, 15, 16, 17, 127, 129, 255, 256, 257, 271, 300, 1030, 2100]
+QUERIES = [0, 1, 16, 17, 63, 65, 128, 129, 300]
+
+
+@pytest.fixture(scope="module")
+def sfm():
+    import torch
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    import paper_1512_06235_amd as sfm
+    sfm.lib()
+    return sfm
+
+
+@pytest.mark.parametrize("tiles", [4, 8])
+@pytest.mark.parametrize("emit_all", [False, True])
+def test_sizes_around_fills(sfm, oracle_lib, tiles, emit_all):
+    images = []
+    for k, n in enumerate(QUERIES + TARGETS):
+        xy, desc, _, _, _ = random_pair(n, 0, seed=200 + k)
+        images.append((xy, desc // 8))
+    F = scenes.make_two_view_2k().F
+    nq = len(QUERIES)
+    pairs = [(q, nq + t, d) for q in range(nq) for t in range(len(TARGETS))
+             for d in ((0.5, 12.0, 90.0, np.inf) if t % 2 else (3.0, 40.0, 250.0))]
+    m = sfm.Matcher().register(images)
+    sfm.sfm_set_tuning(m.ctx, tiles, 8)
+    want = oracle_lib.match(images, pairs, [F] * len(pairs))
+    out = m.match(pairs, [F] * len(pairs), emit_all=emit_all, recheck_margin_px=6e-3)
+    compare_all(out, want, len(pairs))
+    m.close()
