@@ -123,6 +123,7 @@ struct MatchLds {
   uint32_t nc[kBuf];
   int32_t j[2][kBuf];
   uint4 queue[kWaves][kBorderCap];   // {key, rel. position << 7 | tile << 6 | lane, j, -}
+  unsigned long long stats[2][8];    // of this group and the last, in PairCounters' order
 };
 static_assert(sizeof(MatchLds) <= 40960, "four workgroups per CU");
 
@@ -136,6 +137,13 @@ __device__ __forceinline__ void wait_loads() {
   static_assert(N >= 0 && N < 16, "vmcnt range used here");
   compiler_fence();
   __builtin_amdgcn_s_waitcnt(N | 0x0F70);
+  compiler_fence();
+}
+
+// Waits for this wave's LDS accesses.
+__device__ __forceinline__ void wait_lds() {
+  compiler_fence();
+  __builtin_amdgcn_s_waitcnt(0xC07F);   // lgkmcnt(0)
   compiler_fence();
 }
 
@@ -305,23 +313,21 @@ struct Tile {
   int32_t cnt;              // in-band slots of this lane (counts kept)
 };
 
-// Per-wave statistics of the groups of one pair, flushed when the pair changes.
-struct WaveStats {
-  int32_t pair;
-  unsigned long long comparisons, elements, borderline;
-  uint32_t accepted, ties;
-};
-
-__device__ __forceinline__ void flush_stats(const BatchView& v, WaveStats& w, int lane) {
-  if (w.pair >= 0 && lane == 0) {
-    if (w.comparisons) atomicAdd(&v.counters[w.pair].comparisons, w.comparisons);
-    if (w.elements) atomicAdd(&v.counters[w.pair].elements, w.elements);
-    if (w.borderline) atomicAdd(&v.counters[w.pair].borderline, w.borderline);
-    if (w.accepted) atomicAdd(&v.counters[w.pair].accepted, w.accepted);
-    if (w.ties) atomicAdd(&v.counters[w.pair].ties, w.ties);
+// A group's statistics: its waves add theirs in LDS, and once the next group
+// has begun the first wave adds the sums to the pair's counters with one
+// instruction.  (Groups that run side by side are of one pair, whose counters
+// share a cache line, and a line takes an addition in about 5 ns: five per wave
+// and group, 690,000 for 500 pairs, held the kernel up, 475 us.)
+constexpr int kStats = 5;   // the fields of PairCounters
+static_assert(sizeof(PairCounters) == kStats * sizeof(unsigned long long),
+              "a lane per counter");
+__device__ __forceinline__ void flush_stats(const BatchView& v, unsigned long long* sums,
+                                            int32_t pair, int lane) {
+  if (lane < kStats) {
+    const unsigned long long x = sums[lane];
+    sums[lane] = 0;
+    if (x) atomicAdd(reinterpret_cast<unsigned long long*>(v.counters + pair) + lane, x);
   }
-  w.comparisons = w.elements = w.borderline = 0;
-  w.accepted = w.ties = 0;
 }
 
 // What the FP64 decisions and the rare exact passes of one group read (all
@@ -488,12 +494,13 @@ __device__ __forceinline__ void close_chunk(Tile& T, int32_t c0p, int32_t c1p) {
 // ranges, read from the LDS buffer.  `gs` holds the group's query records and
 // its first fill's row indices are in index buffer `par` (both issued by the
 // previous group or the kernel's start).  The group issues the first stage of
-// group gn (if gn >= 0) into the other index buffer.
+// group gn (if gn >= 0) into the other index buffer.  `last_pair` is the pair of
+// the workgroup's last group (-1: none), whose statistics are in the other set.
 template <bool kKeepCounts, int TPW>
 __device__ __forceinline__ void match_group(const BatchView& v, const TileGroup& G, int32_t g,
                                             const GroupStart<TPW>& gs, int par, int32_t gn,
                                             GroupStart<TPW>& gsn, MatchLds& L, int w, int lane,
-                                            WaveStats& ws) {
+                                            int32_t last_pair) {
   const int col = lane & (kQueryTile - 1), rg = lane >> 4;
   const float lo = G.band_lo, hi = G.band_hi;
   const Stream s = make_stream(v, G, L);
@@ -524,8 +531,10 @@ __device__ __forceinline__ void match_group(const BatchView& v, const TileGroup&
   }
 
   // This wave's own index loads (and everything before them) are complete;
-  // the barrier also ends every wave's reads of the previous group's fill.
+  // the barrier also ends every wave's reads of the previous group's fill and
+  // its additions to that group's statistics.
   wait_loads<0>();
+  wait_lds();
   barrier();
   const int32_t nblk0 = min(s.len, kBuf) / kBlock;
   issue_rows(s, L, 0, nblk0, par, w, lane);
@@ -565,6 +574,10 @@ __device__ __forceinline__ void match_group(const BatchView& v, const TileGroup&
     T[k].tie = false;
     T[k].cnt = 0;
   }
+
+  // (After the second barrier: every wave's fetches are on their way first.  The
+  // next group's first barrier orders the zeros before that set's next use.)
+  if (w == 0 && last_pair >= 0) flush_stats(v, L.stats[par ^ 1], last_pair, lane);
 
   uint32_t wcnt = 0;       // in-band slots of the wave (counts not kept per query)
   uint32_t wbl = 0;        // slots decided in FP64
@@ -817,15 +830,15 @@ __device__ __forceinline__ void match_group(const BatchView& v, const TileGroup&
   } else {
     tsum = int32_t(wcnt);
   }
-  if (G.pair != ws.pair) {
-    flush_stats(v, ws, lane);
-    ws.pair = G.pair;
+  if (lane < kStats) {
+    const unsigned long long x =
+        lane == 0   ? (unsigned long long)tsum
+        : lane == 1 ? (unsigned long long)nsteps * (kQueryTile * kQueryTile)
+        : lane == 2 ? wbl
+        : lane == 3 ? nacc
+                    : ties;
+    atomicAdd(&L.stats[par][lane], x);
   }
-  ws.comparisons += (unsigned long long)tsum;
-  ws.borderline += wbl;
-  ws.elements += (unsigned long long)nsteps * (kQueryTile * kQueryTile);
-  ws.accepted += nacc;
-  ws.ties += ties;
 }
 
 // One resident wave of workgroups.  Preparation splits the groups into
@@ -849,20 +862,23 @@ void match_kernel(BatchView v) {
   const int32_t W = (int32_t(gridDim.x) - x + shares - 1) / shares;
   const int32_t g_first = ((c_i32*)v.wg_start)[x] + i;
   const int32_t g_end = ((c_i32*)v.wg_start)[x + 1];
-  WaveStats ws = {-1, 0, 0, 0, 0, 0};
-  if (g_first < g_end) {
-    GroupStart<TPW> gs = start_group<TPW>(v, load_group(v.groups, g_first), lds, 0, wave, lane);
-    int par = 0;
-    for (int32_t g = g_first; g < g_end; g += W) {
-      const TileGroup G = load_group(v.groups, g);
-      GroupStart<TPW> gsn;
-      match_group<kKeepCounts, TPW>(v, G, g, gs, par, g + W < g_end ? g + W : -1, gsn, lds,
-                                    wave, lane, ws);
-      gs = gsn;
-      par ^= 1;
-    }
+  if (g_first >= g_end) return;   // uniform
+  if (threadIdx.x < 16) lds.stats[threadIdx.x >> 3][threadIdx.x & 7] = 0;
+  GroupStart<TPW> gs = start_group<TPW>(v, load_group(v.groups, g_first), lds, 0, wave, lane);
+  int par = 0;
+  int32_t last_pair = -1;
+  for (int32_t g = g_first; g < g_end; g += W) {
+    const TileGroup G = load_group(v.groups, g);
+    GroupStart<TPW> gsn;
+    match_group<kKeepCounts, TPW>(v, G, g, gs, par, g + W < g_end ? g + W : -1, gsn, lds, wave,
+                                  lane, last_pair);
+    gs = gsn;
+    par ^= 1;
+    last_pair = G.pair;
   }
-  flush_stats(v, ws, lane);
+  wait_lds();
+  barrier();
+  if (wave == 0) flush_stats(v, lds.stats[par ^ 1], last_pair, lane);
 }
 
 // Diagnostic of the FP32 band test: over every (query, candidate) slot of

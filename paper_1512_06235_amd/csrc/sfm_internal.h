@@ -116,8 +116,8 @@ struct PairCounters {
   unsigned long long comparisons;
   unsigned long long elements;   // (query, candidate) slots evaluated, padding included
   unsigned long long borderline; // slots whose FP32 distance lay within the margin of d
-  uint32_t accepted;
-  uint32_t ties;            // chunks that needed the tie-break pass
+  unsigned long long accepted;
+  unsigned long long ties;       // chunks that needed the tie-break pass
 };
 
 // Up to kMaxGroupTiles consecutive query tiles of one pair and the union of
