@@ -435,6 +435,7 @@ BatchView batch_view(const sfm_ctx* ctx, const ImageTable& tab, char* ws, const 
   v.res = reinterpret_cast<QueryResult*>(ws + L.res);
   v.twin = reinterpret_cast<int2*>(ws + L.twin);
   v.wg_start = reinterpret_cast<int32_t*>(ws + L.wg_start);
+  v.tickets = L.sum_groups > L.wgs && L.wgs + 1 >= kScheduleInts ? v.wg_start + kTicketAt : nullptr;
   v.gcost = reinterpret_cast<int32_t*>(ws + L.gcost);
   v.pcost = reinterpret_cast<long long*>(ws + L.pcost);
   v.err = ctx->err_dev;

@@ -124,6 +124,7 @@ struct MatchLds {
   int32_t j[2][kBuf];
   uint4 queue[kWaves][kBorderCap];   // {key, rel. position << 7 | tile << 6 | lane, j, -}
   unsigned long long stats[2][8];    // of this group and the last, in PairCounters' order
+  int32_t taken;                     // the workgroup's next group (-1: none)
 };
 static_assert(sizeof(MatchLds) <= 40960, "four workgroups per CU");
 
@@ -490,17 +491,71 @@ __device__ __forceinline__ void close_chunk(Tile& T, int32_t c0p, int32_t c1p) {
   T.k2 = kKeyInf;
 }
 
+// The order of groups.  Workgroup i of the W on XCD x starts with groups i and
+// i + W of share x.  Every later one is drawn from a counter: groups
+// 2 W + s + kCounters t of the share belong to its counter s = i mod kCounters,
+// and a workgroup whose counter has run out looks at all of them.  (The oldest
+// wave of a SIMD issues first, so of four workgroups on a CU with as many groups
+// each, the first was done at 58% of the kernel's time, and the last ran alone:
+// 500 pairs 581 us, 541 now; 569 with one counter per share, whose draws wait
+// for each other.)
+struct Deal {
+  int32_t shares;
+  int32_t own;             // this workgroup's counter
+  int32_t first, end;      // its groups: first + kCounters t < end
+};
+struct CounterGroups {
+  int32_t first, end;
+};
+__device__ __forceinline__ CounterGroups counter_groups(const BatchView& v, int32_t shares,
+                                                        int32_t c) {
+  const int32_t x = c / kCounters;
+  const int32_t W = (int32_t(gridDim.x) - x + shares - 1) / shares;
+  return {v.wg_start[x] + 2 * W + c % kCounters, v.wg_start[x + 1]};
+}
+// One lane's draw (its value returns later).
+__device__ __forceinline__ int32_t draw(const BatchView& v, int32_t c) {
+  return __hip_atomic_fetch_add(v.tickets + kTicketStride * c, 1, __ATOMIC_RELAXED,
+                                __HIP_MEMORY_SCOPE_AGENT);
+}
+// A group from any counter that has one left, looked for by all lanes of a wave
+// (-1: none).  Every failed draw finds its counter past its end, so this ends.
+__device__ __forceinline__ int32_t draw_any(const BatchView& v, int32_t shares, int32_t own,
+                                         int lane) {
+  static_assert(kXcds * kCounters <= 64, "a lane per counter");
+  const bool mine = lane < shares * kCounters;
+  const CounterGroups cg = counter_groups(v, shares, mine ? lane : 0);
+  for (;;) {
+    const int32_t t =
+        __hip_atomic_load(v.tickets + kTicketStride * (mine ? lane : 0), __ATOMIC_RELAXED,
+                          __HIP_MEMORY_SCOPE_AGENT);
+    const unsigned long long left = __ballot(mine && cg.first + kCounters * t < cg.end);
+    if (!left) return -1;
+    const unsigned long long after = left & (~0ull << own);
+    const int pick = __builtin_ctzll(after ? after : left);
+    int32_t g = -1;
+    if (lane == pick) {
+      g = cg.first + kCounters * draw(v, pick);
+      if (g >= cg.end) g = -1;
+    }
+    g = __builtin_amdgcn_readlane(g, pick);
+    if (g >= 0) return g;
+  }
+}
+
 // One group: up to 4 * TPW query tiles (TPW per wave) against their candidate
 // ranges, read from the LDS buffer.  `gs` holds the group's query records and
 // its first fill's row indices are in index buffer `par` (both issued by the
-// previous group or the kernel's start).  The group issues the first stage of
-// group gn (if gn >= 0) into the other index buffer.  `last_pair` is the pair of
-// the workgroup's last group (-1: none), whose statistics are in the other set.
+// previous group or the kernel's start).  L.taken holds the next group (gn;
+// -1: none): this one issues its first stage into the other index buffer, and
+// the first wave takes the group after it, left in L.taken before the results.
+// `last_pair` is the pair of the workgroup's last group (-1: none), whose
+// statistics are in the other set.
 template <bool kKeepCounts, int TPW>
 __device__ __forceinline__ void match_group(const BatchView& v, const TileGroup& G, int32_t g,
-                                            const GroupStart<TPW>& gs, int par, int32_t gn,
+                                            const GroupStart<TPW>& gs, int par, int32_t& gn,
                                             GroupStart<TPW>& gsn, MatchLds& L, int w, int lane,
-                                            int32_t last_pair) {
+                                            const Deal& deal, int32_t last_pair) {
   const int col = lane & (kQueryTile - 1), rg = lane >> 4;
   const float lo = G.band_lo, hi = G.band_hi;
   const Stream s = make_stream(v, G, L);
@@ -536,6 +591,7 @@ __device__ __forceinline__ void match_group(const BatchView& v, const TileGroup&
   wait_loads<0>();
   wait_lds();
   barrier();
+  gn = __builtin_amdgcn_readfirstlane(L.taken);
   const int32_t nblk0 = min(s.len, kBuf) / kBlock;
   issue_rows(s, L, 0, nblk0, par, w, lane);
   nv4u qr[TPW][2];
@@ -578,6 +634,9 @@ __device__ __forceinline__ void match_group(const BatchView& v, const TileGroup&
   // (After the second barrier: every wave's fetches are on their way first.  The
   // next group's first barrier orders the zeros before that set's next use.)
   if (w == 0 && last_pair >= 0) flush_stats(v, L.stats[par ^ 1], last_pair, lane);
+
+  int32_t ticket = 0;
+  if (next && v.tickets && w == 0 && lane == 0) ticket = draw(v, deal.own);
 
   uint32_t wcnt = 0;       // in-band slots of the wave (counts not kept per query)
   uint32_t wbl = 0;        // slots decided in FP64
@@ -769,6 +828,20 @@ __device__ __forceinline__ void match_group(const BatchView& v, const TileGroup&
     }
   }
 
+  // (Every wave has read L.taken: two barriers ago.  The write is complete
+  // before this wave's next barrier.)
+  if (next && w == 0) {
+    int32_t g2;
+    if (v.tickets) {
+      g2 = deal.first + kCounters * __builtin_amdgcn_readfirstlane(ticket);
+      if (g2 >= deal.end) g2 = draw_any(v, deal.shares, deal.own, lane);
+    } else {
+      const int32_t W = gn - g;
+      g2 = gn + W < deal.end ? gn + W : -1;
+    }
+    if (lane == 0) L.taken = g2;
+  }
+
   // Results (the binned position of the match) and statistics.
   int32_t tsum = 0;        // in-band slots of the tiles, by lane (counts kept or recomputed)
   uint32_t nacc = 0, ties = 0;
@@ -855,26 +928,31 @@ void match_kernel(BatchView v) {
   // everything derived from it (tile ranges, queue counts) in SGPRs.
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
   // Workgroup k runs on XCD x = k mod 8 (workgroups are dealt to the XCDs
-  // round-robin) and takes every W-th group of share x, W being the number of
-  // workgroups on that XCD.
+  // round-robin) and works on share x first.
   const int32_t shares = min(kXcds, int32_t(gridDim.x));
   const int32_t x = blockIdx.x % shares, i = blockIdx.x / shares;
   const int32_t W = (int32_t(gridDim.x) - x + shares - 1) / shares;
-  const int32_t g_first = ((c_i32*)v.wg_start)[x] + i;
-  const int32_t g_end = ((c_i32*)v.wg_start)[x + 1];
-  if (g_first >= g_end) return;   // uniform
+  Deal deal;
+  deal.shares = shares;
+  deal.own = x * kCounters + i % kCounters;
+  deal.end = ((c_i32*)v.wg_start)[x + 1];
+  int32_t g = ((c_i32*)v.wg_start)[x] + i;
+  deal.first = g - i + 2 * W + i % kCounters;
+  if (g >= deal.end) return;   // uniform
   if (threadIdx.x < 16) lds.stats[threadIdx.x >> 3][threadIdx.x & 7] = 0;
-  GroupStart<TPW> gs = start_group<TPW>(v, load_group(v.groups, g_first), lds, 0, wave, lane);
+  if (threadIdx.x == 0) lds.taken = g + W < deal.end ? g + W : -1;
+  GroupStart<TPW> gs = start_group<TPW>(v, load_group(v.groups, g), lds, 0, wave, lane);
   int par = 0;
   int32_t last_pair = -1;
-  for (int32_t g = g_first; g < g_end; g += W) {
+  while (g >= 0) {
     const TileGroup G = load_group(v.groups, g);
     GroupStart<TPW> gsn;
-    match_group<kKeepCounts, TPW>(v, G, g, gs, par, g + W < g_end ? g + W : -1, gsn, lds, wave,
-                                  lane, last_pair);
+    int32_t gn;
+    match_group<kKeepCounts, TPW>(v, G, g, gs, par, gn, gsn, lds, wave, lane, deal, last_pair);
     gs = gsn;
     par ^= 1;
     last_pair = G.pair;
+    g = gn;
   }
   wait_lds();
   barrier();

@@ -852,6 +852,7 @@ __global__ __launch_bounds__(256) void schedule_kernel(BatchView v, int32_t pb, 
   const int lane = threadIdx.x & 63;
   const int32_t p = pb + int32_t(blockIdx.x) * 4 + int32_t(threadIdx.x >> 6);
   if (p >= pb + pc) return;
+  if (p == pb && v.tickets && lane < kXcds * kCounters) v.tickets[kTicketStride * lane] = 0;
   // Cost before this pair and in total.
   long long before = 0, total = 0;
 #pragma unroll 4

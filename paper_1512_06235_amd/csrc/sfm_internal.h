@@ -12,6 +12,12 @@ constexpr int kDescBytes = 128;
 constexpr int kQueryTile = 16;          // queries per tile (MFMA N); also candidates per MFMA step
 constexpr int kMatchWaves = 4;          // waves per match workgroup
 constexpr int kXcds = 8;                // XCDs of the GPU (each with its own L2): schedule shares
+// The schedule's table: share starts, then (where the table has room, which it
+// has when the workgroups fill the GPU) counters, each on its own cache line.
+constexpr int kCounters = 4;            // per share
+constexpr int kTicketAt = 16;
+constexpr int kTicketStride = 32;
+constexpr int kScheduleInts = kTicketAt + kTicketStride * (kXcds * kCounters - 1) + 1;
 constexpr int kMaxGroupTiles = 8;       // query tiles sharing one candidate stream, at most
 constexpr int kDefaultGroupTiles = 8;   // the default (4 or 8: one or two tiles per wave)
 constexpr int kDefaultFeaturesPerBin = 8;
@@ -156,6 +162,7 @@ struct BatchView {
   int32_t* gcost;           // per tile group: estimated cost of matching it
   long long* pcost;         // per pair: the sum of its groups' costs
   int32_t* wg_start;        // share x (one per XCD) holds groups [wg_start[x], wg_start[x + 1])
+  int32_t* tickets;         // counters of the groups taken beyond each workgroup's first two, or NULL
   QueryResult* res;
   PairCounters* counters;
   const double* F;          // 9 per pair
