@@ -510,7 +510,7 @@ __device__ __forceinline__ void store_tile_window(const BatchView& v, const Pair
 // item lands at each position; a gather pass then writes the outputs in
 // position order, so the stores are coalesced instead of scattered 8- and
 // 16-byte writes that the L2 cannot merge once a batch outgrows it.
-template <int NT, bool kTargets>
+template <int NT, bool kIndexOnly, bool kTargets>
 __device__ __forceinline__ void sort_side(const BatchView& v, const PairDesc& P,
                                           const PairGeom& g, const ImageDev& I, int32_t* hist,
                                           int32_t* wsum, int32_t nh, uint16_t* perm) {
@@ -600,7 +600,7 @@ __device__ __forceinline__ void sort_side(const BatchView& v, const PairDesc& P,
   for (int32_t r = kCacheRounds; r < rounds; ++r) place_round(r, nullptr);
   if (!perm) return;
   __syncthreads();
-  if (NT == kBinThreadsFew) {
+  if (kIndexOnly) {
     // A batch of few pairs: the item of every position, in position order
     // (coalesced), into cand_j for targets (one of their outputs) or into
     // the records' index field for queries; gather_kernel then writes the
@@ -641,22 +641,29 @@ __device__ __forceinline__ void sort_side(const BatchView& v, const PairDesc& P,
 
 // LDS of the binning workgroup: the histogram, the scan's wave sums and,
 // when the side fits, the 16-bit permutation of its items.
+// 64 KB (two workgroups of 512 threads per CU) hold about 26,000 items at eight
+// per bin; a batch with a larger side takes 128 KB and 1,024 threads, one
+// workgroup per CU, up to 52,000: scattered records of 8 and 16 bytes cost more
+// than the second workgroup hides (200 pairs of 8,000 to 40,000: 277 us with
+// 64 KB, 150 with 128; 500 pairs of 2,000 to 20,000, which fit: 94 and 108).
 constexpr int kBinLdsInts = 16384;
+constexpr int kBinLdsIntsLarge = 32768;
 constexpr int kBinWsumMax = kBinThreadsFew / 64;
 static_assert(kMaxBins + 2 + kBinWsumMax <= kBinLdsInts, "histogram fits");
 
-// Whether a side of n items and nh bins sorts through an LDS permutation
-// (its records then come from gather_kernel) or scatters them directly.
-__host__ __device__ constexpr bool perm_fits(int32_t nh, int32_t n, int32_t wsum_ints) {
-  return ((nh + 2) & ~1) + (n + 1) / 2 <= kBinLdsInts - wsum_ints;
+// Whether a side of n items and nh bins sorts through an LDS permutation or
+// scatters its records directly.
+__host__ __device__ constexpr bool perm_fits(int32_t nh, int32_t n, int32_t lds_ints) {
+  return sort_ints(nh, n) <= lds_ints - kBinWsumMax;
 }
 
-template <int NT>
+// kIndexOnly: sides that sort through the permutation leave their records to
+// gather_kernel.
+template <int NT, int kLdsInts, bool kIndexOnly>
 __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(4)))
 void bin_kernel(BatchView v, int32_t pb, const int32_t* order) {
-  constexpr int kBinWsum = NT / 64;
-  __shared__ int32_t lds[kBinLdsInts];
-  int32_t* const wsum = lds + kBinLdsInts - kBinWsum;
+  __shared__ int32_t lds[kLdsInts];
+  int32_t* const wsum = lds + kLdsInts - kBinWsumMax;
   int32_t* const hist = lds;
   // Workgroup 2k + 1 sorts the targets and 2k the queries of the k-th pair
   // in `order`: both sides of the largest pairs are dispatched first, the
@@ -702,7 +709,7 @@ void bin_kernel(BatchView v, int32_t pb, const int32_t* order) {
   const int32_t n = targets ? P.nb : P.na;
   const int32_t hist_ints = (nh + 2) & ~1;
   uint16_t* perm = nullptr;
-  if (perm_fits(nh, n, kBinWsum)) perm = reinterpret_cast<uint16_t*>(lds + hist_ints);
+  if (perm_fits(nh, n, kLdsInts)) perm = reinterpret_cast<uint16_t*>(lds + hist_ints);
   if (targets) {
     // Padding after the pair's targets: a NaN x fails every band test.
     if (int(threadIdx.x) < kCandPad) {
@@ -712,9 +719,9 @@ void bin_kernel(BatchView v, int32_t pb, const int32_t* order) {
       v.cand_nc[o] = kKeyInf;
       v.cand_j[o] = 0;
     }
-    sort_side<NT, true>(v, P, g, I, hist, wsum, nh, perm);
+    sort_side<NT, kIndexOnly, true>(v, P, g, I, hist, wsum, nh, perm);
   } else {
-    sort_side<NT, false>(v, P, g, I, hist, wsum, nh, perm);
+    sort_side<NT, kIndexOnly, false>(v, P, g, I, hist, wsum, nh, perm);
   }
 }
 
@@ -728,7 +735,7 @@ void bin_kernel(BatchView v, int32_t pb, const int32_t* order) {
 // arithmetic over the GPU takes them off the one workgroup per side.
 constexpr int kGatherThreads = 256;
 __global__ __launch_bounds__(kGatherThreads) void gather_kernel(BatchView v, int32_t pb,
-                                                                int32_t wsum_ints) {
+                                                                int32_t lds_ints) {
   const int32_t p = pb + int32_t(blockIdx.x);
   const PairDesc P = v.pairs[p];
   const bool targets = blockIdx.z != 0;
@@ -737,7 +744,7 @@ __global__ __launch_bounds__(kGatherThreads) void gather_kernel(BatchView v, int
   if (P.ignore_band || base >= n) return;   // uniform
   const PairGeom& g = v.geom[p];
   const int32_t nh = targets ? g.nbins : g.nbins + 1;
-  if (!perm_fits(nh, n, wsum_ints)) return;   // scattered by bin_kernel itself
+  if (!perm_fits(nh, n, lds_ints)) return;   // scattered by bin_kernel itself
   const ImageDev& I = v.images[targets ? P.b : P.a];
   const int32_t pos = base + int32_t(threadIdx.x);
   const int32_t pc = min(pos, n - 1);
@@ -918,16 +925,24 @@ hipError_t launch_prepare(const BatchView& v, int32_t pb, int32_t pc, int32_t gr
   if (pc <= 0) return hipSuccess;
   hipLaunchKernelGGL(geometry_kernel, dim3((pc + 63) / 64), dim3(64), 0, st, v, pb, pc);
   const bool few = 2 * pc <= kFewPairsWorkgroups;
-  if (few)
-    hipLaunchKernelGGL(bin_kernel<kBinThreadsFew>, dim3(2 * pc), dim3(kBinThreadsFew), 0, st, v,
-                       pb, order);
+  const bool large = v.max_sort_ints > kBinLdsInts - kBinWsumMax;
+  const dim3 sides(2 * pc), few_threads(kBinThreadsFew);
+  if (few && large)
+    hipLaunchKernelGGL((bin_kernel<kBinThreadsFew, kBinLdsIntsLarge, true>), sides, few_threads,
+                       0, st, v, pb, order);
+  else if (few)
+    hipLaunchKernelGGL((bin_kernel<kBinThreadsFew, kBinLdsInts, true>), sides, few_threads, 0, st,
+                       v, pb, order);
+  else if (large)
+    hipLaunchKernelGGL((bin_kernel<kBinThreadsFew, kBinLdsIntsLarge, false>), sides, few_threads,
+                       0, st, v, pb, order);
   else
-    hipLaunchKernelGGL(bin_kernel<kBinThreads>, dim3(2 * pc), dim3(kBinThreads), 0, st, v, pb,
-                       order);
+    hipLaunchKernelGGL((bin_kernel<kBinThreads, kBinLdsInts, false>), sides, dim3(kBinThreads), 0,
+                       st, v, pb, order);
   if (few) {
     const int32_t nmax = std::max(std::max(max_queries, v.max_nb), 1);
     hipLaunchKernelGGL(gather_kernel, dim3(pc, (nmax + kGatherThreads - 1) / kGatherThreads, 2),
-                       dim3(kGatherThreads), 0, st, v, pb, kBinThreadsFew / 64);
+                       dim3(kGatherThreads), 0, st, v, pb, large ? kBinLdsIntsLarge : kBinLdsInts);
   }
   const int32_t tiles = (max_queries + kQueryTile - 1) / kQueryTile;
   const int32_t qblocks = (tiles + kRangeTiles - 1) / kRangeTiles;

@@ -28,6 +28,11 @@ constexpr uint32_t kKeyInf = 0xFFFFFFFFu;
 constexpr int32_t kDistInf = 0x7FFFFFFF;
 constexpr uint32_t kDistBias = 1u << 21;  // makes norm2(c) - 2 q.c >= 0
 constexpr int kMaxBins = 8192;          // LDS histogram size per pair
+// LDS words a side of n items in nh bins sorts in: its histogram and the 16-bit
+// permutation of its items.
+__host__ __device__ constexpr int32_t sort_ints(int32_t nh, int32_t n) {
+  return ((nh + 2) & ~1) + (n + 1) / 2;
+}
 constexpr int kBoxFeatures = 16;        // spatially sorted features sharing a bounding box
 constexpr int kOuterBoxes = 16;         // boxes sharing an outer box
 constexpr int kOuterFeatures = kBoxFeatures * kOuterBoxes;
@@ -169,6 +174,7 @@ struct BatchView {
   int32_t* err;             // device error flag
   int32_t n_pairs;
   int32_t total_blocks;
+  int32_t max_sort_ints;    // sort_ints() of the batch's largest side
   int32_t ratio_num, ratio_den;
   int32_t accept_single;
   int32_t keep_counts;

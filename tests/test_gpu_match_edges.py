@@ -46,3 +46,21 @@ def test_sizes_around_fills(sfm, oracle_lib, tiles, emit_all):
     out = m.match(pairs, [F] * len(pairs), emit_all=emit_all, recheck_margin_px=6e-3)
     compare_all(out, want, len(pairs))
     m.close()
+
+
+@pytest.mark.parametrize("n_pairs", [3, 130])
+@pytest.mark.parametrize("largest", [27000, 54000])
+def test_sides_around_the_sort_in_lds(sfm, oracle_lib, n_pairs, largest):
+    """Sides that sort through 64 KB of LDS, through 128 KB and not in LDS, in
+    batches of few and of many pairs."""
+    images = []
+    for k, n in enumerate([largest, 25000, 40]):
+        xy, desc, _, _, _ = random_pair(n, 0, seed=300 + k)
+        images.append((xy, desc))
+    F = scenes.make_two_view_2k().F
+    pairs = ([(2, 0, 2.0), (1, 2, 3.0), (2, 1, 0.5)] + [(2, 2, 4.0)] * n_pairs)[:n_pairs]
+    pairs[-1] = (0, 2, 3.0)
+    m = sfm.Matcher().register(images)
+    out = m.match(pairs, [F] * n_pairs, emit_all=True, recheck_margin_px=6e-3)
+    compare_all(out, oracle_lib.match(images, pairs, [F] * n_pairs), n_pairs)
+    m.close()
