@@ -497,18 +497,18 @@ bool epipole_near_box(const double* F, const float* bb, double half) {
 
 // Whether pairs [0, n) of pd, with matrices F, are matched directly
 // (kernels_direct.hip) or binned, by estimates in microseconds fitted to both
-// forms on 42 calls: 1 pair of 300 to 32,000 features (band 2, 4 and 8 px), 2 to
-// 200 pairs of 300 to 16,000, epipoles inside the image.  (Calls of one
-// process, direct against binned: a pair of 300 features 22 / 43 us, 2,000:
-// 27 / 50, 8,000: 45 / 63, 16,000: 77 / 88; 16,000 with an 8 px band 101 / 97,
-// 24,000: 136 / 107; 37 pairs of 500: 32 / 52, of 301 to 6,007: 96 / 80;
-// epipole inside the image, 7,000: 44 / 439.)
+// forms on 48 calls: 1 pair of 300 to 32,000 features (band 2, 4 and 8 px), 2 to
+// 200 pairs of 300 to 20,000, epipoles inside the image.  (Direct against
+// binned: a pair of 300 features 23 / 44 us, 2,000: 27 / 50, 8,000: 45 / 61,
+// 12,000: 58 / 68, 16,000: 78 / 75, 24,000: 134 / 90; 12,000 with an 8 px band
+// 77 / 75; 8 pairs of 2,000: 35 / 50, 37 of 500: 31 / 52, 30 of 3,000: 96 / 57;
+// epipole inside the image, 7,000: 44 / 428.)
 bool direct_pays(const sfm_ctx* ctx, const PairDesc* pd, const double* F, int32_t n,
                  double margin) {
   // The binned form counts borderline slots within its windows, which are
   // kBandSlackPx wider than the band.
   if (margin > 0.5 * kBandSlackPx) return false;
-  double cost = 0.0, binned = 43.0, side = 0.0;
+  double cost = 0.0, binned = 43.0 + 0.1 * n, side = 0.0;
   for (int32_t k = 0; k < n; ++k) {
     const PairDesc& P = pd[k];
     if (P.nb > kDirectMaxTargets) return false;
@@ -522,12 +522,12 @@ bool direct_pays(const sfm_ctx* ctx, const PairDesc* pd, const double* F, int32_
     const double hit = std::min(boxes, 2.0 * std::sqrt(boxes) + share * boxes);
     cost += double(P.na) * (60.0 + 3.0 * hit + 1.5 * share * double(P.nb));
     side = std::max(side, double(std::max(P.na, P.nb)));
-    binned += 2.2e-4 * P.na;
+    binned += 1e-4 * P.na;
     if (!(P.band < 1e30) || epipole_near_box(F + 9 * size_t(k), bb, P.band + kBandSlackPx))
       binned += 3e-6 * double(P.na) * double(P.nb);
     if (21.0 + 7.5e-6 * cost > 400.0 + binned) return false;   // large batches end here soon
   }
-  return 21.0 + 7.5e-6 * cost < binned + 2.5e-3 * side;
+  return 21.0 + 7.5e-6 * cost < binned + 2e-3 * side;
 }
 
 // One matching call over the images of `tab`; the caller holds ctx->mu.
