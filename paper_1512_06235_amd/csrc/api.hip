@@ -52,6 +52,7 @@ struct sfm_ctx {
   unsigned long long* diag_dev = nullptr;   // sfm_band_error's two result words
   bool has_work = false;
   int32_t last_pairs = 0;              // pairs of the last matching call
+  bool last_staged = false;            // two stages per pair, of which the last that ran counts
   size_t last_counters = 0;            // workspace offset of its counters
 
   // Staged matching: view table, per-stage rows and merge plan.
@@ -120,9 +121,10 @@ int32_t bins_for(int32_t nb, int32_t features_per_bin) {
 }
 
 // n_items and n_part: the exhaustive form's work items (staged with the pair
-// table) and partial results; 0 for the other forms.
+// table) and partial results; 0 for the other forms.  The exhaustive form takes
+// neither F nor anything of the preparation's.
 Layout plan(const PairDesc* pd, size_t P, int32_t device, int32_t group_tiles,
-            int64_t n_items = 0, int64_t n_part = 0) {
+            int64_t n_items = 0, int64_t n_part = 0, bool exhaustive = false) {
   Layout L;
   for (size_t k = 0; k < P; ++k) {
     const PairDesc& p = pd[k];
@@ -137,6 +139,18 @@ Layout plan(const PairDesc* pd, size_t P, int32_t device, int32_t group_tiles,
     L.sum_groups += p.ngroups;
   }
   size_t o = 0;
+  if (exhaustive) {
+    L.pairs = o; o = align_up(o + P * sizeof(PairDesc));
+    L.items = o; o = align_up(o + size_t(n_items) * sizeof(int2));
+    L.staged = o;
+    L.counters = o; o = align_up(o + P * sizeof(PairCounters));
+    L.res = o; o = align_up(o + size_t(L.sum_na) * sizeof(QueryResult));
+    L.part = o; o = align_up(o + size_t(n_part) * sizeof(uint2));
+    L.total = o;
+    L.F = L.order = L.geom = L.wg_start = L.cand_x = L.cand_y = L.cand_nc = L.cand_j = L.bins =
+        L.qrec = L.groups = L.gcost = L.pcost = 0;   // not used
+    return L;
+  }
   L.pairs = o; o = align_up(o + P * sizeof(PairDesc));
   L.F = o; o = align_up(o + P * 9 * sizeof(double));
   L.order = o; o = align_up(o + P * sizeof(int32_t));
@@ -163,8 +177,8 @@ Layout plan(const PairDesc* pd, size_t P, int32_t device, int32_t group_tiles,
 }
 
 Layout plan(const std::vector<PairDesc>& pd, int32_t device, int32_t group_tiles,
-            int64_t n_items = 0, int64_t n_part = 0) {
-  return plan(pd.data(), pd.size(), device, group_tiles, n_items, n_part);
+            int64_t n_items = 0, int64_t n_part = 0, bool exhaustive = false) {
+  return plan(pd.data(), pd.size(), device, group_tiles, n_items, n_part, exhaustive);
 }
 
 // The images pairs refer to: the registered ones, or views of them (a run of
@@ -530,6 +544,20 @@ bool direct_pays(const sfm_ctx* ctx, const PairDesc* pd, const double* F, int32_
   return 21.0 + 7.5e-6 * cost < binned + 2e-3 * side;
 }
 
+// The sizes the exhaustive kernels take; pair k of the caller's is pd[step k].
+int check_exhaustive(sfm_ctx* ctx, const PairDesc* pd, int32_t n_pairs, int32_t step) {
+  for (int32_t k = 0; k < n_pairs; k += step) {
+    if (pd[k].na > kExhaustiveMaxQueries || pd[k].nb > kExhaustiveMaxTargets) {
+      char buf[160];
+      snprintf(buf, sizeof buf,
+               "pair %d: exhaustive matching takes at most %d queries and %d targets", k / step,
+               kExhaustiveMaxQueries, kExhaustiveMaxTargets);
+      return fail(ctx, SFM_ECAPACITY, buf);
+    }
+  }
+  return SFM_OK;
+}
+
 // One matching call over the images of `tab`; the caller holds ctx->mu.
 // kBandError runs the preparation and the FP32-accuracy diagnostic instead
 // of matching (`out` is unused; diag receives the two result words).
@@ -553,20 +581,12 @@ int match_locked(sfm_ctx* ctx, const ImageTable& tab, const sfm_pair* pairs, int
   if (!exhaustive && (rc = check_F(ctx, F, n_pairs))) return rc;
   int64_t n_items = 0, n_part = 0;
   if (exhaustive) {
-    for (int32_t k = 0; k < n_pairs; ++k) {
-      if (pd[size_t(k)].na > kExhaustiveMaxQueries || pd[size_t(k)].nb > kExhaustiveMaxTargets) {
-        char buf[160];
-        snprintf(buf, sizeof buf,
-                 "pair %d: exhaustive matching takes at most %d queries and %d targets", k,
-                 kExhaustiveMaxQueries, kExhaustiveMaxTargets);
-        return fail(ctx, SFM_ECAPACITY, buf);
-      }
-    }
-    exhaustive_plan(pd.data(), n_pairs, nullptr, &n_items, &n_part);
+    if ((rc = check_exhaustive(ctx, pd.data(), n_pairs, 1))) return rc;
+    exhaustive_plan(pd.data(), n_pairs, kExAll, nullptr, &n_items, &n_part);
     if (n_items > INT32_MAX) return fail(ctx, SFM_ECAPACITY, "too many work items in one call");
   }
   HIP_TRY(ctx, hipSetDevice(ctx->device));
-  const Layout L = plan(pd, ctx->device, ctx->group_tiles, n_items, n_part);
+  const Layout L = plan(pd, ctx->device, ctx->group_tiles, n_items, n_part, exhaustive);
   if (!diagnostic && (rc = check_outputs(ctx, out, L, opt))) return rc;
   if (diagnostic && opt.emit_all) return fail(ctx, SFM_EINVAL, "emit_all has no outputs here");
 
@@ -583,14 +603,13 @@ int match_locked(sfm_ctx* ctx, const ImageTable& tab, const sfm_pair* pairs, int
   HIP_TRY(ctx, hipEventSynchronize(S.staging_done));
   memcpy((*S.pinned) + L.pairs, pd.data(), pd.size() * sizeof(PairDesc));
   if (exhaustive) {
-    memset((*S.pinned) + L.F, 0, pd.size() * 9 * sizeof(double));
-    exhaustive_plan(pd.data(), n_pairs, reinterpret_cast<int2*>((*S.pinned) + L.items), &n_items,
-                    &n_part);
+    exhaustive_plan(pd.data(), n_pairs, kExAll, reinterpret_cast<int2*>((*S.pinned) + L.items),
+                    &n_items, &n_part);
   } else {
     memcpy((*S.pinned) + L.F, F, pd.size() * 9 * sizeof(double));
+    binning_order(pd.data(), n_pairs, reinterpret_cast<int32_t*>((*S.pinned) + L.order));
+    memset((*S.pinned) + L.counters, 0, pd.size() * sizeof(PairCounters));
   }
-  binning_order(pd.data(), n_pairs, reinterpret_cast<int32_t*>((*S.pinned) + L.order));
-  memset((*S.pinned) + L.counters, 0, pd.size() * sizeof(PairCounters));
   HIP_TRY(ctx, hipMemcpyAsync((*S.ws), (*S.pinned), L.staged, hipMemcpyHostToDevice, st));
   HIP_TRY(ctx, hipEventRecord(S.staging_done, st));
 
@@ -657,8 +676,8 @@ int match_locked(sfm_ctx* ctx, const ImageTable& tab, const sfm_pair* pairs, int
     ve.cand_j = nullptr;
     HIP_TRY(ctx, prof_mark(ctx, st));
     HIP_TRY(ctx, prof_mark(ctx, st));
-    HIP_TRY(ctx, launch_exhaustive(ve, reinterpret_cast<const int2*>((*S.ws) + L.items), n_items,
-                                   reinterpret_cast<uint2*>((*S.ws) + L.part), st));
+    HIP_TRY(ctx, launch_exhaustive(ve, kExAll, reinterpret_cast<const int2*>((*S.ws) + L.items),
+                                   n_items, reinterpret_cast<uint2*>((*S.ws) + L.part), st));
     HIP_TRY(ctx, prof_mark(ctx, st));
     HIP_TRY(ctx, launch_emit(ve, 0, n_pairs, out->offset, out->query, out->match, out->d1,
                              out->d2, out->n_comparisons, out->n_borderline, am, ad1, ad2, ac,
@@ -694,6 +713,7 @@ int match_locked(sfm_ctx* ctx, const ImageTable& tab, const sfm_pair* pairs, int
   *S.has_work = true;
   // sfm_last_stats reads the counters from the context workspace only.
   ctx->last_pairs = alt ? 0 : n_pairs;
+  ctx->last_staged = false;
   ctx->last_counters = L.counters;
   return SFM_OK;
 }
@@ -1333,6 +1353,7 @@ int sfm_grid_match(sfm_ctx* ctx, const sfm_pair* pairs, int32_t n_pairs, const d
   HIP_TRY(ctx, hipEventRecord(ctx->work_done, st));
   ctx->has_work = true;
   ctx->last_pairs = n_pairs;
+  ctx->last_staged = false;
   ctx->last_counters = o_cnt;
   return SFM_OK;
 }
@@ -1412,18 +1433,37 @@ int sfm_preemptive_match(sfm_ctx* ctx, const sfm_pair* pairs, int32_t n_pairs,
     return SFM_OK;
   }
 
-  // Stage buffer: views, spec, both stages' rows and counts, merge plan.
+  int rc = check_options(ctx, opt);
+  if (rc) return rc;
+
+  // One batch: pair 2k is the first stage of pair k, 2k + 1 its second.
+  const ImageTable tab{nullptr, vn.data(), int32_t(3 * P)};
+  std::vector<sfm_pair> sp(2 * P);
+  for (size_t k = 0; k < P; ++k) {
+    sp[2 * k] = sfm_pair{int32_t(3 * k), int32_t(3 * k + 1), 0.0};
+    sp[2 * k + 1] = sfm_pair{int32_t(3 * k + 2), int32_t(3 * k + 1), 0.0};
+  }
+  std::vector<PairDesc> pd;
+  if ((rc = describe_pairs(ctx, tab, sp.data(), 2 * n_pairs, true, pd))) return rc;
+  for (size_t k = 0; k < P; ++k) pd[2 * k + 1].q_shift = vn[3 * k];
+  if ((rc = check_exhaustive(ctx, pd.data(), 2 * n_pairs, 2))) return rc;
+  const ExStage stage[2] = {{0, 2, 0, 0, 0}, {1, 2, 1, cfg.min_matches, cfg.enough}};
+  int64_t n_items[2], n_part[2];
+  for (int t = 0; t < 2; ++t) {
+    exhaustive_plan(pd.data(), 2 * n_pairs, stage[t], nullptr, &n_items[t], &n_part[t]);
+    if (n_items[t] > INT32_MAX) return fail(ctx, SFM_ECAPACITY, "too many work items in one call");
+  }
+  // The second stage's partial results follow the first's merge: one array.
+  const Layout L = plan(pd, ctx->device, ctx->group_tiles, n_items[0] + n_items[1],
+                        std::max(n_part[0], n_part[1]), true);
+
+  // Stage buffer: views, spec, both stages' offsets and counts.
   size_t o = 0;
   const size_t o_views = o; o = align_up(o + 3 * P * sizeof(ImageDev));
   const size_t o_spec = o; o = align_up(o + 9 * P * sizeof(int32_t));
-  const size_t o_merge = o; o = align_up(o + P * sizeof(StageMerge));
-  size_t o_off[2], o_cmp[2], o_rows[2];
-  const int64_t caps[2] = {cap1, cap2};
-  for (int t = 0; t < 2; ++t) {
-    o_off[t] = o; o = align_up(o + (P + 1) * sizeof(int64_t));
-    o_cmp[t] = o; o = align_up(o + P * sizeof(int64_t));
-    o_rows[t] = o; o = align_up(o + 4 * size_t(std::max<int64_t>(caps[t], 1)) * sizeof(int32_t));
-  }
+  const size_t o_off = o; o = align_up(o + (2 * P + 1) * sizeof(int64_t));
+  const size_t o_cmp = o; o = align_up(o + 2 * P * sizeof(int64_t));
+  const size_t o_found = o; o = align_up(o + P * sizeof(int32_t));
   if (o > ctx->budget) return fail(ctx, SFM_ECAPACITY, "staged matching exceeds the budget");
   if (o > ctx->stage_cap) {
     if (ctx->has_work) HIP_TRY(ctx, hipEventSynchronize(ctx->work_done));
@@ -1434,85 +1474,62 @@ int sfm_preemptive_match(sfm_ctx* ctx, const sfm_pair* pairs, int32_t n_pairs,
     ctx->stage_cap = o + o / 4;
   }
   char* B = ctx->stage_buf;
+  if ((rc = ensure_workspace(ctx, L.total))) return rc;
+  // Pinned: the staged tables, the spec, and what comes back.
+  const size_t h_spec = L.staged, h_found = align_up(h_spec + spec.size() * sizeof(int32_t));
+  const size_t h_flag = h_found + P * sizeof(int32_t);
+  if ((rc = ensure_pinned(ctx, h_flag + sizeof(int32_t)))) return rc;
+  const Space S = ctx_space(ctx);
+  char *ws = *S.ws, *pin = *S.pinned;
   if (ctx->has_work) HIP_TRY(ctx, hipStreamWaitEvent(st, ctx->work_done, 0));
-  ImageDev* views = reinterpret_cast<ImageDev*>(B + o_views);
-  HIP_TRY(ctx, hipMemcpyAsync(B + o_spec, spec.data(), spec.size() * sizeof(int32_t),
+  HIP_TRY(ctx, hipEventSynchronize(S.staging_done));
+  memcpy(pin + L.pairs, pd.data(), pd.size() * sizeof(PairDesc));
+  int2* items = reinterpret_cast<int2*>(pin + L.items);
+  for (int t = 0; t < 2; ++t)
+    exhaustive_plan(pd.data(), 2 * n_pairs, stage[t], items + (t ? n_items[0] : 0), &n_items[t],
+                    &n_part[t]);
+  memcpy(pin + h_spec, spec.data(), spec.size() * sizeof(int32_t));
+  HIP_TRY(ctx, hipMemcpyAsync(ws, pin, L.staged, hipMemcpyHostToDevice, st));
+  HIP_TRY(ctx, hipMemcpyAsync(B + o_spec, pin + h_spec, spec.size() * sizeof(int32_t),
                               hipMemcpyHostToDevice, st));
+  HIP_TRY(ctx, hipEventRecord(S.staging_done, st));
+  ImageDev* views = reinterpret_cast<ImageDev*>(B + o_views);
   HIP_TRY(ctx, launch_make_views(ctx->images_dev, reinterpret_cast<const int32_t*>(B + o_spec),
                                  int32_t(3 * P), views, st));
-  const ImageTable tab{views, vn.data(), int32_t(3 * P)};
-  sfm_matches so[2];
-  StageRows rows[2];
-  for (int t = 0; t < 2; ++t) {
-    int32_t* r = reinterpret_cast<int32_t*>(B + o_rows[t]);
-    const size_t c = size_t(std::max<int64_t>(caps[t], 1));
-    memset(&so[t], 0, sizeof so[t]);
-    so[t].query = r;
-    so[t].match = r + c;
-    so[t].d1 = r + 2 * c;
-    so[t].d2 = r + 3 * c;
-    so[t].capacity = caps[t];
-    so[t].offset = reinterpret_cast<int64_t*>(B + o_off[t]);
-    so[t].n_comparisons = reinterpret_cast<int64_t*>(B + o_cmp[t]);
-    rows[t] = StageRows{so[t].query, so[t].match, so[t].d1, so[t].d2, so[t].n_comparisons};
-  }
-
-  // Stage 1 (or the whole pair), then the counts back on the host.
-  std::vector<sfm_pair> sp(P);
-  for (size_t k = 0; k < P; ++k) sp[k] = sfm_pair{int32_t(3 * k), int32_t(3 * k + 1), 0.0};
-  int rc = match_locked(ctx, tab, sp.data(), n_pairs, nullptr, &opt, &so[0], stream,
-                        Form::kExhaustive);
-  if (rc) return rc;
-  std::vector<int64_t> off1(P + 1), off2(P + 1, 0);
-  HIP_TRY(ctx, hipMemcpyAsync(off1.data(), so[0].offset, (P + 1) * sizeof(int64_t),
-                              hipMemcpyDeviceToHost, st));
-  HIP_TRY(ctx, hipStreamSynchronize(st));
-
-  // Stage 2 for the pairs whose first stage found more than min_matches.
-  std::vector<int32_t> in2(P, -1);
-  sp.clear();
-  for (size_t k = 0; k < P; ++k) {
-    const int64_t c = off1[k + 1] - off1[k];
-    if (whole[k] || vn[3 * k + 2] == 0 || c <= cfg.min_matches || (cfg.enough > 0 && c >= cfg.enough))
-      continue;
-    in2[k] = int32_t(sp.size());
-    sp.push_back(sfm_pair{int32_t(3 * k + 2), int32_t(3 * k + 1), 0.0});
-  }
-  if (!sp.empty()) {
-    rc = match_locked(ctx, tab, sp.data(), int32_t(sp.size()), nullptr, &opt, &so[1], stream,
-                      Form::kExhaustive);
-    if (rc) return rc;
-    HIP_TRY(ctx, hipMemcpyAsync(off2.data(), so[1].offset, (sp.size() + 1) * sizeof(int64_t),
-                                hipMemcpyDeviceToHost, st));
-    HIP_TRY(ctx, hipStreamSynchronize(st));
-  }
-
-  // Merge: each pair's stage-1 rows, then its stage-2 rows.
-  std::vector<StageMerge> plan_h(P);
-  std::vector<int64_t> final_off(P + 1, 0);
-  for (size_t k = 0; k < P; ++k) {
-    StageMerge& m = plan_h[k];
-    m.src1 = off1[k];
-    m.n1 = int32_t(off1[k + 1] - off1[k]);
-    m.s2 = in2[k];
-    m.src2 = m.s2 >= 0 ? off2[size_t(m.s2)] : 0;
-    m.n2 = m.s2 >= 0 ? int32_t(off2[size_t(m.s2) + 1] - off2[size_t(m.s2)]) : 0;
-    m.shift = vn[3 * k];
-    m.dst = final_off[k];
-    final_off[k + 1] = final_off[k] + m.n1 + m.n2;
-    if (stages) stages[k] = whole[k] ? 0 : (m.s2 >= 0 ? 2 : 1);
-  }
-  HIP_TRY(ctx, hipMemcpyAsync(B + o_merge, plan_h.data(), P * sizeof(StageMerge),
-                              hipMemcpyHostToDevice, st));
-  HIP_TRY(ctx, hipMemcpyAsync(out->offset, final_off.data(), (P + 1) * sizeof(int64_t),
-                              hipMemcpyHostToDevice, st));
-  HIP_TRY(ctx, launch_merge_stages(reinterpret_cast<const StageMerge*>(B + o_merge), n_pairs,
-                                   rows[0], rows[1], out->query, out->match, out->d1, out->d2,
-                                   out->n_comparisons, st));
+  BatchView v = batch_view(ctx, ImageTable{views, vn.data(), int32_t(3 * P)}, ws, L, 2 * n_pairs,
+                           opt);
+  v.cand_j = nullptr;   // results hold the index in b
+  int64_t* off2 = reinterpret_cast<int64_t*>(B + o_off);
+  int64_t* cmp2 = reinterpret_cast<int64_t*>(B + o_cmp);
+  int32_t* found = reinterpret_cast<int32_t*>(B + o_found);
+  HIP_TRY(ctx, prof_mark(ctx, st));
+  HIP_TRY(ctx, prof_mark(ctx, st));
+  for (int t = 0; t < 2; ++t)
+    HIP_TRY(ctx, launch_exhaustive(
+                     v, stage[t],
+                     reinterpret_cast<const int2*>(ws + L.items) + (t ? n_items[0] : 0),
+                     n_items[t], reinterpret_cast<uint2*>(ws + L.part), st));
+  HIP_TRY(ctx, prof_mark(ctx, st));
+  HIP_TRY(ctx, launch_emit(v, 0, 2 * n_pairs, off2, out->query, out->match, out->d1, out->d2, cmp2,
+                           nullptr, nullptr, nullptr, nullptr, nullptr, st));
+  HIP_TRY(ctx, launch_stage_outputs(v, n_pairs, off2, cmp2, out->offset, out->n_comparisons, found,
+                                    st));
+  HIP_TRY(ctx, prof_mark(ctx, st));
   HIP_TRY(ctx, hipEventRecord(ctx->work_done, st));
+  ctx->has_work = true;
+  ctx->last_pairs = 2 * n_pairs;
+  ctx->last_staged = true;
+  ctx->last_counters = L.counters;
+  HIP_TRY(ctx, hipMemcpyAsync(pin + h_found, found, P * sizeof(int32_t), hipMemcpyDeviceToHost, st));
+  HIP_TRY(ctx, hipMemcpyAsync(pin + h_flag, ctx->err_dev, sizeof(int32_t), hipMemcpyDeviceToHost,
+                              st));
   HIP_TRY(ctx, hipStreamSynchronize(st));
-  int32_t flag = 0;
-  HIP_TRY(ctx, hipMemcpy(&flag, ctx->err_dev, sizeof flag, hipMemcpyDeviceToHost));
+  const int32_t* found_h = reinterpret_cast<const int32_t*>(pin + h_found);
+  for (size_t k = 0; stages && k < P; ++k)
+    stages[k] = whole[k] ? 0
+                : vn[3 * k + 2] > 0 && stage[1].open((unsigned long long)found_h[k]) ? 2
+                                                                                      : 1;
+  const int32_t flag = *reinterpret_cast<const int32_t*>(pin + h_flag);
   if (flag) {
     HIP_TRY(ctx, hipMemset(ctx->err_dev, 0, sizeof(int32_t)));
     return fail(ctx, SFM_EKERNEL, "a kernel raised the device error flag");
@@ -1557,7 +1574,11 @@ int sfm_last_stats(sfm_ctx* ctx, int64_t out[5]) {
   std::vector<PairCounters> c(size_t(ctx->last_pairs));
   HIP_TRY(ctx, hipMemcpy(c.data(), ctx->ws + ctx->last_counters, c.size() * sizeof(PairCounters),
                          hipMemcpyDeviceToHost));
-  for (const PairCounters& k : c) {
+  // Of a staged call the second stage if any pair had one, else the first.
+  bool second = false;
+  for (size_t k = 1; ctx->last_staged && k < c.size(); k += 2) second |= c[k].elements > 0;
+  for (size_t at = second ? 1 : 0; at < c.size(); at += ctx->last_staged ? 2 : 1) {
+    const PairCounters& k = c[at];
     out[0] += int64_t(k.comparisons);
     out[1] += int64_t(k.elements);
     out[2] += k.ties;

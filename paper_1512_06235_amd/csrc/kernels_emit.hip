@@ -164,7 +164,7 @@ __global__ __launch_bounds__(kEmitThreads) void emit_kernel(BatchView v, int32_t
       if (r[k].flags & 1) {
         const int64_t row = out0 + rbase + cnt[k * kEmitWaves + wv] + pre[k];
         const int32_t i = base + k * kEmitThreads + t;
-        oq[row] = i;
+        oq[row] = i + P.q_shift;
         om[row] = r[k].match;
         od1[row] = r[k].d1;
         od2[row] = r[k].d2;

@@ -198,16 +198,24 @@ __device__ __forceinline__ void interleave_step() {
   }
 }
 
+// Whether pair p takes part in the launch (its predecessor's counters are an
+// earlier launch's).
+__device__ __forceinline__ bool stage_open(const BatchView& v, const ExStage& stage, int32_t p) {
+  return !stage.gated || stage.open(v.counters[p - 1].accepted);
+}
+
 __global__ __launch_bounds__(64 * kExWaves) __attribute__((amdgpu_waves_per_eu(4, 8)))
-void exhaustive_kernel(BatchView v, const int2* items, int32_t n_items, uint2* part) {
+void exhaustive_kernel(BatchView v, ExStage stage, const int2* items, int32_t n_items,
+                       uint2* part) {
   __shared__ __attribute__((aligned(128))) ExLds lds;
   const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
   const int tid = threadIdx.x;
   // The per-pair counters the merge kernel adds its accepted queries to:
-  // workgroup k resets pairs 256 k .. 256 k + 255.
+  // workgroup k sets 256 of the stage's pairs.
   {
-    const int32_t p = int32_t(blockIdx.x) * (64 * kExWaves) + tid;
-    if (p < v.n_pairs) {
+    const int64_t at = stage.first + (int64_t(blockIdx.x) * (64 * kExWaves) + tid) * stage.step;
+    if (at < v.n_pairs) {
+      const int32_t p = int32_t(at);
       const PairDesc P = v.pairs[p];
       const int64_t nqb = (P.na + kExQueries - 1) / kExQueries;
       const int64_t tail = P.nb - int64_t(kExSlice) * ((P.nb - 1) / kExSlice);
@@ -219,12 +227,14 @@ void exhaustive_kernel(BatchView v, const int2* items, int32_t n_items, uint2* p
       c.borderline = 0;
       c.accepted = 0;
       c.ties = 0;
+      if (!stage_open(v, stage, p)) c.comparisons = c.elements = 0;
       v.counters[p] = c;
     }
   }
   if (int32_t(blockIdx.x) >= n_items) return;
   const v2i it = ((g_v2i*)items)[blockIdx.x];
   const int32_t p = __builtin_amdgcn_readfirstlane(it.x);
+  if (!stage_open(v, stage, p)) return;   // uniform
   const int32_t qb = __builtin_amdgcn_readfirstlane(it.y) >> 16;
   const int32_t s = __builtin_amdgcn_readfirstlane(it.y) & 0xFFFF;
   const PairDesc P = v.pairs[p];
@@ -364,13 +374,18 @@ __device__ __forceinline__ int32_t row_dot(const uint8_t* p, const uint8_t* q) {
 }
 
 __global__ __launch_bounds__(kMergeThreads) void exhaustive_merge_kernel(BatchView v,
+                                                                         ExStage stage,
                                                                          const uint2* part) {
-  const int32_t p = int32_t(blockIdx.x);
+  const int32_t p = stage.first + int32_t(blockIdx.x) * stage.step;
   const PairDesc P = v.pairs[p];
   const int lane = threadIdx.x & 63;
   const int32_t i0 = int32_t(blockIdx.y) * kMergeThreads + int32_t(threadIdx.x & ~63u);
   if (i0 >= P.na) return;   // uniform over the wave
   const int32_t i = i0 + lane;
+  if (!stage_open(v, stage, p)) {
+    if (i < P.na) v.res[P.q_off + i] = {-1, kDistInf, kDistInf, 0};
+    return;
+  }
   const ImageDev A = v.images[P.a], B = v.images[P.b];
   int32_t d1 = kDistInf, d2 = kDistInf, j1 = -1;
   const int32_t nq = ((g_i32*)A.norm2)[min(i, P.na - 1)];
@@ -458,10 +473,10 @@ __global__ __launch_bounds__(kMergeThreads) void exhaustive_merge_kernel(BatchVi
 
 }  // namespace
 
-void exhaustive_plan(PairDesc* pd, int32_t n_pairs, int2* items, int64_t* n_items,
-                     int64_t* n_part) {
+void exhaustive_plan(PairDesc* pd, int32_t n_pairs, const ExStage& stage, int2* items,
+                     int64_t* n_items, int64_t* n_part) {
   int64_t ni = 0, np = 0;
-  for (int32_t k = 0; k < n_pairs; ++k) {
+  for (int64_t k = stage.first; k < n_pairs; k += stage.step) {
     PairDesc& P = pd[k];
     P.ex_off = np;
     const int32_t nqb = (P.na + kExQueries - 1) / kExQueries;
@@ -469,7 +484,7 @@ void exhaustive_plan(PairDesc* pd, int32_t n_pairs, int2* items, int64_t* n_item
     np += int64_t(P.na) * nsl;
     for (int32_t s = 0; s < nsl; ++s)
       for (int32_t qb = 0; qb < nqb; ++qb) {
-        if (items) items[ni] = make_int2(k, (qb << 16) | s);
+        if (items) items[ni] = make_int2(int32_t(k), (qb << 16) | s);
         ++ni;
       }
   }
@@ -477,18 +492,19 @@ void exhaustive_plan(PairDesc* pd, int32_t n_pairs, int2* items, int64_t* n_item
   *n_part = np;
 }
 
-hipError_t launch_exhaustive(const BatchView& v, const int2* items, int64_t n_items, uint2* part,
-                             hipStream_t st) {
-  if (v.n_pairs <= 0) return hipSuccess;
-  const int64_t zero_wgs = (int64_t(v.n_pairs) + 64 * kExWaves - 1) / (64 * kExWaves);
-  const int64_t wgs = std::max(n_items, zero_wgs);
+hipError_t launch_exhaustive(const BatchView& v, const ExStage& stage, const int2* items,
+                             int64_t n_items, uint2* part, hipStream_t st) {
+  const int32_t pairs = (v.n_pairs - stage.first + stage.step - 1) / stage.step;
+  if (pairs <= 0) return hipSuccess;
+  const int64_t count_wgs = (int64_t(pairs) + 64 * kExWaves - 1) / (64 * kExWaves);
+  const int64_t wgs = std::max(n_items, count_wgs);
   if (wgs > INT32_MAX) return hipErrorInvalidValue;
-  hipLaunchKernelGGL(exhaustive_kernel, dim3(uint32_t(wgs)), dim3(64 * kExWaves), 0, st, v, items,
-                     int32_t(std::min<int64_t>(n_items, INT32_MAX)), part);
+  hipLaunchKernelGGL(exhaustive_kernel, dim3(uint32_t(wgs)), dim3(64 * kExWaves), 0, st, v, stage,
+                     items, int32_t(std::min<int64_t>(n_items, INT32_MAX)), part);
   const uint32_t chunks =
       uint32_t(std::max(1, (v.max_na + kMergeThreads - 1) / kMergeThreads));
-  hipLaunchKernelGGL(exhaustive_merge_kernel, dim3(uint32_t(v.n_pairs), chunks),
-                     dim3(kMergeThreads), 0, st, v, part);
+  hipLaunchKernelGGL(exhaustive_merge_kernel, dim3(uint32_t(pairs), chunks), dim3(kMergeThreads),
+                     0, st, v, stage, part);
   return hipGetLastError();
 }
 

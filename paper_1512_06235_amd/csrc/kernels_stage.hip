@@ -3,8 +3,12 @@
 // target image's, a second stage the next run of queries against the same
 // targets.  Features are registered in decreasing scale, so a prefix is the
 // highest-scale part of an image; a stage is the exhaustive matcher run on
-// views that point into the registered arrays, and a merge kernel places each
-// pair's rows of both stages one after the other in query order.
+// views that point into the registered arrays.  The two stages of a pair are
+// neighbours in one batch: the second's kernels read on the device whether the
+// first found enough, and one emission writes each pair's rows of both stages
+// one after the other in query order.  (With the counts back on the host
+// between the stages, a merge of both stages' rows and the rest of two calls,
+// 1,770 pairs took 947 us for 508 of matching; 733 now.)
 #include <algorithm>
 
 #include "sfm_internal.h"
@@ -32,31 +36,17 @@ __global__ __launch_bounds__(256) void make_views_kernel(const ImageDev* images,
   }
 }
 
-// One workgroup per pair: copy its first-stage rows, then its second-stage
-// rows with query indices moved past the first stage's queries.
-__global__ __launch_bounds__(256) void merge_stages_kernel(const StageMerge* merge,
-                                                           int32_t n_pairs, StageRows one,
-                                                           StageRows two, int32_t* oq,
-                                                           int32_t* om, int32_t* od1,
-                                                           int32_t* od2, int64_t* ocmp) {
-  for (int32_t p = blockIdx.x; p < n_pairs; p += gridDim.x) {
-    const StageMerge M = merge[p];
-    for (int32_t i = threadIdx.x; i < M.n1; i += blockDim.x) {
-      const int64_t s = M.src1 + i, d = M.dst + i;
-      oq[d] = one.q[s];
-      om[d] = one.m[s];
-      od1[d] = one.d1[s];
-      od2[d] = one.d2[s];
-    }
-    for (int32_t i = threadIdx.x; i < M.n2; i += blockDim.x) {
-      const int64_t s = M.src2 + i, d = M.dst + M.n1 + i;
-      oq[d] = two.q[s] + M.shift;
-      om[d] = two.m[s];
-      od1[d] = two.d1[s];
-      od2[d] = two.d2[s];
-    }
-    if (threadIdx.x == 0 && ocmp) ocmp[p] = one.n_cmp[p] + (M.s2 >= 0 ? two.n_cmp[M.s2] : 0);
-  }
+__global__ __launch_bounds__(256) void stage_outputs_kernel(BatchView v, int32_t n_pairs,
+                                                            const int64_t* offset2,
+                                                            const int64_t* n_cmp2,
+                                                            int64_t* offset, int64_t* n_cmp,
+                                                            int32_t* found) {
+  const int32_t k = int32_t(blockIdx.x * blockDim.x + threadIdx.x);
+  if (k > n_pairs) return;
+  offset[k] = offset2[2 * int64_t(k)];
+  if (k == n_pairs) return;
+  if (n_cmp) n_cmp[k] = n_cmp2[2 * int64_t(k)] + n_cmp2[2 * int64_t(k) + 1];
+  found[k] = int32_t(v.counters[2 * int64_t(k)].accepted);
 }
 
 int32_t grid_for(int64_t n, int64_t per) {
@@ -73,12 +63,12 @@ hipError_t launch_make_views(const ImageDev* images, const int32_t* spec, int32_
   return hipGetLastError();
 }
 
-hipError_t launch_merge_stages(const StageMerge* merge, int32_t n_pairs, StageRows one,
-                               StageRows two, int32_t* out_q, int32_t* out_m, int32_t* out_d1,
-                               int32_t* out_d2, int64_t* out_cmp, hipStream_t st) {
+hipError_t launch_stage_outputs(const BatchView& v, int32_t n_pairs, const int64_t* offset2,
+                                const int64_t* n_cmp2, int64_t* offset, int64_t* n_cmp,
+                                int32_t* found, hipStream_t st) {
   if (n_pairs <= 0) return hipSuccess;
-  hipLaunchKernelGGL(merge_stages_kernel, dim3(grid_for(n_pairs, 1)), dim3(256), 0, st, merge,
-                     n_pairs, one, two, out_q, out_m, out_d1, out_d2, out_cmp);
+  hipLaunchKernelGGL(stage_outputs_kernel, dim3(n_pairs / 256 + 1), dim3(256), 0, st, v, n_pairs,
+                     offset2, n_cmp2, offset, n_cmp, found);
   return hipGetLastError();
 }
 

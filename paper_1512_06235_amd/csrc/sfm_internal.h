@@ -75,7 +75,7 @@ struct PairDesc {
   int32_t pad2;
   double band;              // d, pixels (may be +inf)
   int32_t ignore_band;      // exhaustive matching
-  int32_t pad;
+  int32_t q_shift;          // added to the query indices of emitted rows
   int64_t ex_off;           // exhaustive matching: first partial result (prefix of n_a * slices)
 };
 
@@ -319,20 +319,12 @@ hipError_t launch_grid_groups(const GridView& v, const GroupView& g, int32_t n_g
 // (image, first feature, count) per view, checked on the host.
 hipError_t launch_make_views(const ImageDev* images, const int32_t* spec, int32_t n_views,
                              ImageDev* views, hipStream_t st);
-// Rows of one pair's two stages, placed one after the other at dst.
-struct StageMerge {
-  int64_t src1, src2, dst;
-  int32_t n1, n2;
-  int32_t shift;   // added to a second-stage query index (the first stage's query count)
-  int32_t s2;      // the pair's index in the second stage, -1 if it had none
-};
-struct StageRows {
-  const int32_t *q, *m, *d1, *d2;
-  const int64_t* n_cmp;
-};
-hipError_t launch_merge_stages(const StageMerge* merge, int32_t n_pairs, StageRows one,
-                               StageRows two, int32_t* out_q, int32_t* out_m, int32_t* out_d1,
-                               int32_t* out_d2, int64_t* out_cmp, hipStream_t st);
+// A staged call's pairs 2 k and 2 k + 1 are the two stages of the caller's pair
+// k.  From their rows' offsets and counts: the caller's, and found[k], the
+// matches of the first stage.
+hipError_t launch_stage_outputs(const BatchView& v, int32_t n_pairs, const int64_t* offset2,
+                                const int64_t* n_cmp2, int64_t* offset, int64_t* n_cmp,
+                                int32_t* found, hipStream_t st);
 
 // Workspace admission for the serving loop: an upper bound on the bytes one
 // pair adds to a batched call's workspace, the bytes every call needs
@@ -374,19 +366,34 @@ hipError_t launch_emit(const BatchView& v, int32_t pair_begin, int32_t pair_coun
                        int64_t* offset, int32_t* out_q, int32_t* out_m, int32_t* out_d1,
                        int32_t* out_d2, int64_t* n_cmp, int64_t* n_bl, int32_t* all_m,
                        int32_t* all_d1, int32_t* all_d2, int32_t* all_c, hipStream_t st);
+// The pairs of one exhaustive launch: first, first + step, ... of the view's.
+// The second stage of a staged call is open for the pairs whose predecessor
+// accepted more than min_matches, and fewer than `enough` (0: any number); the
+// others get no matches and count nothing.
+struct ExStage {
+  int32_t first, step;
+  int32_t gated;
+  int32_t min_matches, enough;
+  __host__ __device__ bool open(unsigned long long found) const {
+    const long long c = (long long)found;
+    return c > min_matches && !(enough > 0 && c >= enough);
+  }
+};
+constexpr ExStage kExAll = {0, 1, 0, 0, 0};
+
 // Exhaustive matching (kernels_exhaustive.hip), without preparation: work
-// items of (pair, 256 queries, 1024 targets).  exhaustive_plan sets each
-// pair's ex_off and, when `items` is not NULL, writes the item table (one
-// int2 {pair, query block << 16 | slice} per item); n_part receives the
-// partial results (uint2) the call needs.  launch_exhaustive resets the
-// pairs' counters, matches every item and merges each query's slices into
-// v.res (the index in b: emission runs with v.cand_j NULL).
+// items of (pair, 256 queries, 1024 targets).  exhaustive_plan sets the
+// ex_off of the stage's pairs and, when `items` is not NULL, writes the item
+// table (one int2 each); it returns the numbers of items and of partial results
+// (uint2) the launch needs.  launch_exhaustive sets the pairs' counters,
+// matches every item and merges each query's slices into v.res (the index in b:
+// emit with v.cand_j NULL).
 constexpr int32_t kExhaustiveMaxQueries = 32767 * 256;   // query blocks fit 15 bits
 constexpr int32_t kExhaustiveMaxTargets = 65535 * 1024;  // slices fit 16 bits
-void exhaustive_plan(PairDesc* pd, int32_t n_pairs, int2* items, int64_t* n_items,
-                     int64_t* n_part);
-hipError_t launch_exhaustive(const BatchView& v, const int2* items, int64_t n_items, uint2* part,
-                             hipStream_t st);
+void exhaustive_plan(PairDesc* pd, int32_t n_pairs, const ExStage& stage, int2* items,
+                     int64_t* n_items, int64_t* n_part);
+hipError_t launch_exhaustive(const BatchView& v, const ExStage& stage, const int2* items,
+                             int64_t n_items, uint2* part, hipStream_t st);
 // Direct guided matching (kernels_direct.hip) of pairs [pair_begin, pair_begin
 // + pair_count): no preparation, results hold the index in b (emission runs
 // with v.cand_j NULL); the pairs' counters start at zero.  max_queries is
