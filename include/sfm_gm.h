@@ -386,7 +386,8 @@ int sfm_server_stop(sfm_ctx* ctx);
  * scheduling and preparation costs (Appendix A steps 1-2 leave them open):
  *   group_tiles       query tiles of 16 queries (in pencil order) that one
  *                     match workgroup of four waves streams one candidate
- *                     range for: 4 or 8 (default 8);
+ *                     range for: 4 or 8 (default 8; a call whose groups of 8
+ *                     would all run at once takes 4 where its workspace allows);
  *   features_per_bin  average target features per bin of b's pencil
  *                     binning, 1..1024 (default 8).
  * Results do not depend on them.  They apply to later calls on the context. */

@@ -112,6 +112,7 @@ struct Layout {
   size_t pairs, F, order, items, geom, counters, wg_start, cand_x, cand_y, cand_nc, cand_j, bins,
       qrec, res, twin, groups, gcost, pcost, part, total, staged;
   int32_t wgs = 0;
+  int32_t group_tiles = 0;
   int64_t sum_na = 0, sum_nc = 0, sum_bins = 0, sum_blocks = 0, sum_groups = 0;
   int32_t max_na = 0, max_nb = 0, max_sort_ints = 0;
 };
@@ -126,6 +127,7 @@ int32_t bins_for(int32_t nb, int32_t features_per_bin) {
 Layout plan(const PairDesc* pd, size_t P, int32_t device, int32_t group_tiles,
             int64_t n_items = 0, int64_t n_part = 0, bool exhaustive = false) {
   Layout L;
+  L.group_tiles = group_tiles;
   for (size_t k = 0; k < P; ++k) {
     const PairDesc& p = pd[k];
     L.sum_na += p.na;
@@ -243,6 +245,36 @@ int describe_pairs(sfm_ctx* ctx, const ImageTable& tab, const sfm_pair* pairs, i
   if (n_pairs < 0) return fail(ctx, SFM_EINVAL, "n_pairs < 0");
   pd.resize(size_t(n_pairs));
   return describe_pairs(ctx, tab, pairs, n_pairs, ignore_band, pd.data());
+}
+
+// The workspace of a guided call.  Where the groups of eight tiles of a launch
+// (the whole call, or with `per_pair` each pair) all run at once, the pairs are
+// cut into groups of four instead, if the larger group table fits in `limit`
+// bytes: twice the workgroups, and half the work of the longest.  (Groups of
+// eight against four: a pair of 16,000, 125 groups, 79 / 72 us; 6 pairs of
+// 2,000 to 20,000, 224: 82 / 71; 20 pairs, 875: 100 / 91; 100 pairs of 1,000 to
+// 2,000, 1,148: 75 / 78; 120 pairs, 6,874: 206 / 208.)
+Layout plan_guided(const sfm_ctx* ctx, PairDesc* pd, size_t P, bool per_pair, size_t limit) {
+  auto cut = [&](int32_t tiles) {
+    int64_t grp = 0;
+    for (size_t k = 0; k < P; ++k) {
+      pd[k].ngroups = (pd[k].nblocks + tiles - 1) / tiles;
+      pd[k].grp_off = grp;
+      grp += pd[k].ngroups;
+    }
+  };
+  if (ctx->group_tiles == 8) {
+    int64_t groups = 0;
+    for (size_t k = 0; k < P; ++k)
+      groups = per_pair ? std::max<int64_t>(groups, pd[k].ngroups) : groups + pd[k].ngroups;
+    if (groups <= kFewGroups) {
+      cut(4);
+      const Layout L = plan(pd, P, ctx->device, 4);
+      if (L.total <= limit) return L;
+      cut(8);
+    }
+  }
+  return plan(pd, P, ctx->device, ctx->group_tiles);
 }
 
 // A device workspace, its pinned staging buffer and their events: the
@@ -461,7 +493,7 @@ BatchView batch_view(const sfm_ctx* ctx, const ImageTable& tab, char* ws, const 
   v.ratio_den = opt.ratio_den;
   v.accept_single = opt.accept_single ? 1 : 0;
   v.keep_counts = opt.emit_all ? 1 : 0;
-  v.group_tiles = ctx->group_tiles;
+  v.group_tiles = L.group_tiles;
   v.max_na = L.max_na;
   v.max_nb = L.max_nb;
   v.max_sort_ints = L.max_sort_ints;
@@ -513,16 +545,16 @@ bool epipole_near_box(const double* F, const float* bb, double half) {
 // (kernels_direct.hip) or binned, by estimates in microseconds fitted to both
 // forms on 48 calls: 1 pair of 300 to 32,000 features (band 2, 4 and 8 px), 2 to
 // 200 pairs of 300 to 20,000, epipoles inside the image.  (Direct against
-// binned: a pair of 300 features 23 / 44 us, 2,000: 27 / 50, 8,000: 45 / 61,
-// 12,000: 58 / 68, 16,000: 78 / 75, 24,000: 134 / 90; 12,000 with an 8 px band
-// 77 / 75; 8 pairs of 2,000: 35 / 50, 37 of 500: 31 / 52, 30 of 3,000: 96 / 57;
-// epipole inside the image, 7,000: 44 / 428.)
+// binned: a pair of 300 features 23 / 42 us, 2,000: 27 / 46, 8,000: 45 / 55,
+// 12,000: 58 / 62, 16,000: 78 / 71, 24,000: 134 / 82; 12,000 with an 8 px band
+// 77 / 68; 8 pairs of 2,000: 35 / 46, 37 of 500: 31 / 48, 30 of 3,000: 96 / 56;
+// epipole inside the image, 7,000: 44 / 260.)
 bool direct_pays(const sfm_ctx* ctx, const PairDesc* pd, const double* F, int32_t n,
                  double margin) {
   // The binned form counts borderline slots within its windows, which are
   // kBandSlackPx wider than the band.
   if (margin > 0.5 * kBandSlackPx) return false;
-  double cost = 0.0, binned = 43.0 + 0.1 * n, side = 0.0;
+  double cost = 0.0, binned = 41.0 + 0.1 * n, side = 0.0;
   for (int32_t k = 0; k < n; ++k) {
     const PairDesc& P = pd[k];
     if (P.nb > kDirectMaxTargets) return false;
@@ -541,7 +573,7 @@ bool direct_pays(const sfm_ctx* ctx, const PairDesc* pd, const double* F, int32_
       binned += 3e-6 * double(P.na) * double(P.nb);
     if (21.0 + 7.5e-6 * cost > 400.0 + binned) return false;   // large batches end here soon
   }
-  return 21.0 + 7.5e-6 * cost < binned + 2e-3 * side;
+  return 21.0 + 7.5e-6 * cost < binned + 1.8e-3 * side;
 }
 
 // The sizes the exhaustive kernels take; pair k of the caller's is pd[step k].
@@ -586,7 +618,8 @@ int match_locked(sfm_ctx* ctx, const ImageTable& tab, const sfm_pair* pairs, int
     if (n_items > INT32_MAX) return fail(ctx, SFM_ECAPACITY, "too many work items in one call");
   }
   HIP_TRY(ctx, hipSetDevice(ctx->device));
-  const Layout L = plan(pd, ctx->device, ctx->group_tiles, n_items, n_part, exhaustive);
+  const Layout L = exhaustive ? plan(pd, ctx->device, ctx->group_tiles, n_items, n_part, true)
+                              : plan_guided(ctx, pd.data(), pd.size(), form == Form::kPlain, S.budget);
   if (!diagnostic && (rc = check_outputs(ctx, out, L, opt))) return rc;
   if (diagnostic && opt.emit_all) return fail(ctx, SFM_EINVAL, "emit_all has no outputs here");
 
@@ -659,7 +692,7 @@ int match_locked(sfm_ctx* ctx, const ImageTable& tab, const sfm_pair* pairs, int
         HIP_TRY(ctx, launch_direct(vp, p, 1, pp.na, direct_queries(pp.na), st));
       } else {
         const int32_t g0 = int32_t(pp.grp_off), gn = pp.ngroups;
-        const int32_t wgs = match_workgroups(ctx->device, ctx->group_tiles, gn);
+        const int32_t wgs = match_workgroups(ctx->device, L.group_tiles, gn);
         HIP_TRY(ctx, launch_prepare(v, p, 1, g0, gn, wgs, nullptr, pp.na, st));
         HIP_TRY(ctx, prof_mark(ctx, st));
         HIP_TRY(ctx, launch_match(v, gn > 0 ? wgs : 0, st));
@@ -793,7 +826,7 @@ int noalloc_locked(sfm_ctx* ctx, const sfm_pair* pairs, int32_t n_pairs, const d
   PairDesc* pd = reinterpret_cast<PairDesc*>(g_stage);
   if ((rc = describe_pairs(ctx, registered(ctx), pairs, n_pairs, false, pd))) return rc;
   if ((rc = check_F(ctx, F, n_pairs))) return rc;
-  const Layout L = plan(pd, size_t(n_pairs), ctx->device, ctx->group_tiles);
+  const Layout L = plan_guided(ctx, pd, size_t(n_pairs), false, SFM_NOALLOC_SCRATCH_BYTES);
   if ((rc = check_outputs(ctx, out, L, opt))) return rc;
   if (L.pairs != 0 || L.staged > kNoAllocStageBytes)
     return fail(ctx, SFM_EINVAL, "staging layout does not fit the host buffer");
@@ -1083,7 +1116,7 @@ int sfm_workspace_size(sfm_ctx* ctx, const sfm_pair* pairs, int32_t n_pairs, siz
   const int rc = describe_pairs(ctx, registered(ctx), pairs, n_pairs, false, pd);
   if (rc) return rc;
   HIP_TRY(ctx, hipSetDevice(ctx->device));
-  *bytes = plan(pd, ctx->device, ctx->group_tiles).total;
+  *bytes = plan(pd, ctx->device, ctx->group_tiles).total;   // (more is taken only where it fits)
   return SFM_OK;
 }
 

@@ -18,6 +18,7 @@ constexpr int kCounters = 4;            // per share
 constexpr int kTicketAt = 16;
 constexpr int kTicketStride = 32;
 constexpr int kScheduleInts = kTicketAt + kTicketStride * (kXcds * kCounters - 1) + 1;
+constexpr int32_t kFewGroups = 1024;    // groups that run at once: four workgroups per CU
 constexpr int kMaxGroupTiles = 8;       // query tiles sharing one candidate stream, at most
 constexpr int kDefaultGroupTiles = 8;   // the default (4 or 8: one or two tiles per wave)
 constexpr int kDefaultFeaturesPerBin = 8;

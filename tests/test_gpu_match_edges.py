@@ -40,8 +40,11 @@ def test_sizes_around_fills(sfm, oracle_lib, tiles, emit_all):
     nq = len(QUERIES)
     pairs = [(q, nq + t, d) for q in range(nq) for t in range(len(TARGETS))
              for d in ((0.5, 12.0, 90.0, np.inf) if t % 2 else (3.0, 40.0, 250.0))]
+    if tiles == 8:
+        pairs = 3 * pairs   # fewer groups would be cut into fours
     m = sfm.Matcher().register(images)
     sfm.sfm_set_tuning(m.ctx, tiles, 8)
+    assert tiles == 4 or sum(-(-images[a][0].shape[0] // 128) for a, _, _ in pairs) > 1024
     want = oracle_lib.match(images, pairs, [F] * len(pairs))
     out = m.match(pairs, [F] * len(pairs), emit_all=emit_all, recheck_margin_px=6e-3)
     compare_all(out, want, len(pairs))
