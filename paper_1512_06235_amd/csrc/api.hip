@@ -381,7 +381,7 @@ int replay_batched(sfm_ctx* ctx, const GraphKey& key, int32_t* am, int32_t* ad1,
                    : launch_prepare(v, 0, key.n_pairs, 0, key.sum_groups, key.wgs, key.order,
                                     key.max_na, cs);
     const hipError_t e2 =
-        key.direct ? hipSuccess : launch_match(v, key.sum_groups > 0 ? key.wgs : 0, cs);
+        key.direct ? hipSuccess : launch_match(v, 0, key.sum_groups, key.wgs, cs);
     const hipError_t e3 = launch_emit(v, 0, key.n_pairs, out.offset, out.query, out.match, out.d1,
                                       out.d2, out.n_comparisons, out.n_borderline, am, ad1, ad2, ac, cs);
     hipGraph_t g = nullptr;
@@ -695,7 +695,7 @@ int match_locked(sfm_ctx* ctx, const ImageTable& tab, const sfm_pair* pairs, int
         const int32_t wgs = match_workgroups(ctx->device, L.group_tiles, gn);
         HIP_TRY(ctx, launch_prepare(v, p, 1, g0, gn, wgs, nullptr, pp.na, st));
         HIP_TRY(ctx, prof_mark(ctx, st));
-        HIP_TRY(ctx, launch_match(v, gn > 0 ? wgs : 0, st));
+        HIP_TRY(ctx, launch_match(v, g0, gn, wgs, st));
       }
       HIP_TRY(ctx, prof_mark(ctx, st));
       HIP_TRY(ctx, launch_emit(vp, p, 1, out->offset, out->query, out->match, out->d1, out->d2,
@@ -734,7 +734,7 @@ int match_locked(sfm_ctx* ctx, const ImageTable& tab, const sfm_pair* pairs, int
                                   reinterpret_cast<const int32_t*>((*S.ws) + L.order), L.max_na,
                                   st));
       HIP_TRY(ctx, prof_mark(ctx, st));
-      HIP_TRY(ctx, launch_match(v, L.sum_groups > 0 ? L.wgs : 0, st));
+      HIP_TRY(ctx, launch_match(v, 0, int32_t(L.sum_groups), L.wgs, st));
     }
     HIP_TRY(ctx, prof_mark(ctx, st));
     HIP_TRY(ctx, launch_emit(v, 0, n_pairs, out->offset, out->query, out->match, out->d1,
@@ -866,7 +866,7 @@ int noalloc_locked(sfm_ctx* ctx, const sfm_pair* pairs, int32_t n_pairs, const d
   } else {
     HIP_TRY(ctx, launch_prepare(v, 0, n_pairs, 0, int32_t(L.sum_groups), L.wgs,
                                 reinterpret_cast<const int32_t*>(ws + L.order), L.max_na, st));
-    HIP_TRY(ctx, launch_match(v, L.sum_groups > 0 ? L.wgs : 0, st));
+    HIP_TRY(ctx, launch_match(v, 0, int32_t(L.sum_groups), L.wgs, st));
   }
   const bool ea = opt.emit_all != 0;
   HIP_TRY(ctx, launch_emit(v, 0, n_pairs, out->offset, out->query, out->match, out->d1, out->d2,

@@ -922,7 +922,7 @@ __device__ __forceinline__ void match_group(const BatchView& v, const TileGroup&
 #endif
 template <bool kKeepCounts, int TPW>
 __global__ __launch_bounds__(64 * kWaves) __attribute__((amdgpu_waves_per_eu(SFM_MATCH_WAVES_PER_EU, 8)))
-void match_kernel(BatchView v) {
+void match_kernel(BatchView v, int32_t g0, int32_t n_groups) {
   __shared__ __attribute__((aligned(16))) MatchLds lds;
   // The wave index is uniform: readfirstlane lets the compiler keep
   // everything derived from it (tile ranges, queue counts) in SGPRs.
@@ -935,9 +935,17 @@ void match_kernel(BatchView v) {
   Deal deal;
   deal.shares = shares;
   deal.own = x * kCounters + i % kCounters;
-  deal.end = ((c_i32*)v.wg_start)[x + 1];
-  int32_t g = ((c_i32*)v.wg_start)[x] + i;
-  deal.first = g - i + 2 * W + i % kCounters;
+  int32_t g;
+  if (n_groups <= int32_t(gridDim.x)) {
+    // A workgroup per group: no schedule was made.
+    g = g0 + x * (n_groups / shares) + min(x, n_groups % shares) + i;
+    deal.end = min(g, g0 + n_groups - 1) + 1;
+    deal.first = deal.end;
+  } else {
+    deal.end = ((c_i32*)v.wg_start)[x + 1];
+    g = ((c_i32*)v.wg_start)[x] + i;
+    deal.first = g - i + 2 * W + i % kCounters;
+  }
   if (g >= deal.end) return;   // uniform
   if (threadIdx.x < 16) lds.stats[threadIdx.x >> 3][threadIdx.x & 7] = 0;
   if (threadIdx.x == 0) lds.taken = g + W < deal.end ? g + W : -1;
@@ -1029,19 +1037,23 @@ int32_t match_workgroups(int32_t device, int32_t group_tiles, int64_t groups) {
 }
 
 template <int TPW>
-static void launch_match_t(const BatchView& v, int32_t wgs, hipStream_t st) {
+static void launch_match_t(const BatchView& v, int32_t g0, int32_t n_groups, int32_t wgs,
+                           hipStream_t st) {
   if (v.keep_counts)
-    hipLaunchKernelGGL((match_kernel<true, TPW>), dim3(wgs), dim3(64 * kWaves), 0, st, v);
+    hipLaunchKernelGGL((match_kernel<true, TPW>), dim3(wgs), dim3(64 * kWaves), 0, st, v,
+                       g0, n_groups);
   else
-    hipLaunchKernelGGL((match_kernel<false, TPW>), dim3(wgs), dim3(64 * kWaves), 0, st, v);
+    hipLaunchKernelGGL((match_kernel<false, TPW>), dim3(wgs), dim3(64 * kWaves), 0, st, v,
+                       g0, n_groups);
 }
 
-hipError_t launch_match(const BatchView& v, int32_t wgs, hipStream_t st) {
-  if (wgs <= 0) return hipSuccess;
+hipError_t launch_match(const BatchView& v, int32_t g0, int32_t n_groups, int32_t wgs,
+                        hipStream_t st) {
+  if (n_groups <= 0) return hipSuccess;
   if (v.group_tiles == kWaves)
-    launch_match_t<1>(v, wgs, st);
+    launch_match_t<1>(v, g0, n_groups, wgs, st);
   else
-    launch_match_t<2>(v, wgs, st);
+    launch_match_t<2>(v, g0, n_groups, wgs, st);
   return hipGetLastError();
 }
 

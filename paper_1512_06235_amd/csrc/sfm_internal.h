@@ -361,8 +361,10 @@ hipError_t launch_prepare(const BatchView& v, int32_t pair_begin, int32_t pair_c
 // Workgroups the match kernel uses for `groups` tile groups (one resident wave
 // of workgroups at most).
 int32_t match_workgroups(int32_t device, int32_t group_tiles, int64_t groups);
-// Matches the groups of the last preparation with `wgs` workgroups.
-hipError_t launch_match(const BatchView& v, int32_t wgs, hipStream_t st);
+// Matches groups [g0, g0 + n_groups), those of the last preparation, with `wgs`
+// workgroups.
+hipError_t launch_match(const BatchView& v, int32_t g0, int32_t n_groups, int32_t wgs,
+                        hipStream_t st);
 hipError_t launch_emit(const BatchView& v, int32_t pair_begin, int32_t pair_count,
                        int64_t* offset, int32_t* out_q, int32_t* out_m, int32_t* out_d1,
                        int32_t* out_d2, int64_t* n_cmp, int64_t* n_bl, int32_t* all_m,
