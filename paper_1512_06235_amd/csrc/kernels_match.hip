@@ -1050,6 +1050,7 @@ static void launch_match_t(const BatchView& v, int32_t g0, int32_t n_groups, int
 hipError_t launch_match(const BatchView& v, int32_t g0, int32_t n_groups, int32_t wgs,
                         hipStream_t st) {
   if (n_groups <= 0) return hipSuccess;
+  if (n_groups <= kUnscheduledGroups) wgs = n_groups;
   if (v.group_tiles == kWaves)
     launch_match_t<1>(v, g0, n_groups, wgs, st);
   else

@@ -954,7 +954,7 @@ hipError_t launch_prepare(const BatchView& v, int32_t pb, int32_t pc, int32_t gr
       hipLaunchKernelGGL(tile_ranges_kernel<8>, grid, block, 0, st, v, pb);
   }
   // (With a workgroup per group the match kernel needs no schedule.)
-  if (grp_count > wgs)
+  if (grp_count > std::max(wgs, kUnscheduledGroups))
     hipLaunchKernelGGL(schedule_kernel, dim3((pc + 3) / 4), dim3(256), 0, st, v, pb, pc,
                        grp_begin, grp_count, std::min(kXcds, wgs));
   return hipGetLastError();

@@ -11,7 +11,7 @@ import pytest
 
 import scenes
 from tests.fixtures import random_pair
-from tests.gpu_util import compare_all
+from tests.gpu_util import compare_all, compare_rows
 
 pytestmark = pytest.mark.gpu
 
@@ -66,4 +66,24 @@ def test_sides_around_the_sort_in_lds(sfm, oracle_lib, n_pairs, largest):
     m = sfm.Matcher().register(images)
     out = m.match(pairs, [F] * n_pairs, emit_all=True, recheck_margin_px=6e-3)
     compare_all(out, oracle_lib.match(images, pairs, [F] * n_pairs), n_pairs)
+    m.close()
+
+
+def test_scheduled_groups(sfm, oracle_lib):
+    """More groups than take a workgroup each: resident workgroups draw them from
+    the shares' counters."""
+    images = []
+    for k, n in enumerate([300, 65, 17, 1, 16, 129, 257, 300]):
+        xy, desc, _, _, _ = random_pair(n, 0, seed=400 + k)
+        images.append((xy, desc // 8))
+    F = scenes.make_two_view_2k().F
+    pairs = [(q, t, d) for q in range(4) for t in range(4, 8) for d in (0.5, 20.0, np.inf)]
+    reps = 4400 // sum(-(-images[a][0].shape[0] // 128) for a, _, _ in pairs) + 1
+    want = oracle_lib.match(images, pairs, [F] * len(pairs))
+    m = sfm.Matcher().register(images)
+    out = m.match(pairs * reps, [F] * (len(pairs) * reps), recheck_margin_px=6e-3)
+    for p in range(len(pairs) * reps):
+        compare_rows(*out.pair(p), want.pair(p % len(pairs)), what=f"pair {p}: ")
+    got = out.n_comparisons[:len(pairs) * reps].cpu().numpy().reshape(reps, -1)
+    assert np.array_equal(got, np.tile(want.n_comparisons[:len(pairs)], (reps, 1)))
     m.close()
