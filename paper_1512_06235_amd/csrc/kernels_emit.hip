@@ -5,13 +5,12 @@
 // ascending query index with a ballot + mbcnt prefix inside each wave and a
 // scan over waves.
 #include <algorithm>
+#include <type_traits>
 
 #include "sfm_internal.h"
 
 namespace sfm {
 namespace {
-
-constexpr int kEmitThreads = 1024;
 
 // offset[pb + k + 1] = offset[pb] + sum of accepted over pairs pb..pb+k.
 __global__ __launch_bounds__(1024) void scan_pairs_kernel(BatchView v, int32_t pb, int32_t pc,
@@ -45,28 +44,28 @@ __global__ __launch_bounds__(1024) void scan_pairs_kernel(BatchView v, int32_t p
   }
 }
 
-// One workgroup per chunk of kEmitChunk consecutive queries of a pair (the
-// last chunk of a pair takes whatever remains, in rounds of kEmitChunk).  A
-// round covers kEmitPer slices of kEmitThreads consecutive queries, whose
+// One workgroup of NT threads per chunk of kEmitPer * NT consecutive queries of
+// a pair (the last chunk of a pair takes whatever remains, in rounds of that
+// many).  A round covers kEmitPer slices of NT consecutive queries, whose
 // results are read together with coalesced loads (thread t reads query t of
 // every slice).  Ranks come from a ballot + mbcnt inside each wave and one
 // scan over the (slice, wave) counts of the round; the accepted queries of
 // the pair's earlier chunks are counted first from their flags, so the
 // chunks of a large pair are emitted side by side.  With `fused` (batches of
-// at most kEmitThreads pairs) the workgroup also sums the accepted queries of
+// at most kEmitFused pairs) the workgroup also sums the accepted queries of
 // the batch's earlier pairs for its first row, and the pair's first chunk
 // writes its offset and counts, so no separate scan over pairs runs first.
 constexpr int kEmitPer = 8;
-constexpr int kEmitWaves = kEmitThreads / 64;
-constexpr int32_t kEmitChunk = kEmitThreads * kEmitPer;
+constexpr int32_t kEmitFused = 1024;
 
-__global__ __launch_bounds__(kEmitThreads) void emit_kernel(BatchView v, int32_t pb, int32_t fused,
-                                                            int64_t* offset, int64_t* n_cmp,
-                                                            int64_t* n_bl, int32_t* oq,
-                                                            int32_t* om, int32_t* od1,
-                                                            int32_t* od2, int32_t* am,
-                                                            int32_t* ad1, int32_t* ad2,
-                                                            int32_t* ac) {
+template <int NT>
+__global__ __launch_bounds__(NT) void emit_kernel(BatchView v, int32_t pb, int32_t fused,
+                                                  int64_t* offset, int64_t* n_cmp, int64_t* n_bl,
+                                                  int32_t* oq, int32_t* om, int32_t* od1,
+                                                  int32_t* od2, int32_t* am, int32_t* ad1,
+                                                  int32_t* ad2, int32_t* ac) {
+  constexpr int kEmitWaves = NT / 64;
+  constexpr int32_t kEmitChunk = NT * kEmitPer;
   __shared__ int32_t cnt[kEmitPer * kEmitWaves];   // accepted per (slice, wave), then prefix
   __shared__ int32_t run;
   __shared__ long long wtot[kEmitWaves];
@@ -75,8 +74,9 @@ __global__ __launch_bounds__(kEmitThreads) void emit_kernel(BatchView v, int32_t
   const int t = threadIdx.x, lane = t & 63, wv = t >> 6;
   int64_t out0;
   if (fused) {
-    // Rows of the batch's pairs before this one (p - pb < kEmitThreads).
-    long long a = t < p - pb ? (long long)v.counters[pb + t].accepted : 0;
+    // Rows of the batch's pairs before this one.
+    long long a = 0;
+    for (int32_t k = t; k < p - pb; k += NT) a += (long long)v.counters[pb + k].accepted;
     for (int o = 32; o > 0; o >>= 1) a += __shfl_xor(a, o, 64);
     if (lane == 0) wtot[wv] = a;
     __syncthreads();
@@ -99,7 +99,7 @@ __global__ __launch_bounds__(kEmitThreads) void emit_kernel(BatchView v, int32_t
   // Accepted queries of the chunks before this one.
   int32_t before = 0;
 #pragma unroll 8
-  for (int32_t i = t; i < first; i += kEmitThreads) before += res[i].flags & 1;
+  for (int32_t i = t; i < first; i += NT) before += res[i].flags & 1;
   for (int o = 32; o > 0; o >>= 1) before += __shfl_xor(before, o, 64);
   if (lane == 0) cnt[wv] = before;
   __syncthreads();
@@ -114,7 +114,7 @@ __global__ __launch_bounds__(kEmitThreads) void emit_kernel(BatchView v, int32_t
     QueryResult r[kEmitPer];
 #pragma unroll
     for (int k = 0; k < kEmitPer; ++k) {
-      const int32_t i = base + k * kEmitThreads + t;
+      const int32_t i = base + k * NT + t;
       if (i < last) {
         r[k] = res[i];
       } else {
@@ -130,7 +130,7 @@ __global__ __launch_bounds__(kEmitThreads) void emit_kernel(BatchView v, int32_t
     int32_t pre[kEmitPer];
 #pragma unroll
     for (int k = 0; k < kEmitPer; ++k) {
-      const int32_t i = base + k * kEmitThreads + t;
+      const int32_t i = base + k * NT + t;
       if (am && i < last) {
         am[P.q_off + i] = r[k].match;
         ad1[P.q_off + i] = r[k].d1;
@@ -146,16 +146,19 @@ __global__ __launch_bounds__(kEmitThreads) void emit_kernel(BatchView v, int32_t
     // Exclusive scan of the kEmitPer * kEmitWaves counts in (slice, wave)
     // order by the first wave, two entries per lane.
     if (wv == 0) {
-      static_assert(kEmitPer * kEmitWaves == 128, "two counts per lane");
-      const int32_t c0 = cnt[2 * lane], c1 = cnt[2 * lane + 1];
+      static_assert(kEmitPer * kEmitWaves <= 128, "two counts per lane");
+      const bool has = 2 * lane < kEmitPer * kEmitWaves;
+      const int32_t c0 = has ? cnt[2 * lane] : 0, c1 = has ? cnt[2 * lane + 1] : 0;
       int32_t x = c0 + c1;
       for (int o = 1; o < 64; o <<= 1) {
         const int32_t y = __shfl_up(x, o, 64);
         if (lane >= o) x += y;
       }
       const int32_t ex = x - c0 - c1;
-      cnt[2 * lane] = ex;
-      cnt[2 * lane + 1] = ex + c0;
+      if (has) {
+        cnt[2 * lane] = ex;
+        cnt[2 * lane + 1] = ex + c0;
+      }
       if (lane == 63) run = rbase + x;   // every thread has read rbase already
     }
     __syncthreads();
@@ -163,7 +166,7 @@ __global__ __launch_bounds__(kEmitThreads) void emit_kernel(BatchView v, int32_t
     for (int k = 0; k < kEmitPer; ++k) {
       if (r[k].flags & 1) {
         const int64_t row = out0 + rbase + cnt[k * kEmitWaves + wv] + pre[k];
-        const int32_t i = base + k * kEmitThreads + t;
+        const int32_t i = base + k * NT + t;
         oq[row] = i + P.q_shift;
         om[row] = r[k].match;
         od1[row] = r[k].d1;
@@ -180,13 +183,25 @@ hipError_t launch_emit(const BatchView& v, int32_t pb, int32_t pc, int64_t* offs
                        int32_t* om, int32_t* od1, int32_t* od2, int64_t* n_cmp, int64_t* n_bl,
                        int32_t* am, int32_t* ad1, int32_t* ad2, int32_t* ac, hipStream_t st) {
   if (pc <= 0) return hipSuccess;
-  const int32_t fused = pc <= kEmitThreads ? 1 : 0;
+  const int32_t fused = pc <= kEmitFused ? 1 : 0;
   if (!fused)
     hipLaunchKernelGGL(scan_pairs_kernel, dim3(1), dim3(1024), 0, st, v, pb, pc, offset, n_cmp,
                        n_bl);
-  const uint32_t chunks = uint32_t(std::max(1, (v.max_na + kEmitChunk - 1) / kEmitChunk));
-  hipLaunchKernelGGL(emit_kernel, dim3(pc, chunks), dim3(kEmitThreads), 0, st, v, pb, fused,
-                     offset, n_cmp, n_bl, oq, om, od1, od2, am, ad1, ad2, ac);
+  // 1,024 threads per chunk, unless there are more pairs than such workgroups run
+  // at once (two per CU) and 256 threads cover each pair in one round: what takes
+  // the time is the chain of loads and barriers, so more pairs side by side are
+  // better (3,540 half pairs of up to 2,000 queries: 44 us with 1,024 threads, 13
+  // with 256).
+  auto launch = [&](auto nt) {
+    constexpr int NT = decltype(nt)::value;
+    const uint32_t chunks = uint32_t(std::max(1, (v.max_na + NT * kEmitPer - 1) / (NT * kEmitPer)));
+    hipLaunchKernelGGL(emit_kernel<NT>, dim3(pc, chunks), dim3(NT), 0, st, v, pb, fused, offset,
+                       n_cmp, n_bl, oq, om, od1, od2, am, ad1, ad2, ac);
+  };
+  if (pc > 512 && v.max_na <= 256 * kEmitPer)
+    launch(std::integral_constant<int, 256>());
+  else
+    launch(std::integral_constant<int, 1024>());
   return hipGetLastError();
 }
 

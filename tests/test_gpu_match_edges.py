@@ -69,16 +69,19 @@ def test_sides_around_the_sort_in_lds(sfm, oracle_lib, n_pairs, largest):
     m.close()
 
 
-def test_scheduled_groups(sfm, oracle_lib):
-    """More groups than take a workgroup each: resident workgroups draw them from
-    the shares' counters."""
+@pytest.mark.parametrize("reps", [15, 62])
+def test_many_small_pairs(sfm, oracle_lib, reps):
+    """15: 720 pairs in one fused emission of narrow workgroups.  62: 2,976, whose
+    4,464 groups are more than take a workgroup each, so resident ones draw them
+    from the shares' counters."""
     images = []
     for k, n in enumerate([300, 65, 17, 1, 16, 129, 257, 300]):
         xy, desc, _, _, _ = random_pair(n, 0, seed=400 + k)
         images.append((xy, desc // 8))
     F = scenes.make_two_view_2k().F
     pairs = [(q, t, d) for q in range(4) for t in range(4, 8) for d in (0.5, 20.0, np.inf)]
-    reps = 4400 // sum(-(-images[a][0].shape[0] // 128) for a, _, _ in pairs) + 1
+    groups = reps * sum(-(-images[a][0].shape[0] // 128) for a, _, _ in pairs)
+    assert (groups > 4096) == (reps == 62)
     want = oracle_lib.match(images, pairs, [F] * len(pairs))
     m = sfm.Matcher().register(images)
     out = m.match(pairs * reps, [F] * (len(pairs) * reps), recheck_margin_px=6e-3)
