@@ -9,21 +9,23 @@
 //   - The buffer is filled by LDS DMA (global_load_lds): each wave fetches a
 //     quarter of its 16-position blocks (two 16-byte loads per lane for a
 //     block's 16 descriptor rows, eight lanes per 128-byte row, XOR-swizzled)
-//     and, one load each, its blocks' coordinates and key words.  The rows' indices in b arrive one
-//     group earlier in an index buffer of their own, so no loaded value passes
-//     through a register on its way to LDS.
+//     and, one load each, its blocks' coordinates and key words.  The rows'
+//     indices in b arrive one group earlier in an index buffer of their own, so
+//     no loaded value passes through a register on its way to LDS.
 //   - Per group: one wait and one barrier before the buffer is read, one
 //     barrier before it is refilled.  The next group's row indices and query
-//     records load while the current group computes.  The workgroups on one
-//     XCD take the groups of one contiguous share in turn, so at any time they
-//     work on one or two pairs whose rows stay in that XCD's L2.
+//     records load while the current group computes.  Where the groups do not
+//     take a workgroup each, the workgroups on one XCD draw the groups of one
+//     contiguous share in turn, so at any time they work on one or two pairs
+//     whose rows stay in that XCD's L2.
 //   - Wave w owns tiles w and 2 * 4 - 1 - w (when a group has eight), which
 //     balances the waves of a group whose range lengths drift along it.
 //   - Each tile walks its candidate range in steps of 16 positions.  A step's
 //     rows are the A operand of v_mfma_i32_16x16x64_i8 and the tile's query
 //     rows the resident B operand: two MFMAs give q.c for 16 candidates x 16
-//     queries, exact in int32 (bytes 0..127 fit int8, 128 * 127^2 < 2^31).  The next step's operands are read from LDS before
-//     the current step's fold.
+//     queries, exact in int32 (bytes 0..127 fit int8, 128 * 127^2 < 2^31).
+//     The next step's operands are read from LDS before the current step's
+//     fold.
 //   - Each lane then holds one query and 4 candidates.  It runs the band test
 //     of eqs. (2)-(3) in FP32 on centred coordinates, forms in-band keys
 //         key = ((||c||^2 - 2 q.c + 2^21) << 10) | (position mod 1024)
@@ -31,7 +33,9 @@
 //     35 vector instructions and two MFMAs per step.  (Matrix and vector
 //     instructions do not overlap here, so the vector ones are the loop's cost;
 //     41 of them, with negated queries, one candidate folded at a time and
-//     masked buffer offsets: 502 us for 500 pairs' 2.2 M steps, 475 now.)
+//     masked buffer offsets: 502 us for 500 pairs' 2.2 M steps, 475 with 35,
+//     and 385 now that the counters and the deal of groups below do not hold
+//     the kernel up; 62% of its cycles issue vector instructions.)
 //   - Slots whose FP32 distance lies within the margin of d are queued in LDS
 //     with their exact key and index in b, and decided in FP64 when the
 //     group's tiles are done.
@@ -56,17 +60,13 @@ typedef const __attribute__((address_space(1))) int32_t g_i32;
 typedef __attribute__((address_space(3))) void lds_void;
 
 constexpr int kWaves = kMatchWaves;           // waves per workgroup
-#ifndef SFM_MATCH_BUF
-#define SFM_MATCH_BUF 256
-#endif
-constexpr int kBuf = SFM_MATCH_BUF;           // candidate positions one buffer fill holds (power of two)
+constexpr int kBuf = 256;                     // candidate positions one buffer fill holds
 constexpr int kBlock = 16;                    // positions per DMA block (one step)
 constexpr int kBlocks = kBuf / kBlock;        // blocks of a buffer fill
 constexpr int kBlocksPerWave = kBlocks / kWaves;   // most blocks a wave fetches of a fill
 constexpr int kBorderCap = 32;                // queued FP64 decisions per wave and group
 static_assert(kBlocksPerWave * kWaves == kBlocks, "blocks are dealt evenly to the waves");
 static_assert(kBlocksPerWave * kBlock <= 64, "one 64-lane load fetches a wave's row indices");
-static_assert((kBuf & (kBuf - 1)) == 0, "buffer offsets wrap with a mask");
 static_assert(kQueryTile == kBlock, "one MFMA column block of queries per tile");
 static_assert(kBuf <= kChunk, "a tile's steps in one fill fit one key chunk");
 constexpr uint32_t kKeyDistInf = kKeyInf >> kPosBits;
@@ -914,14 +914,11 @@ __device__ __forceinline__ void match_group(const BatchView& v, const TileGroup&
   }
 }
 
-// One resident wave of workgroups.  Preparation splits the groups into
-// kXcds contiguous shares of about equal estimated cost, one per XCD (each
-// XCD has its own L2).
-#ifndef SFM_MATCH_WAVES_PER_EU
-#define SFM_MATCH_WAVES_PER_EU 4
-#endif
+// A workgroup for each of the n_groups groups from g0 on, or one resident wave
+// of workgroups: then preparation has split the groups into kXcds contiguous
+// shares of about equal estimated cost, one per XCD (each XCD has its own L2).
 template <bool kKeepCounts, int TPW>
-__global__ __launch_bounds__(64 * kWaves) __attribute__((amdgpu_waves_per_eu(SFM_MATCH_WAVES_PER_EU, 8)))
+__global__ __launch_bounds__(64 * kWaves) __attribute__((amdgpu_waves_per_eu(4, 8)))
 void match_kernel(BatchView v, int32_t g0, int32_t n_groups) {
   __shared__ __attribute__((aligned(16))) MatchLds lds;
   // The wave index is uniform: readfirstlane lets the compiler keep

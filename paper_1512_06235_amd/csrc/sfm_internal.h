@@ -357,10 +357,11 @@ int serve_match(sfm_ctx* ctx, ServeSpace* sp, const sfm_pair* pairs, int32_t n_p
 hipError_t launch_register(ImageDev* imgs_dev, int32_t n_images, int32_t* bad_flag,
                            hipStream_t st);
 // Preparation of pairs [pair_begin, pair_begin + pair_count), whose tile groups
-// are [grp_begin, grp_begin + grp_count), for `wgs` match workgroups (the
-// groups are split into min(kXcds, wgs) shares of about equal cost, one per
-// XCD).  `order` (device, may be NULL) lists the pairs in the order binning
-// takes them; `max_queries` is the largest n_a among the pairs.
+// are [grp_begin, grp_begin + grp_count), for `wgs` match workgroups (more
+// groups than kUnscheduledGroups are split into min(kXcds, wgs) shares of about
+// equal cost, one per XCD).  `order` (device, may be NULL) lists the pairs in
+// the order binning takes them; `max_queries` is the largest n_a among the
+// pairs.
 hipError_t launch_prepare(const BatchView& v, int32_t pair_begin, int32_t pair_count,
                           int32_t grp_begin, int32_t grp_count, int32_t wgs,
                           const int32_t* order, int32_t max_queries, hipStream_t st);
