@@ -34,6 +34,7 @@
 // tiles a wave halve the LDS reads but leave two waves a SIMD: 34 and 317 us.
 #include <algorithm>
 
+#include "line.h"
 #include "sfm_internal.h"
 
 namespace sfm {
@@ -356,22 +357,11 @@ void exhaustive_kernel(BatchView v, ExStage stage, const int2* items, int32_t n_
 // at the smallest distance and complete the second smallest.  Queries that
 // fail the ratio test against the other groups alone skip that, unless every
 // query's result is asked for: the second distance could only get smaller.
+// (The four read each of the four rows together: a lane that reads a row of its
+// own asks for every line eight times, 45 us for a staged launch's 1.4 M
+// queries, 28.5 now.  The rest is its chain of reads.)
 constexpr int kMergeThreads = 256;
 constexpr int kMergeBatch = 8;
-
-// Squared L2 of query row i of A and target j of B, four dot products a word.
-__device__ __forceinline__ int32_t row_dot(const uint8_t* p, const uint8_t* q) {
-  uint32_t dot = 0;
-#pragma unroll
-  for (int w = 0; w < kDescBytes / 16; ++w) {
-    const nv4u u = ((g_nv4u*)p)[w], x = ((g_nv4u*)q)[w];
-    dot = __builtin_amdgcn_udot4(u.x, x.x, dot, false);
-    dot = __builtin_amdgcn_udot4(u.y, x.y, dot, false);
-    dot = __builtin_amdgcn_udot4(u.z, x.z, dot, false);
-    dot = __builtin_amdgcn_udot4(u.w, x.w, dot, false);
-  }
-  return int32_t(dot);
-}
 
 __global__ __launch_bounds__(kMergeThreads) void exhaustive_merge_kernel(BatchView v,
                                                                          ExStage stage,
@@ -429,10 +419,13 @@ __global__ __launch_bounds__(kMergeThreads) void exhaustive_merge_kernel(BatchVi
     const int from = max(src, 0);
     const int32_t jj = __shfl(j1, from, 64) + (lane & 3);
     const int32_t qn = __shfl(nq, from, 64);
-    int32_t D = kDistInf;
-    if (src >= 0 && jj < P.nb)
-      D = qn + ((g_i32*)B.norm2)[jj] -
-          2 * row_dot(A.desc + int64_t(i0 + src) * kDescBytes, B.desc + int64_t(jj) * kDescBytes);
+    // (Every lane takes part: clamped rows where it has none.)
+    const int32_t jc = min(max(jj, 0), P.nb - 1);
+    const QuadRows rows = quad_rows(B.desc, jc, lane & 3);
+    const RowPart own = row_part(A.desc, i0 + from, lane & 3);
+    const int32_t norm = ((g_i32*)B.norm2)[jc];
+    const int32_t dot = quad_dots(own, rows, lane & 3);
+    const int32_t D = src >= 0 && jj < P.nb ? qn + norm - 2 * dot : kDistInf;
     // The two smallest of the four and the lowest index of the smallest.
     int32_t w1 = D, w2 = kDistInf, wj = jj;
 #pragma unroll
