@@ -65,10 +65,10 @@ __global__ __launch_bounds__(64 * kDirectWaves) __attribute__((amdgpu_waves_per_
   __shared__ __attribute__((aligned(16))) DirectLds lds[kDirectWaves];
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
   const int quad = lane & 3, sub = lane & (kLanes - 1), grp = lane / kLanes;
-  const int32_t p = pb + int32_t(blockIdx.y);
+  const int32_t p = pb + int32_t(blockIdx.x);
   const PairDesc P = read_uniform(v.pairs, p);
-  if (int32_t(blockIdx.x) * kDirectWaves * per_wave >= P.na) return;   // uniform
-  const int32_t q0 = (int32_t(blockIdx.x) * kDirectWaves + wave) * per_wave;
+  if (int32_t(blockIdx.y) * kDirectWaves * per_wave >= P.na) return;   // uniform
+  const int32_t q0 = (int32_t(blockIdx.y) * kDirectWaves + wave) * per_wave;
   const ImageDev A = read_uniform(v.images, P.a), B = read_uniform(v.images, P.b);
   DirectLds& L = lds[wave];
   const double* F = v.F + 9 * int64_t(p);
@@ -316,7 +316,8 @@ hipError_t launch_direct(const BatchView& v, int32_t pb, int32_t pc, int32_t max
                          int32_t per_wave, hipStream_t st) {
   if (pc <= 0 || max_queries <= 0) return hipSuccess;
   const int32_t per_block = kDirectWaves * per_wave;
-  hipLaunchKernelGGL(direct_kernel, dim3((max_queries + per_block - 1) / per_block, pc),
+  // Pairs along x, which takes any number of them (y ends at 65,535).
+  hipLaunchKernelGGL(direct_kernel, dim3(pc, (max_queries + per_block - 1) / per_block),
                      dim3(64 * kDirectWaves), 0, st, v, pb, per_wave);
   return hipGetLastError();
 }

@@ -1,0 +1,59 @@
+"""Which form a guided call takes, the direct or the binned one, shows in the
+slots it evaluates: sixteen for every box the direct form opens, 256 for every
+step of the binned one.  A recheck margin above half the windows' slack always
+takes the binned form, so the same call with one has the slots to compare with."""
+import numpy as np
+import pytest
+
+from tests.fixtures import random_pair
+
+pytestmark = pytest.mark.gpu
+
+BINNED_MARGIN = 6e-3   # above half of the bin windows' slack of 1e-2 px
+
+
+@pytest.fixture(scope="module")
+def sfm():
+    import torch
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    import paper_1512_06235_amd as sfm
+    sfm.lib()
+    return sfm
+
+
+def slots_of(sfm, m, pairs, Fs, **kw):
+    out = m.match(pairs, Fs, **kw)
+    return out, sfm.sfm_last_stats(m.ctx)["slots"]
+
+
+def goes_direct(sfm, m, pairs, Fs):
+    binned = slots_of(sfm, m, pairs, Fs, recheck_margin_px=BINNED_MARGIN)[1]
+    return slots_of(sfm, m, pairs, Fs)[1] != binned
+
+
+def test_more_pairs_than_a_launch_has_rows(sfm):
+    """70,000 pairs of small images: more than 65,535, which the second and
+    third dimension of a launch end at.  Every pair equals the same pair in a
+    call of its own few."""
+    images, F = [], None
+    for k, n in enumerate((50, 41, 16, 1, 0, 33)):
+        xy, desc, _, _, F = random_pair(n, 0, seed=500 + k)
+        images.append((xy, desc // 16))
+    few = [(a, b, 4.0 + a) for a in range(6) for b in range(6)]
+    many = [few[k % len(few)] for k in range(70_000)]
+    m = sfm.Matcher().register(images)
+    assert goes_direct(sfm, m, many, [F] * len(many))
+    one = m.match(few, [F] * len(few))
+    all_ = m.match(many, [F] * len(many))
+    at = np.arange(len(many)) % len(few)
+    for name in ("n_comparisons", "n_borderline"):
+        a, b = getattr(one, name).cpu().numpy(), getattr(all_, name).cpu().numpy()
+        assert np.array_equal(a[at], b), name
+    off1, off = one.offset.cpu().numpy(), all_.offset.cpu().numpy()
+    assert np.array_equal(np.diff(off), np.diff(off1)[at]) and off1[-1] > 0
+    rows = np.concatenate([np.arange(off1[k], off1[k + 1]) for k in at])
+    for name in ("query", "match", "d1", "d2"):
+        a, b = getattr(one, name).cpu().numpy(), getattr(all_, name).cpu().numpy()
+        assert np.array_equal(a[rows], b[:off[-1]]), name
+    m.close()
