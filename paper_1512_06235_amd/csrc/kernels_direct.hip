@@ -301,7 +301,7 @@ __global__ __launch_bounds__(64 * kDirectWaves) __attribute__((amdgpu_waves_per_
   if (threadIdx.x == 0 && sums[0]) atomicAdd(&C->comparisons, sums[0]);
   if (threadIdx.x == 1 && sums[1]) atomicAdd(&C->elements, sums[1]);
   if (threadIdx.x == 2 && sums[2]) atomicAdd(&C->borderline, sums[2]);
-  if (threadIdx.x == 3 && sums[3]) atomicAdd(&C->accepted, sums[3]);
+  if (threadIdx.x == 3 && sums[3]) atomicAdd(&C->accepted, uint32_t(sums[3]));
 }
 
 }  // namespace

@@ -461,7 +461,7 @@ __global__ __launch_bounds__(kMergeThreads) void exhaustive_merge_kernel(BatchVi
   }
   const unsigned long long m = __ballot(accept);
   if (lane == 0 && m)
-    atomicAdd(&v.counters[p].accepted, (unsigned long long)__builtin_popcountll(m));
+    atomicAdd(&v.counters[p].accepted, uint32_t(__builtin_popcountll(m)));
 }
 
 }  // namespace

@@ -510,7 +510,7 @@ __device__ __forceinline__ void grid_finish(const GridView& v, int64_t q_off, in
     r.flags = (accept ? 1 : 0) | (v.keep_counts ? (n << 1) : 0);
     v.res[q_off + i] = r;
     atomicAdd(&v.counters[pr].comparisons, static_cast<unsigned long long>(n));
-    if (accept) atomicAdd(&v.counters[pr].accepted, 1ull);
+    if (accept) atomicAdd(&v.counters[pr].accepted, 1u);
   }
 }
 
@@ -636,7 +636,7 @@ __global__ __launch_bounds__(64, 4) void grid_query_kernel(GridView v) {
   }
   if (lane == 0) {
     if (comparisons) atomicAdd(&v.counters[pr].comparisons, comparisons);
-    if (accepted) atomicAdd(&v.counters[pr].accepted, (unsigned long long)accepted);
+    if (accepted) atomicAdd(&v.counters[pr].accepted, accepted);
   }
 }
 

@@ -123,7 +123,7 @@ struct MatchLds {
   uint32_t nc[kBuf];
   int32_t j[2][kBuf];
   uint4 queue[kWaves][kBorderCap];   // {key, rel. position << 7 | tile << 6 | lane, j, -}
-  unsigned long long stats[2][8];    // of this group and the last, in PairCounters' order
+  unsigned long long stats[2][8];    // of this group and the last: PairCounters' words
   int32_t taken;                     // the workgroup's next group (-1: none)
 };
 static_assert(sizeof(MatchLds) <= 40960, "four workgroups per CU");
@@ -319,9 +319,12 @@ struct Tile {
 // instruction.  (Groups that run side by side are of one pair, whose counters
 // share a cache line, and a line takes an addition in about 5 ns: five per wave
 // and group, 690,000 for 500 pairs, held the kernel up, 475 us.)
-constexpr int kStats = 5;   // the fields of PairCounters
-static_assert(sizeof(PairCounters) == kStats * sizeof(unsigned long long),
-              "a lane per counter");
+// A lane adds a 64-bit word of PairCounters; the last holds two counters, of
+// which the lower never carries (a pair has fewer than 2^31 queries).
+constexpr int kStats = 4;
+static_assert(sizeof(PairCounters) == kStats * sizeof(unsigned long long) &&
+                  offsetof(PairCounters, accepted) == 24 && offsetof(PairCounters, ties) == 28,
+              "a lane per word");
 __device__ __forceinline__ void flush_stats(const BatchView& v, unsigned long long* sums,
                                             int32_t pair, int lane) {
   if (lane < kStats) {
@@ -908,8 +911,7 @@ __device__ __forceinline__ void match_group(const BatchView& v, const TileGroup&
         lane == 0   ? (unsigned long long)tsum
         : lane == 1 ? (unsigned long long)nsteps * (kQueryTile * kQueryTile)
         : lane == 2 ? wbl
-        : lane == 3 ? nacc
-                    : ties;
+                    : (unsigned long long)ties << 32 | nacc;
     atomicAdd(&L.stats[par][lane], x);
   }
 }

@@ -134,8 +134,8 @@ struct PairCounters {
   unsigned long long comparisons;
   unsigned long long elements;   // (query, candidate) slots evaluated, padding included
   unsigned long long borderline; // slots whose FP32 distance lay within the margin of d
-  unsigned long long accepted;
-  unsigned long long ties;       // chunks that needed the tie-break pass
+  uint32_t accepted;             // at most the pair's queries, as are ...
+  uint32_t ties;                 // ... the chunks that needed the tie-break pass
 };
 
 // Up to kMaxGroupTiles consecutive query tiles of one pair and the union of

@@ -57,3 +57,14 @@ def test_more_pairs_than_a_launch_has_rows(sfm):
         a, b = getattr(one, name).cpu().numpy(), getattr(all_, name).cpu().numpy()
         assert np.array_equal(a[rows], b[:off[-1]]), name
     m.close()
+
+
+def test_bytes_a_pair_takes(sfm):
+    """The workspace of a pair of empty images: descriptor 96, F 72, order 4,
+    geometry 184, counters 32, cost 8, 16 padding targets of 16 bytes, two bin
+    starts.  (A call at its budget, or at the scratch of the form that does not
+    allocate, is refused for a byte more.)"""
+    m = sfm.Matcher().register([random_pair(0, 0, seed=1)[:2]])
+    few, many = (sfm.sfm_workspace_size(m.ctx, [(0, 0, 4.0)] * n) for n in (4096, 8192))
+    assert many - few == 4096 * (96 + 72 + 4 + 184 + 32 + 8 + 16 * 16 + 8)
+    m.close()
