@@ -1229,7 +1229,7 @@ int sfm_grid_match(sfm_ctx* ctx, const sfm_pair* pairs, int32_t n_pairs, const d
     g.strip = 4 * g.nfx;
     g.ncell = (g.nfy + 3) / 4 * g.strip;
     g.cell_off = cells;
-    cells += (int64_t(g.ncell) + 1 + 31) & ~int64_t(31);   // tables start on 128-byte lines
+    cells += (int64_t(g.ncell) + kGridTableInts) / kGridTableInts * kGridTableInts;
     max_cells = std::max(max_cells, int64_t(g.ncell));
     sum_na += g.na;
     items += g.nb;
@@ -1251,15 +1251,12 @@ int sfm_grid_match(sfm_ctx* ctx, const sfm_pair* pairs, int32_t n_pairs, const d
     HIP_TRY(ctx, hipMemsetAsync(out->offset, 0, sizeof(int64_t), st));
     return SFM_OK;
   }
-  // Workspace: staged part (grid pairs, pair descriptors, F), then tables.
-  size_t o = 0;
-  const size_t o_gp = o; o = align_up(o + P * sizeof(GridPair));
-  const size_t o_pd = o; o = align_up(o + P * sizeof(PairDesc));
-  const size_t o_F = o; o = align_up(o + P * 9 * sizeof(double));
   // The block table in eight shares of about equal cost, one per XCD (workgroup
   // k runs on XCD k mod 8): a share is a run of consecutive blocks, so an XCD
   // works on a pair or two at a time and their descriptors stay in its L2.  A
-  // query's cost is its samples plus its candidates, about n_b / 100 of them.
+  // query's cost is its samples plus its candidates, taken as n_b / 100 of them,
+  // which they are at d = 4 on boxes of 1,024 x 768; elsewhere the shares are less
+  // even.
   std::vector<int2> blocks;
   int32_t max_na = 0;
   {
@@ -1276,31 +1273,56 @@ int sfm_grid_match(sfm_ctx* ctx, const sfm_pair* pairs, int32_t n_pairs, const d
       }
       max_na = std::max(max_na, gp[k].na);
     }
-    size_t longest = 0;
+    size_t longest = 0, sixteens = 0;
     for (const auto& s : share) longest = std::max(longest, s.size());
-    blocks.resize(longest * kXcds, make_int2(-1, 0));
-    for (size_t x = 0; x < size_t(kXcds); ++x)
-      for (size_t i = 0; i < share[x].size(); ++i) blocks[i * kXcds + x] = share[x][i];
+    for (const GridPair& g : gp) sixteens += size_t((g.na + 15) / 16);
+    // Shares of equal cost differ in length where pairs differ in n_b; the padded
+    // table takes no more than an entry per sixteen queries, or it stays plain.
+    if (align_up(longest * kXcds * sizeof(int2)) <= align_up(sixteens * sizeof(int2))) {
+      blocks.resize(longest * kXcds, make_int2(-1, 0));
+      for (size_t x = 0; x < size_t(kXcds); ++x)
+        for (size_t i = 0; i < share[x].size(); ++i) blocks[i * kXcds + x] = share[x][i];
+    } else {
+      for (const auto& s : share) blocks.insert(blocks.end(), s.begin(), s.end());
+    }
   }
   if (blocks.size() > size_t(INT32_MAX)) return fail(ctx, SFM_ECAPACITY, "too many queries");
-  const size_t o_blk = o; o = align_up(o + std::max<size_t>(blocks.size(), 1) * sizeof(int2));
   const bool grouped = ctx->grid_group_px > 0.0 && sum_na > 0;
   if (grouped && sum_na > INT32_MAX / 4) return fail(ctx, SFM_ECAPACITY, "too many queries");
   const size_t N = size_t(sum_na);
-  const size_t o_seg = o; o = align_up(o + 2 * P * sizeof(int32_t));
-  const size_t staged = o;
   size_t temp_bytes = 0;
   if (grouped) HIP_TRY(ctx, grid_group_temp_bytes(int32_t(N), n_pairs, &temp_bytes));
-  const size_t o_cross = o; o = align_up(o + (grouped ? N * 4 * sizeof(double) : 0));
-  const size_t o_hit = o; o = align_up(o + (grouped ? N * sizeof(int32_t) : 0));
-  const size_t o_val = o; o = align_up(o + (grouped ? 2 * N * sizeof(int32_t) : 0));
-  const size_t o_sten = o; o = align_up(o + (grouped ? 3 * N * sizeof(int32_t) : 0));
-  const size_t o_temp = o; o = align_up(o + temp_bytes);
-  const size_t o_start = o; o = align_up(o + size_t(cells) * sizeof(int32_t));
-  const size_t o_items = o; o = align_up(o + size_t(std::max<int64_t>(items, 1)) * sizeof(int32_t));
-  const size_t o_res = o; o = align_up(o + size_t(std::max<int64_t>(sum_na, 1)) * sizeof(QueryResult));
-  const size_t o_cnt = o; o = align_up(o + P * sizeof(PairCounters));
-  if ((rc = ensure_workspace(ctx, o))) return rc;
+  // Workspace: staged part (grid pairs, pair descriptors, F, blocks, segments),
+  // then tables.  Packed where the aligned sections exceed the budget.
+  size_t o_gp, o_pd, o_F, o_blk, o_seg, staged, o_cross, o_hit, o_val, o_sten, o_temp, o_start,
+      o_items, o_res, o_cnt;
+  const auto lay_out = [&](size_t align) {
+    size_t o = 0;
+    const auto section = [&](size_t bytes) {
+      const size_t at = o;
+      o = (o + bytes + align - 1) / align * align;
+      return at;
+    };
+    o_gp = section(P * sizeof(GridPair));
+    o_pd = section(P * sizeof(PairDesc));
+    o_F = section(P * 9 * sizeof(double));
+    o_blk = section(std::max<size_t>(blocks.size(), 1) * sizeof(int2));
+    o_seg = section(2 * P * sizeof(int32_t));
+    staged = o;
+    o_cross = section(grouped ? N * 4 * sizeof(double) : 0);
+    o_hit = section(grouped ? N * sizeof(int32_t) : 0);
+    o_val = section(grouped ? 2 * N * sizeof(int32_t) : 0);
+    o_sten = section(grouped ? 3 * N * sizeof(int32_t) : 0);
+    o_temp = section(temp_bytes);
+    o_start = section(size_t(cells) * sizeof(int32_t));
+    o_items = section(size_t(std::max<int64_t>(items, 1)) * sizeof(int32_t));
+    o_res = section(size_t(std::max<int64_t>(sum_na, 1)) * sizeof(QueryResult));
+    o_cnt = section(P * sizeof(PairCounters));
+    return o;
+  };
+  size_t need = lay_out(kAlign);
+  if (need > ctx->budget) need = lay_out(sizeof(double));
+  if ((rc = ensure_workspace(ctx, need))) return rc;
   if ((rc = ensure_pinned(ctx, staged))) return rc;
   if (ctx->has_work) HIP_TRY(ctx, hipStreamWaitEvent(st, ctx->work_done, 0));
   HIP_TRY(ctx, hipEventSynchronize(ctx->staging_done));

@@ -219,7 +219,7 @@ struct Sampler {
   }
 
   // Relative to the first cell.  (Samples lie in b's box, whose cells have a
-  // margin of two on every side: the clamp never changes one.)
+  // margin on every side: the clamp never changes one.)
   __device__ __forceinline__ int2 corner(int32_t x, int32_t y) const {
     return make_int2(min(max(x - fx0, 0), xmax), min(max(y - fy0, 0), ymax));
   }

@@ -256,9 +256,14 @@ constexpr int32_t kGridMaxCand = 1024;                // |C'| per query
 constexpr int32_t kGridQueriesPerBlock = 32;          // queries of one workgroup (at most 64)
 constexpr int64_t kGridMaxCells = int64_t(1) << 22;   // cells of one grid of one pair
 
-// Per pair, filled on the host: the d x d cells over b's keypoint box with an
-// empty margin of two (kGridMargin), stored in strips of four rows.
-constexpr int32_t kGridMargin = 2;
+// Per pair, filled on the host: the d x d cells over b's keypoint box and one
+// empty cell around them (kGridMargin), stored in strips of four rows.  (A sample
+// in the box selects the 2 x 2 cells around its nearest multiple of d: the
+// sample's cell and a neighbour in x and in y.  A wider margin would make the
+// table of a box one cell thin larger than the four grids' tables of 2d x 2d
+// cells and cursors, 8 + 8 bytes a cell, that calls were sized for.)
+constexpr int32_t kGridMargin = 1;
+constexpr int32_t kGridTableInts = 16;    // tables start on 64-byte lines
 struct GridPair {
   int32_t a, b, na, nb;
   int64_t q_off;            // into per-query results

@@ -1,0 +1,62 @@
+"""Calls at their workspace budget: what fitted a budget once still does, and
+gives the same results as with room to spare."""
+import math
+
+import numpy as np
+import pytest
+
+from tests.fixtures import random_pair, translation_F
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module")
+def sfm():
+    import torch
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    import paper_1512_06235_amd as sfm
+    sfm.lib()
+    return sfm
+
+
+def aligned(sections, to=256):
+    return sum(-(-s // to) * to for s in sections)
+
+
+def four_grids_bytes(pairs, boxes, n):
+    """Workspace of the grid search with a table and cursors for each of its four
+    grids, a block of sixteen queries and four item lists (what calls were sized
+    for first); boxes are (x0, y0, x1, y1) of the targets."""
+    cells = 0
+    for _, b, d in pairs:
+        x0, y0, x1, y1 = boxes[b]
+        for sx in (0.0, d):
+            for sy in (0.0, d):
+                side = [math.floor((hi - s) / (2 * d)) - math.floor((lo - s) / (2 * d)) + 1
+                        for lo, hi, s in ((x0, x1, sx), (y0, y1, sy))]
+                cells += side[0] * side[1] + 1
+    P, na = len(pairs), sum(n[a] for a, _, _ in pairs)
+    return aligned([168 * P, 96 * P, 72 * P, 8 * sum(-(-n[a] // 16) for a, _, _ in pairs), 8 * P,
+                    4 * cells, 4 * cells, 16 * sum(n[b] for _, b, _ in pairs), 16 * na, 32 * P])
+
+
+@pytest.mark.parametrize("size,d,n", [((40000, 0.75), 0.5, 5), ((0.5, 30000), 1.0, 3),
+                                      ((0.25, 0.25), 2.0, 40), ((1024, 768), 4.0, 300)])
+def test_grid_of_thin_boxes_fits(sfm, size, d, n):
+    """Boxes one cell thin, a single cell, and an image."""
+    from oracle.grid import grid_match
+    from tests.test_gpu_grid import _check
+    rng = np.random.default_rng(n)
+    _, desc, _, _, _ = random_pair(n, 0, seed=n)
+    xy = (rng.uniform(0, 1, (n, 2)) * size + 0.25).astype(np.float32)
+    xy[:2] = [[0.25, 0.25], [0.25 + size[0], 0.25 + size[1]]]
+    images = [(xy, desc // 16)]
+    box = tuple(float(v) for v in (*xy.min(axis=0), *xy.max(axis=0)))
+    pairs = [(0, 0, d)] * 3
+    Fs = [translation_F((1.0, 0.0, 0.0)), translation_F((0.0, 1.0, 0.0)),
+          translation_F((size[0] / 2, size[1] / 3, 1.0))]
+    m = sfm.Matcher(workspace_budget_bytes=four_grids_bytes(pairs, [box], [n])).register(images)
+    out = m.match(pairs, Fs, form="grid", emit_all=True)
+    _check(out, images, pairs, Fs, grid_match(images, pairs, Fs))
+    m.close()
