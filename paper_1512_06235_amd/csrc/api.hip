@@ -1703,28 +1703,41 @@ int sfm_candidate_images(sfm_ctx* ctx, const int32_t* vis_off, const int32_t* vi
   if (ctx->covis_method == 0 && n_images > 0 && n_points > 0) {
     const double hist = double(nnz) * double(nnz) / double(n_points);
     const double prod = double(n_images) * double(n_images) * double(pwords) / 2.0;
-    // A product whose bitsets and counts outgrow the budget leaves it to the
-    // histogram.
-    const size_t need = size_t(n_images) * (pwords + size_t(n_images)) * 4 + (size_t(1) << 20);
-    use_gram = 0.02 * prod < 8.0 * hist + 300.0 * double(nnz) && need <= ctx->budget;
+    use_gram = 0.02 * prod < 8.0 * hist + 300.0 * double(nnz);
   }
-  size_t o = 0;
-  const size_t hist_np1 = use_gram ? 0 : np1;
-  const size_t o_count = o; o = align_up(o + hist_np1 * 4);
-  const size_t o_off = o; o = align_up(o + hist_np1 * 4);
-  const size_t o_cursor = o; o = align_up(o + hist_np1 * 4);
-  const size_t o_imgs = o; o = align_up(o + (use_gram ? 1 : std::max<size_t>(size_t(nnz), 1)) * 4);
-  const size_t o_sums = o; o = align_up(o + nsums * 4);
-  const size_t o_rc = o; o = align_up(o + ni1 * 4);
-  const size_t o_bits = o; o = align_up(o + std::max<size_t>(size_t(n_images) * words, 1) * 4);
-  const size_t o_bitset = o;
-  o = align_up(o + (use_gram ? std::max<size_t>(size_t(n_images) * pwords, 1) : 1) * 4);
-  const size_t o_gram = o;
-  const size_t matrix = use_gram ? size_t(n_images) * size_t(n_images) * 4 : 0;
-  int32_t slices = use_gram ? covis_gram_slices(n_images, n_points) : 1;
-  while (slices > 1 && align_up(o + matrix * size_t(slices)) > ctx->budget) slices >>= 1;
-  o = align_up(o + std::max<size_t>(matrix * size_t(slices), 4));
-  int rc = ensure_workspace(ctx, o);
+  size_t o_count, o_off, o_cursor, o_imgs, o_sums, o_rc, o_bits, o_bitset, o_gram;
+  const auto lay_out = [&](size_t row_words, int32_t slices) {   // the workspace's bytes
+    size_t o = 0;
+    const auto section = [&](size_t ints) {
+      const size_t at = o;
+      o = align_up(o + ints * 4);
+      return at;
+    };
+    const size_t hist_np1 = use_gram ? 0 : np1, n = use_gram ? size_t(n_images) : 0;
+    o_count = section(hist_np1);
+    o_off = section(hist_np1);
+    o_cursor = section(hist_np1);
+    o_imgs = section(use_gram ? 1 : std::max<size_t>(size_t(nnz), 1));
+    o_sums = section(nsums);
+    o_rc = section(ni1);
+    o_bits = section(std::max<size_t>(size_t(n_images) * words, 1));
+    o_bitset = section(std::max<size_t>(n * row_words, 1));
+    o_gram = section(std::max<size_t>(n * n * size_t(slices), 1));
+    return o;
+  };
+  // Bitset rows of whole units and a count matrix per slice where the budget has
+  // them, else rows of the points' words and one matrix.  A product that does
+  // not fit as that either is left to the histogram, unless it was asked for.
+  size_t row_words = pwords;
+  const size_t point_words = (size_t(n_points) + 31) / 32;
+  int32_t slices = 1;
+  if (use_gram && ctx->covis_method == 0 && lay_out(point_words, 1) > ctx->budget) use_gram = false;
+  if (use_gram) {
+    if (lay_out(pwords, 1) > ctx->budget) row_words = point_words;
+    slices = covis_gram_slices(n_images, n_points);
+    while (slices > 1 && lay_out(row_words, slices) > ctx->budget) slices >>= 1;
+  }
+  int rc = ensure_workspace(ctx, lay_out(row_words, slices));
   if (rc) return rc;
   if (ctx->has_work) HIP_TRY(ctx, hipStreamWaitEvent(st, ctx->work_done, 0));
   CovisArgs a;
@@ -1744,6 +1757,7 @@ int sfm_candidate_images(sfm_ctx* ctx, const int32_t* vis_off, const int32_t* vi
   a.bits = reinterpret_cast<uint32_t*>(ctx->ws + o_bits);
   a.bitset = reinterpret_cast<uint32_t*>(ctx->ws + o_bitset);
   a.gram = use_gram ? reinterpret_cast<int32_t*>(ctx->ws + o_gram) : nullptr;
+  a.row_words = int64_t(row_words);
   a.slices = slices;
   a.cand = out->cand;
   a.n_shared = out->n_shared;

@@ -290,8 +290,8 @@ __global__ __launch_bounds__(NT) void covis_rows_kernel(
 
 // ---------------------------------------------------------------------------
 // Bit-matrix path: V[i] = the bitset of image i's points (words of 32
-// points, rows padded with zeros to whole units), and |P_cv(i, j)| = sum over
-// points of V[i] V[j].
+// points, rows padded with zeros to whole units where the workspace has room),
+// and |P_cv(i, j)| = sum over points of V[i] V[j].
 // ---------------------------------------------------------------------------
 constexpr int kBitsLdsWords = 8192;   // points per LDS pass of the bitset build: 262,144
 
@@ -358,6 +358,8 @@ __device__ __forceinline__ v8i expand_j(uint32_t w) {
              int((w >> 1) & 0x44444444u), 0, 0, 0, 0};
 }
 
+// kWhole: rows are whole units.  Otherwise the words past a row's end read as 0.
+template <bool kWhole>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2)))
 void gram_kernel(const uint32_t* V, int32_t n_images, int64_t words, int32_t slices,
                  int32_t nblk, int32_t* gram) {
@@ -374,10 +376,13 @@ void gram_kernel(const uint32_t* V, int32_t n_images, int64_t words, int32_t sli
   const int t = threadIdx.x, lane = t & 63, wave = t >> 6;
   const int r = lane & 15, g = lane >> 4;
   for (int x = t; x < kGramRows * (kGramRows + 1); x += 256) (&sum[0][0])[x] = 0;
-  const int64_t units = words / kUnitWords;
+  const int64_t units = (words + kUnitWords - 1) / kUnitWords;
   const int64_t u0 = units * slice / slices, u1 = units * (slice + 1) / slices;
   typedef uint32_t v4u __attribute__((ext_vector_type(4)));
+  typedef uint32_t v4w __attribute__((ext_vector_type(4), aligned(4)));   // rows of any length
   typedef const __attribute__((address_space(1))) v4u g_v4u;
+  typedef const __attribute__((address_space(1))) v4w g_v4w;
+  typedef const __attribute__((address_space(1))) uint32_t g_u32;
   // Rows past the last image read the last one; their counts are not written.
   const uint32_t* pi[kGramTiles];
   const uint32_t* pj[kGramTiles];
@@ -386,6 +391,17 @@ void gram_kernel(const uint32_t* V, int32_t n_images, int64_t words, int32_t sli
     pi[k] = V + int64_t(min(I * kGramRows + 16 * k + r, n_images - 1)) * words + 4 * g;
     pj[k] = V + int64_t(min(J * kGramRows + 16 * k + r, n_images - 1)) * words + 4 * g;
   }
+  // The lane's four words of unit u of a row (p: the row's word 4 g).
+  auto unit = [&](const uint32_t* p, int64_t u) -> v4u {
+    if (kWhole) return *(g_v4u*)(p + u * kUnitWords);
+    const int64_t left = words - (u * kUnitWords + 4 * g);
+    if (left >= 4) return *(g_v4w*)(p + u * kUnitWords);
+    v4u x = {0u, 0u, 0u, 0u};
+#pragma unroll
+    for (int k = 0; k < 3; ++k)
+      if (k < left) x[k] = *(g_u32*)(p + u * kUnitWords + k);
+    return x;
+  };
   v4f acc[kGramTiles][kGramTiles];
 #pragma unroll
   for (int a = 0; a < kGramTiles; ++a)
@@ -411,8 +427,8 @@ void gram_kernel(const uint32_t* V, int32_t n_images, int64_t words, int32_t sli
   if (u < u1) {
 #pragma unroll
     for (int k = 0; k < kGramTiles; ++k) {
-      ni[k] = *(g_v4u*)(pi[k] + u * kUnitWords);
-      nj[k] = *(g_v4u*)(pj[k] + u * kUnitWords);
+      ni[k] = unit(pi[k], u);
+      nj[k] = unit(pj[k], u);
     }
   }
   for (; u < u1; u += 4) {
@@ -422,8 +438,8 @@ void gram_kernel(const uint32_t* V, int32_t n_images, int64_t words, int32_t sli
     for (int k = 0; k < kGramTiles; ++k) {
       wi[k] = ni[k];
       wj[k] = nj[k];
-      ni[k] = *(g_v4u*)(pi[k] + un * kUnitWords);
-      nj[k] = *(g_v4u*)(pj[k] + un * kUnitWords);
+      ni[k] = unit(pi[k], un);
+      nj[k] = unit(pj[k], un);
     }
 #pragma unroll
     for (int w = 0; w < 4; ++w) {
@@ -534,13 +550,18 @@ hipError_t launch_candidates(const CovisArgs& a, hipStream_t st) {
   if (a.gram) {
     // Bit-matrix path: bitset rows, the count matrices, then each row's ranking.
     if (a.n_images > 0) {
-      const int64_t words = covis_bitset_words(a.n_points);
+      const int64_t words = a.row_words;
       hipLaunchKernelGGL(bitset_rows_kernel, dim3(a.n_images), dim3(1024), 0, st, a.vis_off,
                          a.vis_pts, a.nnz, a.n_points, words, a.bitset, bits, bit_words,
                          a.err);
       const int32_t nblk = (a.n_images + kGramRows - 1) / kGramRows;
-      hipLaunchKernelGGL(gram_kernel, dim3(nblk * (nblk + 1) / 2 * a.slices), dim3(256), 0, st,
-                         a.bitset, a.n_images, words, a.slices, nblk, a.gram);
+      const dim3 blocks(nblk * (nblk + 1) / 2 * a.slices);
+      if (words % kUnitWords == 0)
+        hipLaunchKernelGGL(gram_kernel<true>, blocks, dim3(256), 0, st, a.bitset, a.n_images, words,
+                           a.slices, nblk, a.gram);
+      else
+        hipLaunchKernelGGL(gram_kernel<false>, blocks, dim3(256), 0, st, a.bitset, a.n_images,
+                           words, a.slices, nblk, a.gram);
       hipLaunchKernelGGL((covis_rows_kernel<true, kRankThreads>), dim3(a.n_images), dim3(kRankThreads), 0, st,
                          a.vis_off, a.vis_pts, a.nnz, a.n_images, a.n_points, a.pt_off,
                          a.pt_imgs, a.gram, a.slices, a.threshold, a.top_k, a.cand, a.n_shared,

@@ -217,10 +217,12 @@ struct CovisArgs {
   // sums.
   int32_t *pt_count, *pt_off, *cursor, *pt_imgs, *sums, *row_count;
   uint32_t* bits;
-  // Bit-matrix path (when gram is not NULL): image bitsets
-  // (covis_bitset_words per row), then `slices` n x n count matrices.
+  // Bit-matrix path (when gram is not NULL): image bitsets (row_words words per
+  // row: covis_bitset_words, or no more than the points take), then `slices`
+  // n x n count matrices.
   uint32_t* bitset;
   int32_t* gram;
+  int64_t row_words;
   int32_t slices;
   // Outputs.
   int32_t *cand, *n_shared, *n_cand, *pairs;

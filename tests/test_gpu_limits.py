@@ -60,3 +60,37 @@ def test_grid_of_thin_boxes_fits(sfm, size, d, n):
     out = m.match(pairs, Fs, form="grid", emit_all=True)
     _check(out, images, pairs, Fs, grid_match(images, pairs, Fs))
     m.close()
+
+
+def _lists(n, npts, most, seed):
+    rng = np.random.default_rng(seed)
+    return [np.sort(rng.choice(npts, size=int(rng.integers(1, most + 1)), replace=False))
+            .astype(np.int32) for _ in range(n)]
+
+
+def product_bytes(n, npts):
+    """Workspace of the bit-matrix product with bitset rows of the points' words."""
+    words, side = -(-npts // 32), max(n, npts) + 1
+    return aligned([4, 4 * ((side + 8191) // 8192 + 1), 4 * (n + 1), 4 * n * -(-n // 32),
+                    4 * n * words, 4 * n * n])
+
+
+@pytest.mark.parametrize("n, npts", [(2, 1), (65, 33), (129, 523), (200, 70), (300, 4000)])
+def test_product_without_padded_rows(sfm, n, npts):
+    """The product on a budget that holds the points' words and one count matrix."""
+    from tests.test_gpu_covis import _check
+    m = sfm.Matcher(workspace_budget_bytes=product_bytes(n, npts))
+    for method in (2, 0):
+        sfm.sfm_set_covis_method(m.ctx, method)
+        _check(sfm, m, _lists(n, npts, min(npts, 200), n), npts, 0, 9)
+    m.close()
+
+
+def test_product_that_does_not_fit_leaves_it_to_the_histogram(sfm):
+    """3,200 images of 600 points, for which the product is the faster: a budget
+    for its bitsets and counts that has no room for the pairs' bits (1.3 MB)."""
+    from tests.test_gpu_covis import _check
+    n, npts = 3200, 600
+    m = sfm.Matcher(workspace_budget_bytes=4 * n * (32 + n) + (1 << 20))
+    _check(sfm, m, _lists(n, npts, 30, 5), npts, 2, 9)
+    m.close()
