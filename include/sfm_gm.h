@@ -484,7 +484,10 @@ int sfm_triangulate(sfm_ctx* ctx, int64_t n_nodes, const int32_t* label, const i
  * {4, 8} and features_per_bin in {4, 8, 16} (one warm-up and `repeats`
  * timed calls each, HIP events on `stream`), keep the fastest setting on the
  * context, and write the mean milliseconds per call to ms_out[3 * i + j]
- * (i over group_tiles, j over features_per_bin; ms_out may be NULL).  Uses
+ * (i over group_tiles, j over features_per_bin; ms_out may be NULL).  Every
+ * trial runs as its setting says, also where sfm_guided_match would match the
+ * batch without binning or in groups of 4 whatever the setting: the setting is
+ * for later calls that heed it.  Uses
  * scratch outputs it allocates and frees; blocks until done. */
 int sfm_autotune(sfm_ctx* ctx, const sfm_pair* pairs, int32_t n_pairs, const double* F,
                  const sfm_options* opt, void* stream, int32_t repeats, double* ms_out);

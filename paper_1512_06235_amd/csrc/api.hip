@@ -329,7 +329,9 @@ int ensure_pin(sfm_ctx* ctx, const Space& sp, size_t bytes) {
 int ensure_workspace(sfm_ctx* ctx, size_t bytes) { return ensure_ws(ctx, ctx_space(ctx), bytes); }
 int ensure_pinned(sfm_ctx* ctx, size_t bytes) { return ensure_pin(ctx, ctx_space(ctx), bytes); }
 
-enum class Form { kBatched, kPlain, kExhaustive, kBandError };
+// kTuned: the batched form as the tuning says, neither direct nor cut into smaller
+// groups (what the autotuner times).
+enum class Form { kBatched, kTuned, kPlain, kExhaustive, kBandError };
 
 sfm_options default_options() {
   sfm_options o;
@@ -618,8 +620,11 @@ int match_locked(sfm_ctx* ctx, const ImageTable& tab, const sfm_pair* pairs, int
     if (n_items > INT32_MAX) return fail(ctx, SFM_ECAPACITY, "too many work items in one call");
   }
   HIP_TRY(ctx, hipSetDevice(ctx->device));
-  const Layout L = exhaustive ? plan(pd, ctx->device, ctx->group_tiles, n_items, n_part, true)
-                              : plan_guided(ctx, pd.data(), pd.size(), form == Form::kPlain, S.budget);
+  const Layout L =
+      exhaustive ? plan(pd, ctx->device, ctx->group_tiles, n_items, n_part, true)
+      : form == Form::kTuned
+          ? plan(pd, ctx->device, ctx->group_tiles)
+          : plan_guided(ctx, pd.data(), pd.size(), form == Form::kPlain, S.budget);
   if (!diagnostic && (rc = check_outputs(ctx, out, L, opt))) return rc;
   if (diagnostic && opt.emit_all) return fail(ctx, SFM_EINVAL, "emit_all has no outputs here");
 
@@ -653,7 +658,8 @@ int match_locked(sfm_ctx* ctx, const ImageTable& tab, const sfm_pair* pairs, int
   if (direct) v.cand_j = nullptr;   // results hold the index in b
 
   // The layout of a batched call, for graph replay.
-  const bool replay = !alt && ctx->graph_replay && !ctx->profiling && form == Form::kBatched;
+  const bool replay = !alt && ctx->graph_replay && !ctx->profiling &&
+                      (form == Form::kBatched || form == Form::kTuned);
   GraphKey key;
   memset(&key, 0, sizeof key);
   if (replay) {
@@ -1888,11 +1894,11 @@ int sfm_autotune(sfm_ctx* ctx, const sfm_pair* pairs, int32_t n_pairs, const dou
     for (int fi = 0; fi < 3 && rc == SFM_OK; ++fi) {
       set(kTiles[ti], kFpb[fi]);
       // One untimed run sizes the workspace for this configuration.
-      rc = run_match(ctx, pairs, n_pairs, F, opt, &out, stream, Form::kBatched);
+      rc = run_match(ctx, pairs, n_pairs, F, opt, &out, stream, Form::kTuned);
       if (rc) break;
       if (hipEventRecord(e0, st) != hipSuccess) { rc = SFM_EHIP; break; }
       for (int32_t r = 0; r < repeats && rc == SFM_OK; ++r)
-        rc = run_match(ctx, pairs, n_pairs, F, opt, &out, stream, Form::kBatched);
+        rc = run_match(ctx, pairs, n_pairs, F, opt, &out, stream, Form::kTuned);
       if (rc) break;
       float ms = 0.0f;
       if (hipEventRecord(e1, st) != hipSuccess || hipEventSynchronize(e1) != hipSuccess ||

@@ -1,7 +1,8 @@
 """Which form a guided call takes, the direct or the binned one, shows in the
 slots it evaluates: sixteen for every box the direct form opens, 256 for every
 step of the binned one.  A recheck margin above half the windows' slack always
-takes the binned form, so the same call with one has the slots to compare with."""
+takes the binned form, so the same call with one has the slots to compare with
+(alike, not equal: the items of a bin or a cell are in no fixed order)."""
 import numpy as np
 import pytest
 
@@ -29,7 +30,8 @@ def slots_of(sfm, m, pairs, Fs, **kw):
 
 def goes_direct(sfm, m, pairs, Fs):
     binned = slots_of(sfm, m, pairs, Fs, recheck_margin_px=BINNED_MARGIN)[1]
-    return slots_of(sfm, m, pairs, Fs)[1] != binned
+    own = slots_of(sfm, m, pairs, Fs)[1]
+    return own % 256 != 0 or abs(own - binned) > 0.02 * binned
 
 
 def test_more_pairs_than_a_launch_has_rows(sfm):
@@ -68,3 +70,38 @@ def test_bytes_a_pair_takes(sfm):
     few, many = (sfm.sfm_workspace_size(m.ctx, [(0, 0, 4.0)] * n) for n in (4096, 8192))
     assert many - few == 4096 * (96 + 72 + 4 + 184 + 32 + 8 + 16 * 16 + 8)
     m.close()
+
+
+def test_autotuner_times_its_settings(sfm):
+    """The trials of a batch that a call would match directly, or in groups of
+    four where the setting says eight, still run as their setting says (the last
+    one: eight tiles, sixteen features per bin)."""
+    images, F = [], None
+    for k, n in enumerate((1500, 16000, 16000)):
+        xy, desc, _, _, F = random_pair(n, 0, seed=600 + k)
+        images.append((xy, desc))
+    m = sfm.Matcher().register(images)
+    small, large = [(0, 0, 4.0)], [(1, 2, 2.5)]
+    binned = dict(recheck_margin_px=BINNED_MARGIN)
+
+    def tuned(pairs):
+        sfm.sfm_autotune(m.ctx, pairs, [F], repeats=1)
+        slots = sfm.sfm_last_stats(m.ctx)["slots"]
+        sfm.sfm_set_tuning(m.ctx, 8, 16)   # (the winner is any of the six)
+        return slots
+
+    assert goes_direct(sfm, m, small, [F])
+    got = tuned(small)
+    want = slots_of(sfm, m, small, [F], **binned)[1]
+    assert got % 256 == 0 and abs(got - want) < 0.05 * want
+    # Groups of eight stream more than one buffer here, and round ranges to
+    # sixteen instead of four positions.  A call keeps them where the larger table
+    # of groups of four does not fit its workspace.
+    got = tuned(large)
+    fours = slots_of(sfm, m, large, [F], **binned)[1]
+    tight = sfm.Matcher(workspace_budget_bytes=sfm.sfm_workspace_size(m.ctx, large)).register(images)
+    sfm.sfm_set_tuning(tight.ctx, 8, 16)
+    eights = slots_of(sfm, tight, large, [F], **binned)[1]
+    assert eights > 1.01 * fours and abs(got - eights) < 0.005 * eights, (fours, eights, got)
+    m.close()
+    tight.close()
