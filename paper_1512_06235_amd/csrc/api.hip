@@ -36,7 +36,10 @@ struct sfm_ctx {
   // Registered images.
   int32_t n_images = 0;
   std::vector<int32_t> n_host;
-  std::vector<float> bbox_host;        // 4 per image: min x, min y, max x, max y
+  struct Extent {                      // of an image's keypoints, as ImageDev has them
+    float bbox[4], crowd[4][2];
+  };
+  std::vector<Extent> extent;
   ImageDev* images_dev = nullptr;      // the image table, and in the same allocation
                                        // everything its entries own
 
@@ -516,9 +519,11 @@ void binning_order(const PairDesc* pd, int32_t n_pairs, int32_t* ord) {
 
 // True when the epipole of b lies in or near b's keypoint box bb, where the
 // binned form scans all of b (setup_pair in kernels_prep.hip; only speed depends
-// on this).  half: half the band's width.
-bool epipole_near_box(const double* F, const float* bb, double half) {
+// on this).  half: half the band's width.  Otherwise *dir is the direction of the
+// lines at the box's centre.
+bool epipole_near_box(const double* F, const float* bb, double half, LineDirection* dir) {
   double best = 0.0, e[3] = {0.0, 0.0, 0.0};
+  *dir = kAlongX;
   for (int p = 0; p < 3; ++p) {   // the best-conditioned pair of columns
     const int i = p == 2 ? 1 : 0, j = p == 0 ? 1 : 2;
     const double x = F[3 + i] * F[6 + j] - F[6 + i] * F[3 + j];
@@ -533,49 +538,86 @@ bool epipole_near_box(const double* F, const float* bb, double half) {
     }
   }
   if (!(best > 0.0)) return true;
-  if (std::fabs(e[2]) <= 1e-12 * std::hypot(e[0], e[1])) return false;
-  const double ex = e[0] / e[2], ey = e[1] / e[2];
-  const double ux = 0.5 * (double(bb[0]) + bb[2]) - ex, uy = 0.5 * (double(bb[1]) + bb[3]) - ey;
-  const double un = std::hypot(ux, uy);
-  double vmin = INFINITY;
-  for (int c = 0; c < 4; ++c)
-    vmin = std::min(vmin, ((bb[(c & 1) * 2] - ex) * ux + (bb[(c >> 1) * 2 + 1] - ey) * uy) / un);
-  return !(vmin > std::max(1.0, 4.0 * half));
+  double ux = e[0], uy = e[1];
+  if (!(std::fabs(e[2]) <= 1e-12 * std::hypot(e[0], e[1]))) {
+    const double ex = e[0] / e[2], ey = e[1] / e[2];
+    ux = 0.5 * (double(bb[0]) + bb[2]) - ex;
+    uy = 0.5 * (double(bb[1]) + bb[3]) - ey;
+    const double un = std::hypot(ux, uy);
+    double vmin = INFINITY;
+    for (int c = 0; c < 4; ++c)
+      vmin = std::min(vmin, ((bb[(c & 1) * 2] - ex) * ux + (bb[(c >> 1) * 2 + 1] - ey) * uy) / un);
+    if (!(vmin > std::max(1.0, 4.0 * half))) return true;
+  }
+  const double x = std::fabs(ux) * (double(bb[3]) - bb[1]), y = std::fabs(uy) * (double(bb[2]) - bb[0]);
+  constexpr double kOctant = 0.41421356;   // tan(22.5 degrees)
+  if (!(y > kOctant * x))
+    *dir = kAlongX;
+  else if (x < kOctant * y)
+    *dir = kAlongY;
+  else
+    *dir = (ux > 0.0) == (uy > 0.0) ? kDiagonal : kAntidiagonal;
+  return false;
 }
 
 // Whether pairs [0, n) of pd, with matrices F, are matched directly
 // (kernels_direct.hip) or binned, by estimates in microseconds fitted to both
-// forms on 48 calls: 1 pair of 300 to 32,000 features (band 2, 4 and 8 px), 2 to
-// 200 pairs of 300 to 20,000, epipoles inside the image.  (Direct against
-// binned: a pair of 300 features 23 / 42 us, 2,000: 27 / 46, 8,000: 45 / 55,
-// 12,000: 58 / 62, 16,000: 78 / 71, 24,000: 134 / 82; 12,000 with an 8 px band
-// 77 / 68; 8 pairs of 2,000: 35 / 46, 37 of 500: 31 / 48, 30 of 3,000: 96 / 56;
-// epipole inside the image, 7,000: 44 / 260.)
+// forms on 53 calls of evenly spread features (1 pair of 300 to 30,000, bands of
+// 2, 4 and 8 px, epipoles inside the image; 6 to 800 pairs of 300 to 6,000) and 72
+// of crowded ones (500 to 12,000 of them, 30 to 100% in a strip or around a
+// point).
+//   Direct: the launches, and the work of all queries beside the chain of reads of
+// the query with the most candidates.  Binned: the launches, more with every pair
+// (less from 129 on, which are binned by other workgroups), the largest side's
+// binning, the chain of steps of a crowded tile, all slots; and, where a tile's
+// FP64 decisions outgrow their queue, the tile once more.
+//   (Direct against binned: a pair of 300 features 24 / 41 us, 2,000: 27 / 44,
+// 8,000: 45 / 50, 12,000: 58 / 58, 16,000: 75 / 63; 14,000 with a 2 px band 56 /
+// 55, 10,000 with 8 px 68 / 58; 8 pairs of 2,000: 35 / 46, 60 of 600: 38 / 45, 100
+// of 300: 41 / 51, 300 of 300: 77 / 65, 37 of 2,000: 69 / 49; epipole inside the
+// image, 7,001: 43 / 157.  12,000 features in a strip of 100 px along the lines:
+// 196 / 87, of 20 px: 804 / 1,650; 8,000, four fifths within 20 px: 117 / 69.)
 bool direct_pays(const sfm_ctx* ctx, const PairDesc* pd, const double* F, int32_t n,
                  double margin) {
   // The binned form counts borderline slots within its windows, which are
   // kBandSlackPx wider than the band.
   if (margin > 0.5 * kBandSlackPx) return false;
-  double cost = 0.0, binned = 41.0 + 0.1 * n, side = 0.0;
+  double work = 0.0, reads = 0.0, side = 0.0, steps = 0.0;
+  double binned = 40.0 + (n <= 128 ? 0.1 * n : 4.0 + 0.058 * n);
   for (int32_t k = 0; k < n; ++k) {
     const PairDesc& P = pd[k];
     if (P.nb > kDirectMaxTargets) return false;
-    const float* bb = &ctx->bbox_host[4 * size_t(P.b)];
-    const double w = std::max(1.0, double(bb[2]) - double(bb[0]));
-    const double h = std::max(1.0, double(bb[3]) - double(bb[1]));
-    // The share of b's features in a band as long as the box is wide or high,
-    // and the boxes it crosses.
-    const double share = std::min(1.0, 2.0 * P.band * std::max(w, h) / (w * h));
-    const double boxes = double(P.nb) / kBoxFeatures;
+    if (P.na == 0) continue;
+    const double na = P.na, nb = P.nb;
+    const sfm_ctx::Extent& X = ctx->extent[size_t(P.b)];
+    const double w = std::max(1.0, double(X.bbox[2]) - double(X.bbox[0]));
+    const double h = std::max(1.0, double(X.bbox[3]) - double(X.bbox[1]));
+    LineDirection dir;
+    const bool inside = epipole_near_box(F + 9 * size_t(k), X.bbox, P.band + kBandSlackPx, &dir);
+    const double across = inside           ? std::min(w, h)
+                          : dir == kAlongX ? h
+                          : dir == kAlongY ? w
+                                           : 2.0 * w * h / std::hypot(w, h);
+    const auto crowd = [&](int i) -> double {
+      return inside ? std::max(X.crowd[kAlongX][i], X.crowd[kAlongY][i]) : X.crowd[dir][i];
+    };
+    // Candidates of a query, of the query with the most, and the boxes a line
+    // crosses.
+    const double even = 2.0 * P.band / across;
+    const double share = std::min(1.0, even * crowd(0));
+    const double own = nb * share, peak = nb * std::min(1.0, even * crowd(1));
+    const double boxes = nb / kBoxFeatures;
     const double hit = std::min(boxes, 2.0 * std::sqrt(boxes) + share * boxes);
-    cost += double(P.na) * (60.0 + 3.0 * hit + 1.5 * share * double(P.nb));
-    side = std::max(side, double(std::max(P.na, P.nb)));
-    binned += 1e-4 * P.na;
-    if (!(P.band < 1e30) || epipole_near_box(F + 9 * size_t(k), bb, P.band + kBandSlackPx))
-      binned += 3e-6 * double(P.na) * double(P.nb);
-    if (21.0 + 7.5e-6 * cost > 400.0 + binned) return false;   // large batches end here soon
+    work += na * (4.5e-4 + 7e-6 * hit + 9e-6 * own);
+    reads = std::max(reads, 0.051 * peak + 0.098 * hit + 0.004 * hit * hit);
+    side = std::max(side, 1e-3 * std::max(na, nb));
+    binned += 1.2e-6 * na * own;
+    if (inside || !(P.band < 1e30)) binned += 2e-6 * na * nb;
+    const bool again = 2.0 * kQueryTile * margin * peak > 20.0 * P.band;
+    steps = std::max(steps, 0.015 * (own + peak) + (again ? 0.3 * own : 0.0));
+    if (work > 400.0 + binned + steps) return false;   // large batches end here soon
   }
-  return 21.0 + 7.5e-6 * cost < binned + 1.8e-3 * side;
+  return 21.0 + 0.014 * n + std::hypot(work, reads) < binned + side + steps;
 }
 
 // The sizes the exhaustive kernels take; pair k of the caller's is pd[step k].
@@ -1013,7 +1055,7 @@ static void free_registration(sfm_ctx* ctx) {
   ctx->images_dev = nullptr;
   ctx->n_images = 0;
   ctx->n_host.clear();
-  ctx->bbox_host.clear();
+  ctx->extent.clear();
 }
 
 int sfm_destroy(sfm_ctx* ctx) {
@@ -1107,10 +1149,13 @@ int sfm_register_images(sfm_ctx* ctx, const sfm_image* images, int32_t n_images)
   memcpy(host.data(), table.data(), o_bad);
   ctx->n_images = n_images;
   ctx->n_host.resize(size_t(n_images));
-  ctx->bbox_host.resize(4 * size_t(n_images));
+  ctx->extent.resize(size_t(n_images));
   for (int32_t k = 0; k < n_images; ++k) {
+    const ImageDev& d = host[size_t(k)];
+    sfm_ctx::Extent& x = ctx->extent[size_t(k)];
     ctx->n_host[size_t(k)] = images[k].n;
-    for (int c = 0; c < 4; ++c) ctx->bbox_host[4 * size_t(k) + size_t(c)] = host[size_t(k)].bbox[c];
+    memcpy(x.bbox, d.bbox, sizeof x.bbox);
+    memcpy(x.crowd, d.crowd, sizeof x.crowd);
   }
   return SFM_OK;
 }
@@ -1208,7 +1253,7 @@ int sfm_grid_match(sfm_ctx* ctx, const sfm_pair* pairs, int32_t n_pairs, const d
       return fail(ctx, SFM_ECAPACITY, buf);
     }
     g.d = s.band_px;
-    for (int c = 0; c < 4; ++c) g.box[c] = double(ctx->bbox_host[4 * size_t(s.b) + size_t(c)]);
+    for (int c = 0; c < 4; ++c) g.box[c] = double(ctx->extent[size_t(s.b)].bbox[c]);
     g.q_off = sum_na;
     g.item_off = items;
     const double two_d = 2.0 * g.d;

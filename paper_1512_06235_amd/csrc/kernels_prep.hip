@@ -77,16 +77,18 @@ __global__ __launch_bounds__(256) void register_kernel(ImageDev* imgs, int32_t* 
 
 // ---------------------------------------------------------------------------
 // Registration: the features of an image in spatial order, for the direct form
-// of guided matching.  One workgroup per image sorts them by the Hilbert index
-// of their cell of a 64 x 64 grid over the keypoint box (counting sort; the
-// order within a cell is arbitrary, nothing depends on it), then writes the
-// bounding boxes.  40,000 features take about
-// 40 us, once per image.
+// of guided matching, and how crowded they are, for the choice of that form.
+// One workgroup per image sorts them by the Hilbert index of their cell of a
+// 64 x 64 grid over the keypoint box (counting sort; the order within a cell is
+// arbitrary, nothing depends on it), then writes the bounding boxes.  40,000
+// features take about 40 us, once per image.
 // ---------------------------------------------------------------------------
 constexpr int kOrderThreads = 1024;
 constexpr int kHilbertBits = 6;
 constexpr int kOrderBins = 1 << (2 * kHilbertBits);
 static_assert(kOrderBins == 4 * kOrderThreads, "four bins per thread in the scan");
+constexpr int kStrips = 1 << kHilbertBits;
+static_assert(kStrips == 64, "a lane per strip");
 
 __device__ __forceinline__ uint32_t hilbert(uint32_t x, uint32_t y) {
   uint32_t d = 0;
@@ -113,9 +115,27 @@ __device__ __forceinline__ uint32_t hilbert(uint32_t x, uint32_t y) {
   return d;
 }
 
-__global__ __launch_bounds__(kOrderThreads) void order_kernel(const ImageDev* imgs) {
+// ImageDev's crowd of one direction: c is this lane's strip's features, of n.
+__device__ __forceinline__ void crowding(int32_t c, int32_t n, float* to) {
+  float sq = float(c) * float(c);
+  int32_t most = c;
+  for (int o = 32; o > 0; o >>= 1) {
+    sq += __shfl_xor(sq, o, 64);
+    most = max(most, __shfl_xor(most, o, 64));
+  }
+  // Less what the scatter of counts adds by itself.
+  const float f = float(n), even = f / kStrips;
+  const float own = fmaxf(1.0f, (sq - f) / (f * even));
+  if ((threadIdx.x & 63) == 0) {
+    to[0] = own;
+    to[1] = fmaxf(own, (float(most) - 2.0f * sqrtf(float(most))) / even);
+  }
+}
+
+__global__ __launch_bounds__(kOrderThreads) void order_kernel(ImageDev* imgs) {
   __shared__ int32_t cnt[kOrderBins];
   __shared__ int32_t wsum[kOrderThreads / 64];
+  __shared__ int32_t strips[4][kStrips];   // by LineDirection
   const ImageDev im = imgs[blockIdx.x];
   if (im.n == 0) return;
   const int t = threadIdx.x, lane = t & 63, wave = t >> 6;
@@ -134,9 +154,20 @@ __global__ __launch_bounds__(kOrderThreads) void order_kernel(const ImageDev* im
                    uint32_t(fminf(fmaxf((p.y - y0) * ky, 0.0f), kTop)));
   };
   for (int c = t; c < kOrderBins; c += kOrderThreads) cnt[c] = 0;
+  if (t < 4 * kStrips) strips[t / kStrips][t % kStrips] = 0;
   __syncthreads();
   for (int32_t j = t; j < im.n; j += kOrderThreads) atomicAdd(&cnt[bin(j)], 1);
   __syncthreads();
+  // The strips' features from the cells': four cells a thread.
+  for (uint32_t k = 0; k < 4; ++k) {
+    const uint32_t x = 4 * (t & 15) + k, y = uint32_t(t) >> 4;
+    const int32_t c = cnt[hilbert(x, y)];
+    if (!c) continue;
+    atomicAdd(&strips[kAlongX][y], c);
+    atomicAdd(&strips[kAlongY][x], c);
+    atomicAdd(&strips[kDiagonal][(x + kStrips - 1 - y) / 2], c);
+    atomicAdd(&strips[kAntidiagonal][(x + y) / 2], c);
+  }
   int32_t own[4], sum = 0;
 #pragma unroll
   for (int k = 0; k < 4; ++k) {
@@ -150,6 +181,7 @@ __global__ __launch_bounds__(kOrderThreads) void order_kernel(const ImageDev* im
   }
   if (lane == 63) wsum[wave] = inc;
   __syncthreads();
+  if (wave < 4) crowding(strips[wave][lane], im.n, imgs[blockIdx.x].crowd[wave]);
   int32_t run = inc - sum;
   for (int k = 0; k < wave; ++k) run += wsum[k];
 #pragma unroll

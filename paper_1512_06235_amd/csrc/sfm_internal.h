@@ -65,7 +65,15 @@ struct ImageDev {
   int32_t n;
   int32_t pad;
   float bbox[4];            // min x, min y, max x, max y of the keypoints
+  // How crowded the keypoints are across lines of each LineDirection: over 64
+  // strips along such lines, the features of a keypoint's own strip and of the
+  // fullest one, in 64ths of all of them (at least 1).
+  float crowd[4][2];
 };
+
+// Of lines in an image's keypoint box scaled to a square: along x, along y, and
+// along its two diagonals (x and y grow together, or not).
+enum LineDirection : int32_t { kAlongX, kAlongY, kDiagonal, kAntidiagonal };
 
 // Per pair, filled on the host: sizes and workspace offsets.
 struct PairDesc {

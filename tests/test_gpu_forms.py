@@ -105,3 +105,46 @@ def test_autotuner_times_its_settings(sfm):
     assert eights > 1.01 * fours and abs(got - eights) < 0.005 * eights, (fours, eights, got)
     m.close()
     tight.close()
+
+
+def _strip(n, along, width, seed):
+    """Keypoints in a strip of a 1,024 x 768 image, along its middle or a diagonal."""
+    rng = np.random.default_rng(seed)
+    _, desc, _, _, _ = random_pair(n, 0, seed=seed)
+    u, v = rng.uniform(0, 768, n), rng.uniform(-width / 2, width / 2, n)
+    xy = {"x": np.stack([u * 4 / 3, 384 + v], 1), "y": np.stack([512 + v, u], 1),
+          "diagonal": np.stack([u * 4 / 3 + v, u], 1),
+          "antidiagonal": np.stack([1023 - u * 4 / 3 + v, u], 1)}[along]
+    xy = np.clip(xy, 0, [1023, 767])
+    xy[:4] = [[0, 0], [1023, 0], [0, 767], [1023, 767]]
+    return xy.astype(np.float32), desc
+
+
+LINES = {"x": (1.0, 0.0, 0.0), "y": (0.0, 1.0, 0.0), "diagonal": (4.0, 3.0, 0.0),
+         "antidiagonal": (4.0, -3.0, 0.0)}
+
+
+@pytest.mark.parametrize("along", list(LINES))
+def test_crowded_keypoints_are_binned(sfm, along):
+    """10,000 features in a strip of 60 px: lines along it have ten times the
+    candidates of an even spread's, where the direct form takes twice the binned
+    one's time, lines across it no more than an even spread's."""
+    from tests.fixtures import translation_F
+    across = {"x": "y", "y": "x", "diagonal": "antidiagonal", "antidiagonal": "diagonal"}[along]
+    m = sfm.Matcher().register([_strip(10000, along, 60.0, s) for s in (1, 2)])
+    pairs = [(0, 1, 4.0)]
+    assert not goes_direct(sfm, m, pairs, [translation_F(LINES[along])])
+    assert goes_direct(sfm, m, pairs, [translation_F(LINES[across])])
+    m.close()
+
+
+@pytest.mark.parametrize("n, band, direct", [(300, 4.0, True), (8000, 2.0, True), (6000, 8.0, True),
+                                             (16000, 2.0, False), (16000, 8.0, False)])
+def test_form_of_a_pair(sfm, n, band, direct):
+    """A pair of evenly spread features, well to either side of where the two
+    forms take as long."""
+    images = [random_pair(n, 0, seed=700 + k)[:2] for k in range(2)]
+    F = random_pair(1, 1, seed=1)[4]
+    m = sfm.Matcher().register(images)
+    assert goes_direct(sfm, m, [(0, 1, band)], [F]) == direct
+    m.close()
