@@ -34,8 +34,9 @@
  * Memory.  All image, descriptor and output buffers are device memory owned
  * by the caller.  Pair lists and fundamental matrices are host memory, read
  * before the call returns.  The library owns only its context: the table of
- * registered images, per-feature squared norms and a workspace it grows on
- * demand up to the budget given to sfm_create().
+ * registered images with what registration computes of them (8 bytes per
+ * feature, and 13 more in images of at most 65,536 features), and a workspace it
+ * grows on demand up to the budget given to sfm_create().
  *
  * Around the matcher, the library also selects the image pairs to match
  * from the coarse model's point-camera visibility (Section 6.1,
@@ -136,7 +137,9 @@ int sfm_destroy(sfm_ctx* ctx);
 
 /* Register the images that pairs refer to by index (replaces any previous
  * set).  Checks that every descriptor byte is <= 127 (SFM_EINVAL otherwise),
- * precomputes squared norms and keypoint bounding boxes.  Blocks until done.
+ * precomputes squared norms, the exhaustive matcher's constant terms, keypoint
+ * bounding boxes and, for images of at most 65,536 features, the features in
+ * spatial order.  Blocks until done.
  * The caller's buffers must stay valid while the registration is in use. */
 int sfm_register_images(sfm_ctx* ctx, const sfm_image* images, int32_t n_images);
 

@@ -1087,7 +1087,10 @@ int sfm_register_images(sfm_ctx* ctx, const sfm_image* images, int32_t n_images)
   if (ctx->has_work) HIP_TRY(ctx, hipEventSynchronize(ctx->work_done));
   free_registration(ctx);
   std::vector<ImageDev> host(static_cast<size_t>(n_images));
-  size_t total = 0, outers = 0;   // features, outer boxes of whole images
+  size_t total = 0, outers = 0;   // features, outer boxes of the spatial orders
+  const auto outer_boxes = [](int32_t n) -> size_t {
+    return n > kDirectMaxTargets ? 0 : (size_t(n) + kOuterFeatures - 1) / kOuterFeatures;
+  };
   for (int32_t k = 0; k < n_images; ++k) {
     const sfm_image& s = images[k];
     if (s.n < 0 || (s.n > 0 && (!s.xy || !s.desc))) {
@@ -1096,7 +1099,7 @@ int sfm_register_images(sfm_ctx* ctx, const sfm_image* images, int32_t n_images)
       return fail(ctx, SFM_EINVAL, buf);
     }
     total += size_t(s.n);
-    outers += (size_t(s.n) + kOuterFeatures - 1) / kOuterFeatures;
+    outers += outer_boxes(s.n);
   }
   if (n_images == 0) return SFM_OK;
   // One allocation: the table and the flag of bad input, squared norms and
@@ -1123,13 +1126,15 @@ int sfm_register_images(sfm_ctx* ctx, const sfm_image* images, int32_t n_images)
     d.desc = images[k].desc;
     d.norm2 = reinterpret_cast<int32_t*>(base + o_norm2) + at;
     d.cword = reinterpret_cast<int32_t*>(base + o_cword) + at;
-    d.outer = reinterpret_cast<float4*>(base + o_outer) + ob;
-    d.box = reinterpret_cast<float4*>(base + o_box) + ob * kOuterBoxes;
-    d.sxy = reinterpret_cast<float2*>(base + o_sxy) + ob * kOuterFeatures;
-    d.sj = reinterpret_cast<int32_t*>(base + o_sj) + ob * kOuterFeatures;
     d.n = images[k].n;
     at += size_t(d.n);
-    ob += (size_t(d.n) + kOuterFeatures - 1) / kOuterFeatures;
+    if (const size_t boxes = outer_boxes(d.n)) {
+      d.outer = reinterpret_cast<float4*>(base + o_outer) + ob;
+      d.box = reinterpret_cast<float4*>(base + o_box) + ob * kOuterBoxes;
+      d.sxy = reinterpret_cast<float2*>(base + o_sxy) + ob * kOuterFeatures;
+      d.sj = reinterpret_cast<int32_t*>(base + o_sj) + ob * kOuterFeatures;
+      ob += boxes;
+    }
   }
   memcpy(table.data(), host.data(), o_bad);
   hipError_t e = hipMemcpy(base, table.data(), table.size(), hipMemcpyHostToDevice);

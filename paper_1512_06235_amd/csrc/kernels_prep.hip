@@ -137,7 +137,7 @@ __global__ __launch_bounds__(kOrderThreads) void order_kernel(ImageDev* imgs) {
   __shared__ int32_t wsum[kOrderThreads / 64];
   __shared__ int32_t strips[4][kStrips];   // by LineDirection
   const ImageDev im = imgs[blockIdx.x];
-  if (im.n == 0) return;
+  if (im.n == 0 || im.n > kDirectMaxTargets) return;   // no order is kept
   const int t = threadIdx.x, lane = t & 63, wave = t >> 6;
   float2* sxy = const_cast<float2*>(im.sxy);
   int32_t* sj = const_cast<int32_t*>(im.sj);

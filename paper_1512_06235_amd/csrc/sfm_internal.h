@@ -57,7 +57,8 @@ struct ImageDev {
   const int32_t* cword;     // int32[n], owned by the context: norm2 - 127 * (sum of the bytes) + 2^21
   // The features in spatial order (order_kernel), padded to whole outer boxes,
   // owned by the context: coordinates on the image box's centre, original
-  // indices, and the centres and half extents of the boxes and outer boxes.
+  // indices, and the centres and half extents of the boxes and outer boxes.  NULL
+  // for images of more than kDirectMaxTargets features.
   const float2* sxy;
   const int32_t* sj;
   const float4* box;
@@ -67,7 +68,7 @@ struct ImageDev {
   float bbox[4];            // min x, min y, max x, max y of the keypoints
   // How crowded the keypoints are across lines of each LineDirection: over 64
   // strips along such lines, the features of a keypoint's own strip and of the
-  // fullest one, in 64ths of all of them (at least 1).
+  // fullest one, in 64ths of all of them (at least 1).  0 without a spatial order.
   float crowd[4][2];
 };
 

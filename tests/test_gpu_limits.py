@@ -94,3 +94,35 @@ def test_product_that_does_not_fit_leaves_it_to_the_histogram(sfm):
     m = sfm.Matcher(workspace_budget_bytes=4 * n * (32 + n) + (1 << 20))
     _check(sfm, m, _lists(n, npts, 30, 5), npts, 2, 9)
     m.close()
+
+
+def test_registration_keeps_no_order_of_large_images(sfm):
+    """The spatial order (13 bytes a feature and padding) is for images of at most
+    65,536 features; larger ones keep the two words per feature that matching
+    reads.  Matching at either side of the size equals the exhaustive form on an
+    unbounded band."""
+    import torch
+    gen = torch.Generator(device="cuda").manual_seed(1)
+
+    def image(n):
+        xy = torch.rand(n, 2, device="cuda", generator=gen) * 1000
+        return xy, torch.randint(0, 128, (n, 128), dtype=torch.uint8, device="cuda", generator=gen)
+
+    large = [image(400_000) for _ in range(4)]
+    torch.cuda.synchronize()
+    m = sfm.Matcher().register([image(40)])   # (kernels are loaded)
+    torch.cuda.synchronize()
+    free = torch.cuda.mem_get_info()[0]
+    m.register(large)
+    took = free - torch.cuda.mem_get_info()[0]
+    assert 8 * 1_600_000 <= took < 8 * 1_600_000 + (6 << 20), took
+    edge = [image(65536), image(65537), image(40)]
+    m.register(edge)
+    F = random_pair(1, 1, seed=1)[4]
+    pairs = [(2, 0, np.inf), (2, 1, np.inf)]
+    for kw in (dict(), dict(accept_single=True, ratio_num=100)):
+        a = m.match(pairs, [F] * 2, emit_all=True, **kw)
+        b = m.match(pairs, None, form="bruteforce", emit_all=True, **kw)
+        for name in ("offset", "n_comparisons", "all_match", "all_d1", "all_d2", "all_count"):
+            assert torch.equal(getattr(a, name), getattr(b, name)), name
+    m.close()
