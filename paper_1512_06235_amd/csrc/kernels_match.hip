@@ -71,13 +71,18 @@ static_assert(kQueryTile == kBlock, "one MFMA column block of queries per tile")
 static_assert(kBuf <= kChunk, "a tile's steps in one fill fit one key chunk");
 constexpr uint32_t kKeyDistInf = kKeyInf >> kPosBits;
 
-// nv - 2048 dot in one instruction (v_mad_i32_i24; |dot| <= 128 * 127^2 < 2^23
-// and the result wraps like the 32-bit expression): the key of a candidate.
-// `m2048` is -2048 behind an asm statement, or it would become a shift and a
-// subtraction.
-__device__ __forceinline__ uint32_t key_of(uint32_t nv, int32_t dot, int32_t m2048) {
-  return nv + uint32_t(((dot << 8) >> 8) * ((m2048 << 8) >> 8));
+// nv - 2048 dot modulo 2^32 in one instruction (v_mad_i32_i24; |dot| <=
+// 128 * 127^2 < 2^23): the key of a candidate.  `m2048` is -2048 behind an asm
+// statement, or it would become a shift and a subtraction.
+__host__ __device__ __forceinline__ constexpr uint32_t key_of(uint32_t nv, int32_t dot,
+                                                              int32_t m2048) {
+  const int32_t a = int32_t(uint32_t(dot) << 8) >> 8, b = int32_t(uint32_t(m2048) << 8) >> 8;
+  return nv + uint32_t(a) * uint32_t(b);   // (as signed numbers the product overflows)
 }
+static_assert(key_of(0xFFFFFC00u, kDescBytes * 127 * 127, -2048) ==
+                  uint32_t(0xFFFFFC00ull - 2048ull * kDescBytes * 127 * 127) &&
+              key_of(5u, 0, -2048) == 5u,
+              "keys of the largest products");
 
 // The middle and the smallest of three as one instruction each (of the
 // expressions the compiler splits some into two).
