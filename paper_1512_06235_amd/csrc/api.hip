@@ -110,15 +110,17 @@ int hip_fail(sfm_ctx* ctx, hipError_t e, const char* what) {
     if (_e != hipSuccess) return hip_fail((ctx), _e, #expr); \
   } while (0)
 
-// Sections of one call's workspace.
+// Sections of one call's workspace (0: not used).
 struct Layout {
-  size_t pairs, F, order, items, geom, counters, wg_start, cand_x, cand_y, cand_nc, cand_j, bins,
-      qrec, res, twin, groups, gcost, pcost, part, total, staged;
+  size_t pairs = 0, F = 0, order = 0, items = 0, geom = 0, counters = 0, wg_start = 0, cand_x = 0,
+         cand_y = 0, cand_nc = 0, cand_j = 0, bins = 0, qrec = 0, res = 0, twin = 0, groups = 0,
+         gcost = 0, pcost = 0, part = 0, total = 0, staged = 0;
   int32_t wgs = 0;
   int32_t group_tiles = 0;
   int64_t sum_na = 0, sum_nc = 0, sum_bins = 0, sum_blocks = 0, sum_groups = 0;
   int32_t max_na = 0, max_nb = 0, max_sort_ints = 0;
 };
+static_assert(Layout().twin == 0 && Layout().cand_j == 0, "no section is left unset");
 
 int32_t bins_for(int32_t nb, int32_t features_per_bin) {
   return std::max<int32_t>(1, std::min<int32_t>(kMaxBins, nb / features_per_bin));
@@ -152,8 +154,6 @@ Layout plan(const PairDesc* pd, size_t P, int32_t device, int32_t group_tiles,
     L.res = o; o = align_up(o + size_t(L.sum_na) * sizeof(QueryResult));
     L.part = o; o = align_up(o + size_t(n_part) * sizeof(uint2));
     L.total = o;
-    L.F = L.order = L.geom = L.wg_start = L.cand_x = L.cand_y = L.cand_nc = L.cand_j = L.bins =
-        L.qrec = L.groups = L.gcost = L.pcost = 0;   // not used
     return L;
   }
   L.pairs = o; o = align_up(o + P * sizeof(PairDesc));
