@@ -232,7 +232,6 @@ int describe_pairs(sfm_ctx* ctx, const ImageTable& tab, const sfm_pair* pairs, i
     p.blk_off = blk;
     p.grp_off = grp;
     p.band = ignore_band ? INFINITY : s.band_px;
-    p.ignore_band = ignore_band ? 1 : 0;
     q += p.na;
     c += p.nb + kCandPad;
     bo += p.nbins + 1;

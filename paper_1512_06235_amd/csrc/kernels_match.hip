@@ -305,7 +305,7 @@ __device__ __forceinline__ GroupStart<TPW> start_group(const BatchView& v, const
 }
 
 // One query tile of a wave: its query column (one query per lane, four lanes
-// per query), the negated query bytes as the MFMA B operand and the running
+// per query), the query's bytes as the MFMA B operand and the running
 // result.  Distances are kept as key distances (D - ||q||^2 + 2^21, the top
 // 22 bits of a key), so chunks merge without the query's norm.
 struct Tile {

@@ -280,7 +280,7 @@ __device__ void setup_pair(const PairDesc& P, const ImageDev& B, const double* F
   g.mode = kModeFullScan;
   g.ex = g.ey = 0.0; g.ux = 1.0; g.uy = 0.0; g.S = 1.0;
   g.kmin = 0.0; g.kmax = 0.0; g.inv_delta = 0.0;
-  if (P.ignore_band || !(P.band < 1e30) || P.nb == 0 || !(en > 0.0)) return;
+  if (!(P.band < 1e30) || P.nb == 0 || !(en > 0.0)) return;
 
   for (int k = 0; k < 3; ++k) e[k] /= en;
   const double exy = hypot(e[0], e[1]);
@@ -708,34 +708,6 @@ void bin_kernel(BatchView v, int32_t pb, const int32_t* order) {
   const int32_t nh = targets ? g.nbins : g.nbins + 1;
   const ImageDev I = v.images[targets ? P.b : P.a];
 
-  if (P.ignore_band) {
-    // Exhaustive matching keeps b in its own order: one bin, position = index.
-    if (targets) {
-      for (int32_t j = threadIdx.x; j < P.nb + kCandPad; j += blockDim.x) {
-        const bool pad = j >= P.nb;
-        v.cand_x[P.c_off + j] = pad ? NAN : 0.0f;
-        v.cand_y[P.c_off + j] = 0.0f;
-        v.cand_nc[P.c_off + j] =
-            pad ? kKeyInf
-                : ((uint32_t(I.norm2[j]) + kDistBias) << kPosBits) | uint32_t(j & (kChunk - 1));
-        v.cand_j[P.c_off + j] = pad ? 0 : j;
-      }
-      if (threadIdx.x == 0) {
-        v.bin_start[P.bin_off] = 0;
-        for (int k = 1; k <= g.nbins; ++k) v.bin_start[P.bin_off + k] = P.nb;
-      }
-    } else {
-      for (int32_t i = threadIdx.x; i < P.na; i += blockDim.x) {
-        QueryRec r;
-        r.a = 0.0f; r.b = 0.0f; r.c = 0.0f; r.i = i;
-        v.qrec[P.q_off + i] = r;
-      }
-      for (int32_t t = threadIdx.x; t < P.nblocks; t += blockDim.x)
-        v.twin[P.blk_off + t] = make_int2(0, 0);
-    }
-    return;
-  }
-
   for (int k = threadIdx.x; k < nh; k += blockDim.x) hist[k] = 0;
   __syncthreads();
   const int32_t n = targets ? P.nb : P.na;
@@ -773,7 +745,7 @@ __global__ __launch_bounds__(kGatherThreads) void gather_kernel(BatchView v, int
   const bool targets = blockIdx.z != 0;
   const int32_t n = targets ? P.nb : P.na;
   const int32_t base = int32_t(blockIdx.y) * kGatherThreads;
-  if (P.ignore_band || base >= n) return;   // uniform
+  if (base >= n) return;   // uniform
   const PairGeom& g = v.geom[p];
   const int32_t nh = targets ? g.nbins : g.nbins + 1;
   if (!perm_fits(nh, n, lds_ints)) return;   // scattered by bin_kernel itself

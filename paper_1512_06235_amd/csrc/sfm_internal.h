@@ -90,8 +90,8 @@ struct PairDesc {
   int32_t ngroups;          // ceil(nblocks / group tiles)
   int32_t pad2;
   double band;              // d, pixels (may be +inf)
-  int32_t ignore_band;      // exhaustive matching
   int32_t q_shift;          // added to the query indices of emitted rows
+  int32_t pad3;
   int64_t ex_off;           // exhaustive matching: first partial result (prefix of n_a * slices)
 };
 
