@@ -1856,7 +1856,7 @@ int sfm_triangulate(sfm_ctx* ctx, int64_t n_nodes, const int32_t* label, const i
     return fail(ctx, SFM_EINVAL, "a pointer is NULL");
   HIP_TRY(ctx, hipSetDevice(ctx->device));
   hipStream_t st = reinterpret_cast<hipStream_t>(stream);
-  if (n_nodes > scan_limit()) return fail(ctx, SFM_EHIP, "too many nodes");
+  if (n_nodes > kMaxTriangulateNodes) return fail(ctx, SFM_EHIP, "too many nodes");
   int rc = ensure_workspace(ctx, align_up((4 * size_t(n_nodes) + 3) * sizeof(int32_t)));
   if (rc) return rc;
   if (ctx->has_work) HIP_TRY(ctx, hipStreamWaitEvent(st, ctx->work_done, 0));

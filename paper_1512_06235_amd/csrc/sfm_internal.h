@@ -255,7 +255,9 @@ hipError_t launch_scan(const int32_t* in, int32_t* out, int64_t n, bool inclusiv
 // Tracks and triangulation (kernels_tracks.hip).
 hipError_t launch_tracks(int64_t n_nodes, const int32_t* edges, int64_t n_edges, int32_t* label,
                          int32_t* err, hipStream_t st);
-// ws: 4 n_nodes + 3 int32, 8-byte aligned.
+// ws: 4 n_nodes + 3 int32, 8-byte aligned.  (The limit is the call's, no kernel
+// ends there.)
+constexpr int64_t kMaxTriangulateNodes = int64_t(1) << 26;
 hipError_t launch_triangulate(int64_t n_nodes, const int32_t* label, const int32_t* node_image,
                               const float* node_xy, const double* P, int32_t n_images,
                               int32_t* ws, double* X, int32_t* n_obs, int32_t* err,
