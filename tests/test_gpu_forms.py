@@ -148,3 +148,118 @@ def test_form_of_a_pair(sfm, n, band, direct):
     m = sfm.Matcher().register(images)
     assert goes_direct(sfm, m, [(0, 1, band)], [F]) == direct
     m.close()
+
+
+EPIPOLES = {"inside": (300.0, 200.0, 1.0), "at infinity": (1.0, 0.3, 0.0), "vertical": (0.0, 1.0, 0.0),
+            "just outside": (-40.0, 380.0, 1.0), "far": (5e7, 1e3, 1.0)}
+
+
+@pytest.mark.parametrize("form", ["direct", "binned"])
+@pytest.mark.parametrize("epipole", list(EPIPOLES))
+def test_epipoles_in_both_forms(sfm, oracle_lib, epipole, form):
+    from tests.fixtures import translation_F
+    from tests.gpu_util import compare_all
+    xa, da, xb, db, _ = random_pair(1200, 2500, seed=44)
+    images = [(xa, da), (xb, db)]
+    F = translation_F(EPIPOLES[epipole])
+    pairs = [(0, 1, 4.0), (0, 1, 12.0), (1, 0, 2.5)]
+    m = sfm.Matcher().register(images)
+    assert goes_direct(sfm, m, pairs, [F] * 3)
+    kw = dict(recheck_margin_px=BINNED_MARGIN) if form == "binned" else dict()
+    out = m.match(pairs, [F] * 3, emit_all=True, **kw)
+    compare_all(out, oracle_lib.match(images, pairs, [F] * 3), 3)
+    m.close()
+
+
+@pytest.mark.parametrize("form", ["direct", "binned"])
+@pytest.mark.parametrize("na,nb", [(0, 50), (50, 0), (1, 1), (31, 2), (33, 700), (97, 1), (2100, 3000)])
+def test_ragged_and_empty_in_both_forms(sfm, oracle_lib, na, nb, form):
+    from tests.gpu_util import compare_all
+    xa, da, xb, db, F = random_pair(na, nb, seed=na * 7 + nb)
+    images = [(xa, da), (xb, db)]
+    m = sfm.Matcher().register(images)
+    kw = dict(recheck_margin_px=BINNED_MARGIN) if form == "binned" else dict()
+    for band in (4.0, 30.0):
+        pairs, Fs = [(0, 1, band), (1, 0, band)], [F, F.T]
+        if na * nb > 5000 and band < 10.0:
+            assert goes_direct(sfm, m, pairs, Fs)
+        compare_all(m.match(pairs, Fs, emit_all=True, **kw),
+                    oracle_lib.match(images, pairs, Fs), 2)
+    m.close()
+
+
+@pytest.mark.parametrize("nb", [1, 15, 16, 17, 255, 256, 257, 1024, 1025, 4097, 9000])
+def test_direct_sizes_around_boxes(sfm, oracle_lib, nb):
+    """One box, one outer box, sixteen of them, and one feature to either side."""
+    from tests.gpu_util import compare_all
+    images = [(xy, desc // 16) for xy, desc in
+              (random_pair(n, 0, seed=800 + n)[:2] for n in (1, 3, 63, 130, nb))]
+    F = random_pair(1, 1, seed=1)[4]
+    pairs = [(k, 4, d) for k in range(4) for d in (0.0, 3.0)] + [(4, 3, 5.0)]
+    m = sfm.Matcher().register(images)
+    if nb >= 1024:   # (smaller, some opened boxes may happen to be whole steps)
+        assert goes_direct(sfm, m, pairs, [F] * len(pairs))
+    out = m.match(pairs, [F] * len(pairs), emit_all=True)
+    compare_all(out, oracle_lib.match(images, pairs, [F] * len(pairs)), len(pairs))
+    m.close()
+
+
+def test_direct_lists_that_overflow(sfm, oracle_lib):
+    """Features exactly on one line and on one point, finer than the strips that
+    the choice of the form goes by: lanes with more members than they hold, in
+    calls that go direct."""
+    from tests.fixtures import translation_F
+    from tests.gpu_util import compare_all
+    rng = np.random.default_rng(9)
+    xa, da, xb, db, _ = random_pair(200, 3000, seed=8)
+    db[1500:1700] = db[10]
+    xb[:400] = [400.0, 300.0]
+    xb[400:900, 1] = 300.0
+    xa[:80, 1] = 300.0 + rng.uniform(-0.4, 0.4, 80).astype(np.float32)
+    da[:20] = db[10]
+    images = [(xa, da), (xb, db)]
+    F = translation_F((1.0, 0.0, 0.0))
+    m = sfm.Matcher().register(images)
+    for pairs in ([(0, 1, 0.25)], [(0, 1, 0.5), (1, 0, 0.25)]):
+        assert goes_direct(sfm, m, pairs, [F] * len(pairs))
+        out = m.match(pairs, [F] * len(pairs), emit_all=True)
+        assert int(out.all_count.max()) >= 900
+        compare_all(out, oracle_lib.match(images, pairs, [F] * len(pairs)), len(pairs))
+    m.close()
+
+
+def test_replay_of_a_direct_layout(sfm):
+    """A layout that goes direct, captured and replayed with other matrices in
+    between, its outputs overwritten before every call and eager work after it."""
+    import torch
+    images = [random_pair(n, 0, seed=900 + n)[:2] for n in (1500, 1700)]
+    F0 = random_pair(1, 1, seed=1)[4]
+    turns = [np.array([[1, 0, dx], [0, 1, dy], [0, 0, 1.0]]).T @ F0 for dx, dy in
+             ((0, 0), (3, -2), (0, 0), (-7, 5), (11, 4))]
+    pairs = [(0, 1, 4.0), (1, 0, 3.0)]
+    m = sfm.Matcher().register(images)
+    st, opt = torch.cuda.current_stream(), sfm.options(emit_all=True)
+    names = ("offset", "n_comparisons", "n_borderline", "all_match", "all_d1", "all_d2", "all_count")
+    out, want = m.buffers(pairs, emit_all=True), []
+
+    def call(F):
+        for k in names + ("query", "match", "d1", "d2"):
+            getattr(out, k).fill_(-7)
+        sfm.sfm_guided_match(m.ctx, sfm.PairBatch(pairs, [F, F.T]), None, out, opt, st)
+        y = (torch.ones(1 << 16, device="cuda") * 2.0).sum()
+        sfm.sfm_sync(m.ctx, st)
+        assert y.item() == 2.0 * (1 << 16)
+        n = int(out.offset[2])
+        return [getattr(out, k).cpu().numpy().copy() for k in names] + \
+            [getattr(out, k)[:n].cpu().numpy().copy() for k in ("query", "match", "d1", "d2")]
+
+    for F in turns:
+        assert goes_direct(sfm, m, pairs, [F, F.T])
+        want.append(call(F))
+    assert any(not np.array_equal(a, b) for a, b in zip(want[0], want[1]))
+    sfm.sfm_set_graph_replay(m.ctx, True)
+    for rep in range(3):
+        for F, w in zip(turns, want):
+            assert all(np.array_equal(a, b) for a, b in zip(call(F), w)), rep
+    sfm.sfm_set_graph_replay(m.ctx, False)
+    m.close()
