@@ -644,12 +644,12 @@ def main():
     ap.add_argument("--no-stress", action="store_true",
                     help="skip the 20,000-request stress-serving run")
     ap.add_argument("--no-autotune", action="store_true",
-                    help="keep the default tuning (2 tiles per group, 8 features per bin)")
+                    help="keep the default tuning (8 tiles per group, 8 features per bin)")
     ap.add_argument("--tune-cache", default=os.path.join(ROOT, "paper_1512_06235_amd",
                                                          "tune_cache.json"),
                     help="tuning cache file (read, and written when the batch's key is new)")
     ap.add_argument("--tuning", default=None, metavar="TILESxFEATURES",
-                    help="use this tuning instead of autotuning, e.g. 2x4")
+                    help="use this tuning instead of autotuning, e.g. 8x4")
     ap.add_argument("--serving-seconds", type=float, default=20.0)
     ap.add_argument("--serving-rates", default="200,1000,5000",
                     help="offered pair requests per second, comma-separated")

@@ -253,9 +253,9 @@ int describe_pairs(sfm_ctx* ctx, const ImageTable& tab, const sfm_pair* pairs, i
 // (the whole call, or with `per_pair` each pair) all run at once, the pairs are
 // cut into groups of four instead, if the larger group table fits in `limit`
 // bytes: twice the workgroups, and half the work of the longest.  (Groups of
-// eight against four: a pair of 16,000, 125 groups, 79 / 72 us; 6 pairs of
-// 2,000 to 20,000, 224: 82 / 71; 20 pairs, 875: 100 / 91; 100 pairs of 1,000 to
-// 2,000, 1,148: 75 / 78; 120 pairs, 6,874: 206 / 208.)
+// eight against four: a pair of 16,000, 125 groups, 67 / 63 us; 6 pairs of 2,000
+// to 20,000, 224: 74 / 63; 20 pairs, 875: 89 / 81; 100 pairs of 1,000 to 2,000,
+// 1,148: 62 / 63; 30 pairs, 1,912: 96 / 99; 60 pairs, 3,650: 131 / 140.)
 Layout plan_guided(const sfm_ctx* ctx, PairDesc* pd, size_t P, bool per_pair, size_t limit) {
   auto cut = [&](int32_t tiles) {
     int64_t grp = 0;

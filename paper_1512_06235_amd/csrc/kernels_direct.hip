@@ -22,12 +22,12 @@
 // every candidate row among 16 to 128 queries where here each query reads its
 // own (direct_pays in api.hip).
 //
-// Measured: a pair of 2,000 features 12.5 us (the call 27 against 53 us), of
-// 16,000 features 61 us (80 against 89), of 7,001 with the epipole in the image
-// 29 us (43 against 438).  Bound by the VALU and by chains of L2 reads; of the
-// 61 us the box tests take 22, the opened boxes 14, the distances 20.  A wave
-// per query, with boxes of 64 features and scalar bookkeeping, took 62 us there
-// and 130 instead of 75 on 37 pairs of 301 to 6,007 features.
+// Measured: a pair of 2,000 features 12.5 us (the call 27, binned 44), of 7,001
+// with the epipole in the image 28 us (43 and 157), of 16,000 61 us (75 and 63:
+// such a pair is binned).  Bound by the VALU and by chains of L2 reads; of the 61
+// us the box tests take 22, the opened boxes 14, the distances 20.  A wave per
+// query, with boxes of 64 features and scalar bookkeeping, took 62 us there and
+// 130 instead of 75 on 37 pairs of 301 to 6,007 features.
 #include <algorithm>
 #include <cmath>
 

@@ -359,7 +359,7 @@ void exhaustive_kernel(BatchView v, ExStage stage, const int2* items, int32_t n_
 // query's result is asked for: the second distance could only get smaller.
 // (The four read each of the four rows together: a lane that reads a row of its
 // own asks for every line eight times, 45 us for a staged launch's 1.4 M
-// queries, 28.5 now.  The rest is its chain of reads.)
+// queries, 28.5 so.  The rest is its chain of reads.)
 constexpr int kMergeThreads = 256;
 constexpr int kMergeBatch = 8;
 

@@ -505,8 +505,10 @@ __device__ __forceinline__ void close_chunk(Tile& T, int32_t c0p, int32_t c1p) {
 // and a workgroup whose counter has run out looks at all of them.  (The oldest
 // wave of a SIMD issues first, so of four workgroups on a CU with as many groups
 // each, the first was done at 58% of the kernel's time, and the last ran alone:
-// 500 pairs 581 us, 541 now; 569 with one counter per share, whose draws wait
-// for each other.)
+// 500 pairs 581 us, 541 with the counters; 569 with one counter per share, whose
+// draws wait for each other.)  Without counters (the table holds them from 1,008
+// resident workgroups on, so a partition of the GPU has none) every workgroup
+// takes each W-th group of its share.
 struct Deal {
   int32_t shares;
   int32_t own;             // this workgroup's counter

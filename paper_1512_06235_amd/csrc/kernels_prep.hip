@@ -676,8 +676,10 @@ __device__ __forceinline__ void sort_side(const BatchView& v, const PairDesc& P,
 // 64 KB (two workgroups of 512 threads per CU) hold about 26,000 items at eight
 // per bin; a batch with a larger side takes 128 KB and 1,024 threads, one
 // workgroup per CU, up to 52,000: scattered records of 8 and 16 bytes cost more
-// than the second workgroup hides (200 pairs of 8,000 to 40,000: 277 us with
-// 64 KB, 150 with 128; 500 pairs of 2,000 to 20,000, which fit: 94 and 108).
+// than the second workgroup hides, from the first large side on, which then ends
+// last (200 pairs of 8,000 to 40,000: 277 us with 64 KB, 150 with 128; 500 pairs
+// of 2,000 to 20,000, which fit: 94 and 108; the same with one side of 30,000
+// among the thousand, the whole preparation: 144 and 119, with twelve 169 and 123).
 constexpr int kBinLdsInts = 16384;
 constexpr int kBinLdsIntsLarge = 32768;
 constexpr int kBinWsumMax = kBinThreadsFew / 64;
@@ -769,10 +771,9 @@ __global__ __launch_bounds__(kGatherThreads) void gather_kernel(BatchView v, int
 // Candidate range of every query tile (its bin window mapped through b's
 // bin starts) and of every group of K consecutive tiles, with the group
 // record and its schedule cost.  Block (p, c) takes tiles [256c, 256c + 256)
-// of pair p: one thread per tile, one thread per group. The
-// records are built in LDS and stored by the whole block: 43,000 of them took
-// 19 us when each thread stored its own 176 bytes apart from the next one's, 6
-// now.
+// of pair p: one thread per tile, one thread per group.  The records are built in
+// LDS and stored by the whole block: 30,700 of them take 6 us, and took 19 when
+// each thread stored its own 176 bytes apart from the next one's.
 constexpr int kRangeThreads = 256;
 constexpr int kRangeTiles = kRangeThreads;
 static_assert(kRangeTiles % kMaxGroupTiles == 0, "a block holds whole groups");

@@ -8,7 +8,7 @@
 // first found enough, and one emission writes each pair's rows of both stages
 // one after the other in query order.  (With the counts back on the host
 // between the stages, a merge of both stages' rows and the rest of two calls,
-// 1,770 pairs took 947 us for 508 of matching; 733 now.)
+// 1,770 pairs took 947 us for 508 of matching; 680 so.)
 #include <algorithm>
 
 #include "sfm_internal.h"

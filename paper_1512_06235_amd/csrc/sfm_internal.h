@@ -21,9 +21,10 @@ constexpr int kScheduleInts = kTicketAt + kTicketStride * (kXcds * kCounters - 1
 constexpr int32_t kFewGroups = 1024;    // groups that run at once: four workgroups per CU
 // Launches of at most this many groups take a workgroup per group, in the order
 // they are dispatched, and no schedule.  (Against 1,024 resident workgroups that
-// draw their groups: 30 pairs, 1,912 groups, 107 / 118 us; 60 pairs, 3,650, 147 /
-// 153; 120 pairs, 6,874, 208 / 206; 500 pairs, 43,000, 561 / 534: there the next
-// group's first loads, which a resident workgroup issues early, count.)
+// draw their groups: 100 small pairs, 1,148 groups, 62 / 65 us; 30 pairs, 1,912,
+// 96 / 110; 60 pairs, 3,650, 131 / 140; 120 pairs, 6,874, 189 / 187; 500 pairs,
+// 30,697, 539 / 515: there the next group's first loads, which a resident
+// workgroup issues early, count.)
 constexpr int32_t kUnscheduledGroups = 4096;
 constexpr int kMaxGroupTiles = 8;       // query tiles sharing one candidate stream, at most
 constexpr int kDefaultGroupTiles = 8;   // the default (4 or 8: one or two tiles per wave)
