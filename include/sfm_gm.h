@@ -404,10 +404,10 @@ int sfm_get_tuning(sfm_ctx* ctx, int32_t* group_tiles, int32_t* features_per_bin
  * layout seen for the first time is launched directly, so callers whose
  * batches change every call pay no capture.  The copy of the pairs and F into
  * the workspace stays a stream copy.  Results are identical to stream
- * launches.  Measured on MI355X, replay is no faster than launching the
- * kernels on the stream (the 500-pair batch: 0.667 vs 0.660 ms; one 16k pair:
- * 0.132 vs 0.127 ms) and a capture costs a few milliseconds, hence off by
- * default.  Disabling frees the graph.  Profiling (sfm_set_profiling) uses
+ * launches.  Measured on MI355X, replay is slower than launching the kernels
+ * on the stream (the 500-pair batch: 0.528 vs 0.517 ms; one pair of 16,000
+ * features: 0.068 vs 0.062 ms, of 2,000: 0.033 vs 0.026 ms) and a capture
+ * costs a few milliseconds, hence off by default.  Disabling frees the graph.  Profiling (sfm_set_profiling) uses
  * stream launches. */
 int sfm_set_graph_replay(sfm_ctx* ctx, int32_t enable);
 
