@@ -591,6 +591,7 @@ bool direct_pays(const sfm_ctx* ctx, const PairDesc* pd, const double* F, int32_
     const sfm_ctx::Extent& X = ctx->extent[size_t(P.b)];
     const double w = std::max(1.0, double(X.bbox[2]) - double(X.bbox[0]));
     const double h = std::max(1.0, double(X.bbox[3]) - double(X.bbox[1]));
+    if (std::max(w, h) > kDirectMaxExtent) return false;
     LineDirection dir;
     const bool inside = epipole_near_box(F + 9 * size_t(k), X.bbox, P.band + kBandSlackPx, &dir);
     const double across = inside           ? std::min(w, h)

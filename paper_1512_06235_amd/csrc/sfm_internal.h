@@ -46,6 +46,11 @@ constexpr int kOuterBoxes = 16;         // boxes sharing an outer box
 constexpr int kOuterFeatures = kBoxFeatures * kOuterBoxes;
 constexpr int32_t kDirectMaxTargets = 65536;   // spatial positions fit 16 bits
 constexpr double kBandSlackPx = 1e-2;   // bin windows widen the band by this
+// Keypoint boxes wider or higher than this are not matched directly: the FP32
+// distance errs by a few roundings of half of it (6e-3 px), and once that reached
+// the windows' slack the direct form would take slots that the binned form's
+// windows leave out.
+constexpr double kDirectMaxExtent = 32768.0;
 constexpr int32_t kGroupStartCost = 48;  // schedule cost of starting a tile group
 constexpr int32_t kSegCost = 4;          // schedule cost of streaming one 64-position segment
 constexpr int32_t kStepCost = 2;         // schedule cost of one 16 x 16 step of one tile

@@ -150,6 +150,25 @@ def test_form_of_a_pair(sfm, n, band, direct):
     m.close()
 
 
+@pytest.mark.parametrize("ext, direct", [(3e4, True), (4e4, False), (6e7, False)])
+def test_vast_images_are_binned(sfm, ext, direct):
+    """Where the FP32 distance errs by more than the bin windows' slack, the two
+    forms would take different slots: boxes of more than 32,768 px are binned."""
+    from tests.fixtures import translation_F
+    rng = np.random.default_rng(197)
+    n = 900
+    along = np.array([1.0, 0.3]) / np.hypot(1.0, 0.3)
+    xa = rng.uniform(0, ext, (n, 2)).astype(np.float32)
+    xb = xa.astype(np.float64) + rng.uniform(-0.3, 0.3, (n, 1)) * ext * along \
+        + rng.uniform(-6, 6, (n, 1)) * [-along[1], along[0]]
+    xb = np.clip(xb, 0, ext)
+    images = [(xa, random_pair(n, 0, seed=11)[1]),
+              (xb.astype(np.float32), random_pair(n, 0, seed=12)[1])]
+    m = sfm.Matcher().register(images)
+    assert goes_direct(sfm, m, [(0, 1, 4.0)], [translation_F((1.0, 0.3, 0.0))]) == direct
+    m.close()
+
+
 EPIPOLES = {"inside": (300.0, 200.0, 1.0), "at infinity": (1.0, 0.3, 0.0), "vertical": (0.0, 1.0, 0.0),
             "just outside": (-40.0, 380.0, 1.0), "far": (5e7, 1e3, 1.0)}
 
