@@ -10,7 +10,8 @@
 // few trees per track.  Then an edge whose ends still have different roots hooks the
 // larger root under the smaller with a compare-and-swap; finds halve paths as
 // they go.  Parents only ever decrease, so paths terminate and each component's
-// root is its smallest node id: a label independent of the order of work.
+// root is its smallest node id: a label independent of the order of work.  Few
+// edges are left to the compare-and-swaps alone (kHookEdges).
 // (About 1 M edges over 0.5 M observations: hook 12 us, two label passes 18, union
 // 30.  Hooking roots from the start, the edges raced for them: 158 us.  The
 // union is bound by its link reads, four random words per edge, and the few
@@ -43,6 +44,10 @@ __global__ __launch_bounds__(256) void fill_i32_kernel(int32_t* p, int64_t n) {
 __device__ __forceinline__ int32_t load_link(const int32_t* p) {
   return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WAVEFRONT);
 }
+// The same past the caches, for walks that links of a moment ago shorten.
+__device__ __forceinline__ int32_t load_fresh(const int32_t* p) {
+  return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
 __device__ __forceinline__ void store_link(int32_t* p, int32_t v) {
   __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
@@ -74,12 +79,15 @@ __global__ __launch_bounds__(256) void uf_hook_kernel(int32_t* parent, const int
 
 // Root of x, halving the path on the way (each write replaces a parent by
 // one of its own ancestors, so concurrent finds and hooks stay consistent).
+// kFresh: links are read past the caches.
+template <bool kFresh>
 __device__ __forceinline__ int32_t uf_find(int32_t* parent, int32_t x) {
-  int32_t cur = load_link(&parent[x]);
+  auto load = [](const int32_t* p) { return kFresh ? load_fresh(p) : load_link(p); };
+  int32_t cur = load(&parent[x]);
   if (cur == x) return x;
   int32_t prev = x;
   int32_t next;
-  while (cur > (next = load_link(&parent[cur]))) {
+  while (cur > (next = load(&parent[cur]))) {
     store_link(&parent[prev], next);
     prev = cur;
     cur = next;
@@ -87,15 +95,20 @@ __device__ __forceinline__ int32_t uf_find(int32_t* parent, int32_t x) {
   return cur;
 }
 
+template <bool kFresh>
 __global__ __launch_bounds__(256) void uf_union_kernel(int32_t* parent, const int32_t* edges,
-                                                       int64_t n_edges, int64_t n_nodes) {
+                                                       int64_t n_edges, int64_t n_nodes,
+                                                       int32_t* err) {
+  auto load = [](const int32_t* p) { return kFresh ? load_fresh(p) : load_link(p); };
   for (int64_t k = int64_t(blockIdx.x) * blockDim.x + threadIdx.x; k < n_edges;
        k += int64_t(gridDim.x) * blockDim.x) {
     const int32_t u = edges[2 * k], v = edges[2 * k + 1];
-    if (u < 0 || v < 0 || int64_t(u) >= n_nodes || int64_t(v) >= n_nodes)
-      continue;   // flagged by the hook pass
-    if (load_link(&parent[u]) == load_link(&parent[v])) continue;   // one set already
-    int32_t ru = uf_find(parent, u), rv = uf_find(parent, v);
+    if (u < 0 || v < 0 || int64_t(u) >= n_nodes || int64_t(v) >= n_nodes) {
+      *err = 1;
+      continue;
+    }
+    if (load(&parent[u]) == load(&parent[v])) continue;   // one set already
+    int32_t ru = uf_find<kFresh>(parent, u), rv = uf_find<kFresh>(parent, v);
     while (ru != rv) {
       if (ru < rv) {
         const int32_t t = ru;
@@ -106,8 +119,8 @@ __global__ __launch_bounds__(256) void uf_union_kernel(int32_t* parent, const in
       // parent meanwhile: find both roots again.
       const int32_t old = atomicCAS(&parent[ru], ru, rv);
       if (old == ru) break;
-      ru = uf_find(parent, old);
-      rv = uf_find(parent, rv);
+      ru = uf_find<kFresh>(parent, old);
+      rv = uf_find<kFresh>(parent, rv);
     }
   }
 }
@@ -115,9 +128,18 @@ __global__ __launch_bounds__(256) void uf_union_kernel(int32_t* parent, const in
 // Root of x without writing: the labelling pass below must not use the
 // halving find, whose writes (an ancestor read before another thread stored
 // its node's root) could replace a finished label by a non-root ancestor.
+// Walks longer than eight links read them past the caches, where labels that
+// other threads have stored meanwhile cut them short (a chain of 20,000 nodes: 206
+// us for the whole call with cached links throughout, 79 so; chains of tens of
+// links, as tracks have, are as fast as with cached links).
 __device__ __forceinline__ int32_t uf_root(const int32_t* parent, int32_t x) {
   int32_t cur = x, next;
-  while (cur > (next = load_link(&parent[cur]))) cur = next;
+  for (int hops = 0; hops < 8; ++hops) {
+    next = load_link(&parent[cur]);
+    if (!(cur > next)) return cur;
+    cur = next;
+  }
+  while (cur > (next = load_fresh(&parent[cur]))) cur = next;
   return cur;
 }
 
@@ -283,18 +305,29 @@ int32_t blocks_for(int64_t n) {
 
 }  // namespace
 
+// Up to this many edges the hooks and their compression, two launches, cost more
+// than they spare the unions, whose links are then read past the caches: a match
+// graph of 497 edges takes 16 us without them and 22 with, chains of 1,000 nodes 26
+// to 50 and 29.  Above it the unions alone depend on the order of the edges (a
+// chain of 4,000 nodes: 43 to 323 us without, 45 to 47 with; match graphs of 4,255
+// edges: 20 and 22, of 19,637: 28 and 23, of 152,870: 64 and 26).
+constexpr int64_t kHookEdges = 1024;
+
 // The label array is the union-find's parent array.
 hipError_t launch_tracks(int64_t n_nodes, const int32_t* edges, int64_t n_edges, int32_t* label,
                          int32_t* err, hipStream_t st) {
   if (n_nodes <= 0) return hipSuccess;
   hipLaunchKernelGGL(uf_init_kernel, dim3(blocks_for(n_nodes)), dim3(256), 0, st, label, n_nodes);
-  if (n_edges > 0) {
+  if (n_edges > 0 && n_edges <= kHookEdges) {
+    hipLaunchKernelGGL(uf_union_kernel<true>, dim3(blocks_for(n_edges)), dim3(256), 0, st, label,
+                       edges, n_edges, n_nodes, err);
+  } else if (n_edges > 0) {
     const dim3 per_edge(blocks_for(n_edges)), per_node(blocks_for(n_nodes));
     hipLaunchKernelGGL(uf_hook_kernel, per_edge, dim3(256), 0, st, label, edges, n_edges, n_nodes,
                        err);
     hipLaunchKernelGGL(uf_label_kernel, per_node, dim3(256), 0, st, label, n_nodes);
-    hipLaunchKernelGGL(uf_union_kernel, per_edge, dim3(256), 0, st, label, edges, n_edges,
-                       n_nodes);
+    hipLaunchKernelGGL(uf_union_kernel<false>, per_edge, dim3(256), 0, st, label, edges, n_edges,
+                       n_nodes, err);
   }
   hipLaunchKernelGGL(uf_label_kernel, dim3(blocks_for(n_nodes)), dim3(256), 0, st, label, n_nodes);
   return hipGetLastError();

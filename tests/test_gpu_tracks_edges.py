@@ -102,3 +102,35 @@ def test_union_shapes(m, kind):
     sfm.sfm_tracks(m.ctx, n, torch.as_tensor(edges).cuda(), label)
     sfm.sfm_sync(m.ctx)
     assert np.array_equal(label.cpu().numpy(), tr.tracks(n, edges))
+
+
+@pytest.mark.parametrize("n_edges", [1, 2, 255, 256, 257, 1023, 1024, 1025])
+def test_few_edges_and_many(m, n_edges):
+    """Up to 1,024 edges go to the unions alone, more through hooks first: the
+    same labels, whatever the graph and the order of its edges."""
+    import torch
+    import paper_1512_06235_amd as sfm
+    rng = np.random.default_rng(n_edges)
+    n = n_edges + 1
+    i = np.arange(n_edges)
+    relabel = rng.permutation(n)
+    chain = np.stack([i, i + 1], 1)
+    graphs = {"chain": chain, "chain reversed": chain[::-1], "chain flipped": chain[:, ::-1],
+              "edges shuffled": rng.permutation(chain), "nodes shuffled": relabel[chain],
+              "star": np.stack([i, np.full(n_edges, n_edges)], 1),
+              "chains of nine": np.stack([i, np.where(i % 9 == 8, i, i + 1)], 1),
+              "random": rng.integers(0, n, (n_edges, 2))}
+    label = torch.empty(n, dtype=torch.int32, device="cuda")
+    for what, edges in graphs.items():
+        edges = np.ascontiguousarray(edges, np.int32)
+        sfm.sfm_tracks(m.ctx, n, torch.as_tensor(edges).cuda(), label)
+        sfm.sfm_sync(m.ctx)
+        assert np.array_equal(label.cpu().numpy(), tr.tracks(n, edges)), what
+    for bad in (-1, n):   # the other edges are still used, the bad one is reported
+        edges = np.ascontiguousarray(chain, np.int32)
+        edges[n_edges // 2, 1] = bad
+        with pytest.raises(sfm.SfmError):
+            sfm.sfm_tracks(m.ctx, n, torch.as_tensor(edges).cuda(), label)
+            sfm.sfm_sync(m.ctx)
+        rest = np.delete(edges, n_edges // 2, 0)
+        assert np.array_equal(label.cpu().numpy(), tr.tracks(n, rest))
